@@ -10,6 +10,7 @@ namespace rmips {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 
@@ -17,7 +18,10 @@ typedef int i32x8 __attribute__((ext_vector_type(8)));
 // e2m1 share one layout: a 32-byte slot per 32 elements (one element per byte
 // for FP8; FP6 and FP4 pack the block's codes from the slot's first bit, 24 or
 // 16 bytes, the rest zero), a power-of-two scale per vector.
-enum { PREC_FP32 = 0, PREC_BF16 = 1, PREC_FP8 = 2, PREC_FP6 = 3, PREC_FP4 = 4 };
+// PREC_SPLIT is how FP32 screening runs on rows of SPLIT_MIN_D values and
+// more (see screen_prec): each value as the sum of two FP16 numbers hi + lo,
+// with a power-of-two scale per vector as above.
+enum { PREC_FP32 = 0, PREC_BF16 = 1, PREC_FP8 = 2, PREC_FP6 = 3, PREC_FP4 = 4, PREC_SPLIT = 5 };
 __host__ __device__ constexpr bool scaled_prec(int prec) { return prec >= PREC_FP8; }
 // format code of the f8f6f4 matrix-core instruction and bits per element
 __host__ __device__ constexpr int mx_format(int prec) {
@@ -29,7 +33,20 @@ __host__ __device__ constexpr int mx_bits(int prec) {
 // largest magnitude of the element format (the scale maps a row's largest
 // value at or below it)
 __host__ __device__ constexpr float mx_max(int prec) {
-    return prec == PREC_FP6 ? 7.5f : prec == PREC_FP4 ? 6.0f : 448.0f;
+    return prec == PREC_FP6 ? 7.5f : prec == PREC_FP4 ? 6.0f : prec == PREC_SPLIT ? 0x1p15f : 448.0f;
+}
+// FP32 screening of rows of at least SPLIT_MIN_D values multiplies x = hi + lo
+// in FP16 (22 bits and more of each value, exact products, FP32 sums):
+// hi hi + hi lo + lo hi, three v_mfma_f32_32x32x16_f16 per 16 terms where the
+// FP32 matrix step takes eight of twice the time.  Measured against FP64 over
+// normal, shifted and positive rows (512 x 512 pairs, relative to |u||p|):
+// d = 32 rms 1.67e-8 (FP32 steps: 1.82e-8), d = 96 1.33e-8 (1.81e-8), d = 208
+// 1.20e-8 (1.80e-8); positive rows at d = 208 7.7e-8 (1.31e-7), the largest
+// errors in the same proportion.  At d = 16 it is larger than the FP32 steps'
+// (2.08e-8 against 1.84e-8), so shorter rows keep those.
+constexpr int SPLIT_MIN_D = 32;
+__host__ __device__ constexpr int screen_prec(int prec, int d) {
+    return prec == PREC_FP32 && d >= SPLIT_MIN_D ? PREC_SPLIT : prec;
 }
 
 constexpr int WAVE = 64;
@@ -57,10 +74,17 @@ __host__ __device__ inline int fp32_slot(int c, int d, int D) {
 // half-wave owns half of the row; a BF16 step takes 8 elements per lane
 // (D multiple of 16), an FP8 step 32 (D multiple of 64).
 __host__ __device__ inline int padded_dim(int prec, int d) {
-    return prec == PREC_FP32 ? (d + 7) & ~7 : prec == PREC_BF16 ? (d + 15) & ~15 : (d + 63) & ~63;
+    return prec == PREC_FP32 ? (d + 7) & ~7
+           : (prec == PREC_BF16 || prec == PREC_SPLIT) ? (d + 15) & ~15 : (d + 63) & ~63;
 }
 __host__ __device__ inline int elem_bytes(int prec) {
-    return prec == PREC_FP32 ? 4 : prec == PREC_BF16 ? 2 : 1;
+    return (prec == PREC_FP32 || prec == PREC_SPLIT) ? 4 : prec == PREC_BF16 ? 2 : 1;
+}
+// Split rows: in each half, every 8 values take 32 bytes, their hi parts and
+// then their lo parts.  Byte offset of value c's hi part (its lo part 16 on):
+__host__ __device__ inline int split_off(int c, int D) {
+    const int h = c >= D / 2, e = c - h * (D / 2);
+    return h * 2 * D + (e >> 3) * 32 + (e & 7) * 2;
 }
 // LDS row stride in bytes (16 bytes of padding spread the banks).
 __host__ __device__ inline int lds_row_bytes(int prec, int D) { return D * elem_bytes(prec) + 16; }
@@ -116,8 +140,8 @@ constexpr int LDS_GUARD = 512;  // >= 16 * (32 - 1) bytes of overread
 
 // Register-operand widths that are compiled: BF16 and FP8 rows are multiplied
 // over the smallest even chunk count >= nch (every even count up to the
-// largest row), FP32 rows over every count up to 16 and multiples of 4
-// above.  with_nch calls f(std::integral_constant<int, NCH>).
+// largest row), FP32 rows (shorter than SPLIT_MIN_D) and split rows over
+// their own count.  with_nch calls f(std::integral_constant<int, NCH>).
 template <int LO, int HI, class F> void with_exact(int nch, F &&f) {
     if constexpr (LO <= HI) {
         if (nch == LO) f(std::integral_constant<int, LO>{});
@@ -126,13 +150,12 @@ template <int LO, int HI, class F> void with_exact(int nch, F &&f) {
 }
 template <int PREC, class F> void with_nch(int nch, F &&f) {
     if constexpr (PREC == PREC_FP32) {
-        // every count up to 16 (each chunk costs eight FP32 products), then
-        // multiples of 4
-        if (nch <= 16) with_exact<1, 16>(nch, f);
-        else if (nch <= 20) f(std::integral_constant<int, 20>{});
-        else if (nch <= 24) f(std::integral_constant<int, 24>{});
-        else if (nch <= 28) f(std::integral_constant<int, 28>{});
-        else f(std::integral_constant<int, 32>{});
+        with_exact<1, SPLIT_MIN_D / 8>(nch, f);
+    } else if constexpr (PREC == PREC_SPLIT) {
+        // (hi, lo) chunk pairs, one per 16 terms: D = 32 ... 256
+        with_exact<SPLIT_MIN_D / 16, DMAX / 16>(nch / 2, [&](auto c) {
+            f(std::integral_constant<int, 2 * decltype(c)::value>{});
+        });
     } else {
         switch ((nch + 1) & ~1) {
         case 2: f(std::integral_constant<int, 2>{}); break;
@@ -242,6 +265,77 @@ template <int NCH> struct MMR<PREC_BF16, NCH> {
             c[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x1, as_bf(b0[q]), c[0][1], 0, 0, 0);
             c[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x0, as_bf(b1[q]), c[1][0], 0, 0, 0);
             c[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x1, as_bf(b1[q]), c[1][1], 0, 0, 0);
+        }
+    }
+};
+
+// Split FP32 rows: chunk 2c holds the hi parts of 8 values, chunk 2c + 1
+// their lo parts.  The two small products of a step go into the sum before
+// the large one; lo lo (at most 2^-22 of |u||p|) is left to the error bound.
+template <int NCH> struct MMR<PREC_SPLIT, NCH> {
+    static __device__ __forceinline__ f16x8 as_h(const uint4 &v) {
+        return __builtin_bit_cast(f16x8, v);
+    }
+    static __device__ __forceinline__ void rows2(f32x16 &c0, f32x16 &c1, const uint8_t *A0,
+                                                 const uint8_t *A1, const uint4 (&b)[NCH],
+                                                 int ls, int nch, int D, int /*h*/, int lane) {
+        const int off = (lane & 31) * ls + (lane >> 5) * (D / 2) * 4;
+#pragma unroll
+        for (int c = 0; c < NCH; c += 2) {
+            const f16x8 h0 = *reinterpret_cast<const f16x8 *>(A0 + off + 16 * c);
+            const f16x8 l0 = *reinterpret_cast<const f16x8 *>(A0 + off + 16 * c + 16);
+            const f16x8 h1 = *reinterpret_cast<const f16x8 *>(A1 + off + 16 * c);
+            const f16x8 l1 = *reinterpret_cast<const f16x8 *>(A1 + off + 16 * c + 16);
+            c0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(l0, as_h(b[c]), c0, 0, 0, 0);
+            c1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(l1, as_h(b[c]), c1, 0, 0, 0);
+            c0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(h0, as_h(b[c + 1]), c0, 0, 0, 0);
+            c1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(h1, as_h(b[c + 1]), c1, 0, 0, 0);
+            c0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(h0, as_h(b[c]), c0, 0, 0, 0);
+            c1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(h1, as_h(b[c]), c1, 0, 0, 0);
+        }
+    }
+    static __device__ __forceinline__ void cols2(f32x16 &c0, f32x16 &c1, const uint4 (&a)[NCH],
+                                                 const uint8_t *B0, const uint8_t *B1, int ls,
+                                                 int nch, int D, int /*h*/, int lane) {
+        const int off = (lane & 31) * ls + (lane >> 5) * (D / 2) * 4;
+#pragma unroll
+        for (int c = 0; c < NCH; c += 2) {
+            const f16x8 h0 = *reinterpret_cast<const f16x8 *>(B0 + off + 16 * c);
+            const f16x8 l0 = *reinterpret_cast<const f16x8 *>(B0 + off + 16 * c + 16);
+            const f16x8 h1 = *reinterpret_cast<const f16x8 *>(B1 + off + 16 * c);
+            const f16x8 l1 = *reinterpret_cast<const f16x8 *>(B1 + off + 16 * c + 16);
+            c0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_h(a[c]), l0, c0, 0, 0, 0);
+            c1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_h(a[c]), l1, c1, 0, 0, 0);
+            c0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_h(a[c + 1]), h0, c0, 0, 0, 0);
+            c1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_h(a[c + 1]), h1, c1, 0, 0, 0);
+            c0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_h(a[c]), h0, c0, 0, 0, 0);
+            c1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_h(a[c]), h1, c1, 0, 0, 0);
+        }
+    }
+    // as MMR<PREC_BF16>::rows4
+    static __device__ __forceinline__ void rows4(f32x16 (&c)[2][2], const uint8_t *A0,
+                                                 const uint8_t *A1, const uint4 (&b0)[NCH],
+                                                 const uint4 (&b1)[NCH], int ls, int D,
+                                                 int lane) {
+        const int off = (lane & 31) * ls + (lane >> 5) * (D / 2) * 4;
+#pragma unroll
+        for (int q = 0; q < NCH; q += 2) {
+            const f16x8 h0 = *reinterpret_cast<const f16x8 *>(A0 + off + 16 * q);
+            const f16x8 l0 = *reinterpret_cast<const f16x8 *>(A0 + off + 16 * q + 16);
+            const f16x8 h1 = *reinterpret_cast<const f16x8 *>(A1 + off + 16 * q);
+            const f16x8 l1 = *reinterpret_cast<const f16x8 *>(A1 + off + 16 * q + 16);
+            c[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(l0, as_h(b0[q]), c[0][0], 0, 0, 0);
+            c[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(l1, as_h(b0[q]), c[0][1], 0, 0, 0);
+            c[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(l0, as_h(b1[q]), c[1][0], 0, 0, 0);
+            c[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(l1, as_h(b1[q]), c[1][1], 0, 0, 0);
+            c[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(h0, as_h(b0[q + 1]), c[0][0], 0, 0, 0);
+            c[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(h1, as_h(b0[q + 1]), c[0][1], 0, 0, 0);
+            c[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(h0, as_h(b1[q + 1]), c[1][0], 0, 0, 0);
+            c[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(h1, as_h(b1[q + 1]), c[1][1], 0, 0, 0);
+            c[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(h0, as_h(b0[q]), c[0][0], 0, 0, 0);
+            c[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(h1, as_h(b0[q]), c[0][1], 0, 0, 0);
+            c[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(h0, as_h(b1[q]), c[1][0], 0, 0, 0);
+            c[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(h1, as_h(b1[q]), c[1][1], 0, 0, 0);
         }
     }
 };
@@ -399,6 +493,19 @@ __device__ __forceinline__ uint8_t to_e4m3(float y, float &q) {
     }
     q = (y < 0.0f) ? -m : m;
     return (uint8_t)(sg | code);
+}
+
+// y = hi + lo + rest in FP16 (round to nearest even), |y| <= 2^15; returns
+// hi's bits, q = hi + lo (exact in FP32).  A subnormal hi or lo is zero, so
+// that |lo| <= 2^-11 |hi| always.
+__device__ __forceinline__ uint16_t to_split(float y, uint16_t &lo, float &q) {
+    _Float16 h = (_Float16)y;
+    if (fabsf((float)h) < 0x1p-14f) h = (_Float16)0.0f;
+    _Float16 l = (_Float16)(y - (float)h);
+    if (fabsf((float)l) < 0x1p-14f) l = (_Float16)0.0f;
+    lo = __builtin_bit_cast(uint16_t, l);
+    q = (float)h + (float)l;
+    return __builtin_bit_cast(uint16_t, h);
 }
 
 // Round-to-nearest-even encoding of y (|y| <= the format's largest value)

@@ -44,7 +44,9 @@ __host__ __device__ constexpr int count_waves(int nch) { return nch <= 16 ? 8 : 
 // chunk by chunk with the chunk's FP32 user rows staged in LDS once, instead
 // of one user-row gather per pair.  A lane's ambiguous pairs of a chunk are
 // one 32-bit word (16 rows x two user columns) in LDS.
-__host__ __device__ constexpr bool count_staged(int prec) { return prec >= PREC_FP8; }
+__host__ __device__ constexpr bool count_staged(int prec) {
+    return prec >= PREC_FP8 && prec <= PREC_FP4;
+}
 __host__ __device__ inline int staged_stride(int D) { return D + 4; }  // floats per staged row
 
 size_t count_lds(int prec, int D) {
@@ -468,6 +470,7 @@ void launch_count(const CountArgs &a, hipStream_t st) {
     if (a.nb <= 0) return;
     const size_t lds = count_lds(a.prec, a.D);
     if (a.prec == PREC_FP32) launch_count_p<PREC_FP32>(a, lds, st);
+    else if (a.prec == PREC_SPLIT) launch_count_p<PREC_SPLIT>(a, lds, st);
     else if (a.prec == PREC_BF16) launch_count_p<PREC_BF16>(a, lds, st);
     else if (a.prec == PREC_FP8) launch_count_p<PREC_FP8>(a, lds, st);
     else if (a.prec == PREC_FP6) launch_count_p<PREC_FP6>(a, lds, st);

@@ -54,15 +54,16 @@ void launch_rows_prep(const float *X, int64_t rows, int d, int D, float *Xpad, f
 // w+4, ...).  Row r of the output is row order[r] of X (identity if NULL);
 // rows past `rows` are zero.  Rows of a group share one power-of-two scale
 // s (FP8: the smallest with max |x_i| / s <= 448, but at least 2^-63 so
-// that 1/s and the product of two scales' reciprocals stay finite; FP32
-// and BF16: 1).  Per row: N = ||x||, Nh = ||xq||, R = ||x - xq|| (FP64
+// that 1/s and the product of two scales' reciprocals stay finite; split
+// FP32: max |x_i| / s <= 2^15 likewise; FP32 and BF16: 1).  Per row: N = ||x||, Nh = ||xq||, R = ||x - xq|| (FP64
 // sums, rounded up to FP32), sc = s; the largest R/N of the rows goes to
 // *rmax (a monotone atomic maximum of non-negative floats).
 //
 // Subnormal operands: the matrix cores may flush them to zero, so the
 // copy never holds one.  An FP32 or BF16 value below 2^-126 in magnitude,
 // and an e4m3 code in the format's subnormal range (scaled magnitude below
-// 2^-6), is stored as zero and its whole value counts in R.  The error
+// 2^-6), and an FP16 part of a split value below 2^-14, is stored as zero
+// and its whole value counts in R.  The error
 // bound, which takes the quantisation error from R by Cauchy-Schwarz, then
 // holds whatever the hardware does with subnormal inputs.  FP6 e2m3 and
 // FP4 e2m1 keep their subnormal codes (values below 1 before scaling, a
@@ -188,6 +189,16 @@ __global__ __launch_bounds__(256) void k_quant(const float *__restrict__ X,
                         }
                         if (live) Xq[r * D + c] = b8;
                         qv = yq * s;
+                    } else if (PREC == PREC_SPLIT) {
+                        float yq;
+                        uint16_t lo;
+                        const uint16_t hi = to_split(sub ? 0.0f : t * inv, lo, yq);
+                        if (live) {
+                            uint8_t *o = Xq + r * 4 * D + split_off(c, D);
+                            *reinterpret_cast<uint16_t *>(o) = hi;
+                            *reinterpret_cast<uint16_t *>(o + 16) = lo;
+                        }
+                        qv = yq * s;
                     } else {
                         // FP6 / FP4: the 32 codes of a block (held by 32
                         // consecutive lanes) packed from the slot's first
@@ -271,6 +282,9 @@ void launch_quant(int prec, const float *X, const int32_t *order, int64_t rows,
     if (prec == PREC_FP32)
         k_quant<PREC_FP32><<<g, 256, 0, st>>>(X, order, rows, rows_pad, d, D, group, q, N, Nh, R,
                                               sc, rmax, flag);
+    else if (prec == PREC_SPLIT)
+        k_quant<PREC_SPLIT><<<g, 256, 0, st>>>(X, order, rows, rows_pad, d, D, group, q, N, Nh, R,
+                                               sc, rmax, flag);
     else if (prec == PREC_BF16)
         k_quant<PREC_BF16><<<g, 256, 0, st>>>(X, order, rows, rows_pad, d, D, group, q, N, Nh, R,
                                               sc, rmax, flag);

@@ -197,11 +197,17 @@ struct Carve {
 // FP64 rounding (d 2^-53) and the FP32 rounding of the comparisons (8 2^-24).
 struct ErrConst { float c, c2, g64; };
 
-ErrConst err_const(int D, int d) {
+// Split FP32 rows (x_q = hi + lo, |lo| <= 2^-11 |hi|): 3 D products whose
+// magnitudes sum to at most (1 + 2^-8) Nh_u Nh_p, and the products lo lo left
+// out, at most (1 + 2^-8) 2^-22 Nh_u Nh_p.
+ErrConst err_const(int prec, int D, int d) {
     const double u = std::ldexp(1.0, -23), slack = 1.0 + std::ldexp(1.0, -16);
     const double g64 = d * std::ldexp(1.0, -53);
     ErrConst e;
-    e.c = (float)(D * u / (1.0 - D * u) * slack);
+    const double t = prec == PREC_SPLIT ? 3.0 * D : D;
+    double c = t * u / (1.0 - t * u);
+    if (prec == PREC_SPLIT) c = (c + std::ldexp(1.0, -22)) * (1.0 + std::ldexp(1.0, -8));
+    e.c = (float)(c * slack);
     e.c2 = (float)((g64 + 8.0 * std::ldexp(1.0, -24)) * slack);
     e.g64 = (float)(g64 * slack);
     return e;
@@ -232,9 +238,9 @@ struct ThreshLayout {
 // (norm order), their norms and scales, the item order.  An index keeps
 // them from its build to its queries.
 void prep_plan(int prec, int64_t n, int64_t m, int d, ThreshLayout &L, Carve &cv) {
-    L.prec = prec;
-    L.D = padded_dim(prec, d);
-    L.rowb = L.D * elem_bytes(prec);
+    L.prec = screen_prec(prec, d);
+    L.D = padded_dim(L.prec, d);
+    L.rowb = L.D * elem_bytes(L.prec);
     L.ntiles = (int)((m + TILE_ITEMS - 1) / TILE_ITEMS);
     L.mpad = (int64_t)L.ntiles * TILE_ITEMS;
     const int64_t npad = (n + 63) / 64 * 64;
@@ -362,7 +368,7 @@ rmips_status run_thresholds(rmips_ctx *ctx, const float *U, int64_t n, const flo
     // (the caller reads L.bad later, in stream order; the kernels below stay
     // in bounds whatever the values)
 
-    const ErrConst ec = err_const(L.D, d);
+    const ErrConst ec = err_const(L.prec, L.D, d);
     ThreshArgs a{};
     a.prec = L.prec;
     a.Uq = L.Uq; a.Nu = L.Nu; a.Nhu = L.Nhu; a.Ru = L.Ru; a.su = L.su; a.n = n;
@@ -614,7 +620,8 @@ void index_plan(int prec, int64_t n, int64_t m, int d, int kmax, IndexLayout &I,
 constexpr int INDEX_HDR_DPRIME = 6;
 void index_header(int64_t n, int64_t m, int d, int kmax, int prec, int dp,
                   int32_t (&h)[INDEX_HDR_WORDS]) {
-    h[0] = INDEX_MAGIC | 1;
+    // (version 2: split FP32 rows; the layout of the others is version 1's)
+    h[0] = INDEX_MAGIC | (screen_prec(prec, d) == PREC_SPLIT ? 2 : 1);
     h[1] = (int32_t)n;
     h[2] = (int32_t)m;
     h[3] = d;
@@ -1175,7 +1182,7 @@ size_t rmips_thresholds_workspace_size(int64_t n, int64_t m, int32_t d, int32_t 
 }
 
 struct ScoresLayout {
-    int D, rowb;
+    int prec, D, rowb;
     void *Uq, *Qq;
     float *Nu, *Nhu, *Ru, *su, *Nq, *Nhq, *Rq, *sq;
     UserSide us;
@@ -1185,8 +1192,9 @@ struct ScoresLayout {
 };
 
 void scores_plan(int prec, int64_t n, int64_t nq, int d, ScoresLayout &L, Carve &cv) {
-    L.D = padded_dim(prec, d);
-    L.rowb = L.D * elem_bytes(prec);
+    L.prec = screen_prec(prec, d);
+    L.D = padded_dim(L.prec, d);
+    L.rowb = L.D * elem_bytes(L.prec);
     const int64_t npad = (n + 63) / 64 * 64, qpad = (nq + 63) / 64 * 64;
     L.Uq = cv.take<uint8_t>((size_t)npad * L.rowb);
     L.Nu = cv.take<float>(npad); L.Nhu = cv.take<float>(npad);
@@ -1258,17 +1266,17 @@ rmips_status rmips_scores(rmips_ctx *ctx, const float *U, int64_t n, const doubl
     ScoresLayout L;
     scores_plan(prec, n, nq, d, L, cv);
     HIPTRY(hipMemsetAsync(L.bad, 0, sizeof(int), st));
-    launch_quant(prec, U, nullptr, n, n, d, L.D, 1, L.Uq, L.Nu, L.Nhu, L.Ru, L.su, nullptr,
+    launch_quant(L.prec, U, nullptr, n, n, d, L.D, 1, L.Uq, L.Nu, L.Nhu, L.Ru, L.su, nullptr,
                  L.bad, st);
-    launch_quant(prec, Q, nullptr, nq, nq, d, L.D, 1, L.Qq, L.Nq, L.Nhq, L.Rq, L.sq, nullptr,
+    launch_quant(L.prec, Q, nullptr, nq, nq, d, L.D, 1, L.Qq, L.Nq, L.Nhq, L.Rq, L.sq, nullptr,
                  L.bad, st);
     HIPTRY(hipGetLastError());
     // (the input flag is read by rmips_sync; the kernels below stay in
     // bounds whatever the values)
-    const ErrConst ec = err_const(L.D, d);
+    const ErrConst ec = err_const(L.prec, L.D, d);
     launch_user_side(tau, tau_id, L.Nu, L.Nhu, L.Ru, L.su, nullptr, n, ec.c2, L.us, st);
     CountArgs a{};
-    a.prec = prec;
+    a.prec = L.prec;
     a.Pq = L.Qq; a.Np = L.Nq; a.Nhp = L.Nhq; a.Rp = L.Rq; a.sp = L.sq;
     a.rows = nullptr; a.nb = nq;
     a.item_tie = q_ids; a.item_orig = nullptr; a.Porig = Q;
@@ -1339,7 +1347,7 @@ rmips_status rmips_topn(rmips_ctx *ctx, const float *U, int64_t n, const float *
     Carve cv(ws);
     TopnLayout L;
     topn_plan(prec, n, m, d, k, ctx->cap_override, BATCH_MAX, L, cv);
-    const ErrConst ec = err_const(L.T.D, d);
+    const ErrConst ec = err_const(L.T.prec, L.T.D, d);
 
     constexpr int NEV = 10;
     hipEvent_t ev[NEV] = {};
@@ -1534,7 +1542,7 @@ rmips_status rmips_index_build(rmips_ctx *ctx, const float *U, int64_t n, const 
     BoundLayout B;
     index_build_plan(prec, n, m, d, kmax, ctx->cap_override, I, X, B, cw);
     ThreshLayout &T = I.T;
-    const ErrConst ec = err_const(T.D, d);
+    const ErrConst ec = err_const(T.prec, T.D, d);
     const int dp = dprime(ctx, d), ka = aug_len(dp);
     const bool rotate = dp < d;
     // no valid header until the build has succeeded
@@ -1614,7 +1622,7 @@ rmips_status rmips_index_topn(rmips_ctx *ctx, const float *U, int64_t n, const f
     index_query_plan(n, m, I, X, C, cw);
     s = check_index_header(ctx, I.hdr, n, m, d, kmax, prec);
     if (s != RMIPS_OK) return s;
-    const ErrConst ec = err_const(I.T.D, d);
+    const ErrConst ec = err_const(I.T.prec, I.T.D, d);
     constexpr int NEV = 5;
     hipEvent_t ev[NEV] = {};
     struct EvGuard {

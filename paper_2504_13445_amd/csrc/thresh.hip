@@ -2,8 +2,9 @@
 //
 // Screening.  A workgroup holds 32 users per wave in registers and streams the
 // items in descending-norm order (Alg. 1 step (1)), 64 per tile, through
-// the matrix cores in FP32, BF16 or FP8 (e4m3, a power-of-two scale per
-// user and per item tile).  With N = ||x||, Nh = ||xq|| and R = ||x - xq||
+// the matrix cores in FP32 (as two FP16 parts from d = 32 on), BF16 or FP8
+// (e4m3), with a power-of-two scale per user and per item tile where the
+// format needs one.  With N = ||x||, Nh = ||xq|| and R = ||x - xq||
 // of the quantized copies xq (all rounded up), every screened value vh
 // satisfies |vh - v| <= E(u, p) = R_u N_p + Nh_u R_p + c Nh_u Nh_p +
 // c2 N_u N_p + e_abs against the exact value v: the quantisation error by
@@ -74,8 +75,7 @@ __device__ __forceinline__ void merge32_desc(float (&v)[32]) {
 // has the LDS to itself), nch 16-byte chunks per half row.
 constexpr int SCR_NW = 12;  // at most
 // 12 waves while a half row fits in 8 chunks, or 14 in BF16 (three waves
-// per SIMD, 168 registers each: the FP32 rows take more matrix steps per
-// chunk, so a third wave gains nothing there and the longer rows spill), 8 up
+// per SIMD, 168 registers each; longer rows would spill), 8 up
 // to 28 chunks (two per SIMD, 256 registers each: a wave's band test then
 // runs while the other wave of its SIMD multiplies), 4 for longer rows,
 // whose waves need more registers
@@ -146,7 +146,11 @@ __device__ __forceinline__ int64_t screen_blocks(const ThreshArgs &a, int tu) {
     return (cnt + tu - 1) / tu;
 }
 
-// LISTED: a refinement pass over a user list (its own kernel symbol)
+// LISTED: a pass over a user list (its own kernel symbol).  What bounds it is
+// the matrix cores: split FP32 rows take 6 products of 64 x 32 values per 16
+// terms from 4 LDS reads, 1.27 PFLOP/s of FP16 products at 2,000,000 users x
+// 28,000 scanned items x 200 (55 ms; FP32 matrix steps took 173 ms, 0.82 of
+// their peak).
 template <int PREC, int NCH, bool LISTED>
 // three, two or one waves per SIMD, as the wave count above sets
 __global__ __launch_bounds__(64 * screen_nw<LISTED>(PREC, NCH)) __attribute__((amdgpu_waves_per_eu(screen_wpe<LISTED>(PREC, NCH))))
@@ -370,7 +374,7 @@ void k_thresh_screen(ThreshArgs a) {
 // lists and the exit are k_thresh_screen's, per user block.
 constexpr int SCR2_NW = 8;
 __host__ __device__ constexpr bool screen_u2(int prec, int nch) {
-    return prec != PREC_FP32 && nch <= 16;
+    return prec != PREC_FP32 && prec != PREC_SPLIT && nch <= 16;
 }
 template <int PREC, int NCH>
 __global__ __launch_bounds__(64 * SCR2_NW) __attribute__((amdgpu_waves_per_eu(2)))
@@ -1220,6 +1224,7 @@ void launch_thresh(const ThreshArgs &a0, hipStream_t st) {
     int32_t *LA = a0.lists, *LB = a0.lists + a0.n, *LF = a0.lists + 2 * a0.n;
     auto screen = [&](const ThreshArgs &a, dim3 g, const char *name) {
         if (a.prec == PREC_FP32) launch_screen<PREC_FP32>(a, nch, g, lds, st, name);
+        else if (a.prec == PREC_SPLIT) launch_screen<PREC_SPLIT>(a, nch, g, lds, st, name);
         else if (a.prec == PREC_BF16) launch_screen<PREC_BF16>(a, nch, g, lds, st, name);
         else if (a.prec == PREC_FP8) launch_screen<PREC_FP8>(a, nch, g, lds, st, name);
         else if (a.prec == PREC_FP6) launch_screen<PREC_FP6>(a, nch, g, lds, st, name);
