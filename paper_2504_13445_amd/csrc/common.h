@@ -58,6 +58,23 @@ constexpr int LDS_PAD = 4;        // floats added to an LDS row (bank spread)
 // products and sums that fall into the FP32 subnormal range.
 constexpr float E_ABS = 0x1p-99f;
 
+// Absolute slack of the Eq. (3) bound.
+constexpr float BOUND_ABS_SLACK = 0x1p-60f;
+
+// The largest float below t (t finite).  For y = rn(x), pred(y) <= x: the
+// subtraction in bound_thr is thus rounded down.
+__device__ __forceinline__ float float_pred(float t) {
+    const uint32_t b = __float_as_uint(t);
+    return __uint_as_float(t > 0.0f ? b - 1u : (t < 0.0f ? b + 1u : 0x80000001u));
+}
+
+// A user's threshold in the bound kernels: a pair's bound acc counts when
+// acc >= t = pred(tau_lo - slack), that is when pred(t) - acc is negative
+// (bound_bit).
+__device__ __forceinline__ float bound_thr(float tau_lo) {
+    return float_pred(float_pred(tau_lo - BOUND_ABS_SLACK));
+}
+
 // FP32 rows split at h = ceil(d / 2): values 0..h-1 open the first half
 // (D / 2 slots), values h..d-1 the second, each half padded with zeros at
 // its end, so that value slots 4c + q >= h of both halves are zero and their

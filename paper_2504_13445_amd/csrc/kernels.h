@@ -58,17 +58,14 @@ void launch_quant(int prec, const float *X, const int32_t *order, int64_t rows,
 // Per-user data of the counting stage, in an order given by `order`
 // (sorted position -> user id; NULL = identity).
 struct UserSide {
-    float *N;        // ||u|| rounded up
-    float *Nh;       // ||u_q|| (quantized copy) rounded up
-    float *R;        // ||u - u_q|| rounded up
     float *sinv;     // 1 / (power-of-two scale of the quantized copy), exact
-    float *tau_hi;   // tau rounded up to FP32
-    float *tau_lo;   // tau rounded down to FP32
+    float *tau_b;    // the bound kernels' threshold (see bound_thr)
     double *tau;     // exact tau
     int32_t *tau_id; // item id of the k-th element
     int32_t *uid;    // user id of this position
     // the fields the counting kernel needs per user, in one 16-byte record:
-    // {tau_hi, tau_lo, R + c2 N, Nh}; with the items' largest N, Nh, R the
+    // {tau rounded up, tau rounded down, R + c2 N, Nh} (N, Nh, R: the norms
+    // of the row, its copy and their difference); with the items' largest the
     // bound is E = (R + c2 N) N_p + Nh (R_p + c Nh_p) + e_abs
     float4 *thr;
 };
@@ -191,8 +188,7 @@ struct BoundArgs {
     int ka;                            // augmented row length 16 KS: KS <= 11, or even up to 18
     const uint4 *Pb; int64_t m, mpad;  // augmented item rows (norm order), BF16
     const uint4 *Ub;                   // augmented user rows (rho order), BF16
-    const float *tau_lo;               // per sorted user
-    float abs_slack;                   // absolute slack of the bound
+    const float *tau_b;                // per sorted user
     const int32_t *cs;                 // CS prefix per item (non-increasing)
     int nsplit; int32_t *partial;
     unsigned long long *pairs;         // stats: evaluated pairs (may be NULL)

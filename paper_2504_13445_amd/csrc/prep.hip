@@ -366,12 +366,8 @@ __global__ void k_user_side(const double *__restrict__ tau, const int32_t *__res
     if (r >= n) return;
     int64_t u = order ? order[r] : r;
     double t = tau[u];
-    out.N[r] = Nu[u];
-    out.Nh[r] = Nhu[u];
-    out.R[r] = Ru[u];
     out.sinv[r] = 1.0f / su[u];  // exact: su is a power of two
-    out.tau_hi[r] = __double2float_ru(t);
-    out.tau_lo[r] = __double2float_rd(t);
+    out.tau_b[r] = bound_thr(__double2float_rd(t));
     out.tau[r] = t;
     out.tau_id[r] = tau_id[u];
     out.uid[r] = (int32_t)u;

@@ -521,12 +521,8 @@ struct TopnLayout {
 };
 
 void user_side_plan(int64_t n, UserSide &us, Carve &cv) {
-    us.N = cv.take<float>(n);
-    us.Nh = cv.take<float>(n);
-    us.R = cv.take<float>(n);
     us.sinv = cv.take<float>(n);
-    us.tau_hi = cv.take<float>(n);
-    us.tau_lo = cv.take<float>(n);
+    us.tau_b = cv.take<float>(n);
     us.tau = cv.take<double>(n);
     us.tau_id = cv.take<int32_t>(n);
     us.uid = cv.take<int32_t>(n);
@@ -685,8 +681,8 @@ void run_prefix(const ThreshLayout &T, PrefixLayout &X, int64_t n, int64_t m, fl
 // the matrix cores included: the flushed terms of a row sum to at most
 // 2^-126 sqrt(ka) 1.42 * 2^60 < 2^-61, and products that underflow FP32 to
 // far less.
+// (BOUND_ABS_SLACK, taken off the threshold by bound_thr)
 constexpr float BOUND_SLACK = 0x1p-7f;
-constexpr float BOUND_ABS_SLACK = 0x1p-60f;
 
 // Stage (c), second part: the Eq. (3)/(6) bound count of every item (norm
 // order) into `uscore`, over the users of its prefix (users' augmented rows
@@ -699,8 +695,8 @@ void run_bound(const float *U, const PrefixLayout &X, const BoundLayout &B, cons
     launch_rotate_aug(U, X.uperm, n, n, d, Wd, dp, ka, BOUND_SLACK, B.Ua, st);
     BoundArgs ba{};
     ba.ka = ka;
-    ba.Pb = B.Pa; ba.m = m; ba.mpad = mpad; ba.Ub = B.Ua; ba.tau_lo = X.us.tau_lo;
-    ba.abs_slack = BOUND_ABS_SLACK; ba.cs = X.cs;
+    ba.Pb = B.Pa; ba.m = m; ba.mpad = mpad; ba.Ub = B.Ua; ba.tau_b = X.us.tau_b;
+    ba.cs = X.cs;
     ba.nsplit = B.nsplitB; ba.partial = B.partialB; ba.pairs = pairs;
     if (e0) (void)hipEventRecord(e0, st);
     launch_bound(ba, st);
@@ -747,8 +743,8 @@ hipError_t refine_segment(const Refine &R, CountLayout &C, int64_t r0, int64_t r
                       st);
     BoundArgs ba{};
     ba.ka = ka;
-    ba.Pb = R.B->Pa; ba.m = ns; ba.mpad = ns; ba.Ub = R.B->Ua; ba.tau_lo = R.X->us.tau_lo;
-    ba.abs_slack = BOUND_ABS_SLACK; ba.cs = C.sg_cs;
+    ba.Pb = R.B->Pa; ba.m = ns; ba.mpad = ns; ba.Ub = R.B->Ua; ba.tau_b = R.X->us.tau_b;
+    ba.cs = C.sg_cs;
     // few items: more splits of each block's users than the full pass takes,
     // within the partial counts' room
     const int64_t room = (int64_t)R.B->nsplitB * R.m / ns;

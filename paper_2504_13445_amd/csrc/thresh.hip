@@ -370,11 +370,12 @@ void k_thresh_screen(ThreshArgs a) {
 // formats, with two blocks of 32 users per wave: each item chunk read from
 // LDS feeds four products (two item blocks x two user blocks), half the LDS
 // reads per product of k_thresh_screen.  8 waves of 64 users (two per SIMD:
-// both users' half rows stay in registers).  The band test, the candidate
+// both users' half rows stay in registers; split FP32 rows fit without
+// spills up to 10 chunks, d = 80).  The band test, the candidate
 // lists and the exit are k_thresh_screen's, per user block.
 constexpr int SCR2_NW = 8;
 __host__ __device__ constexpr bool screen_u2(int prec, int nch) {
-    return prec != PREC_FP32 && prec != PREC_SPLIT && nch <= 16;
+    return prec == PREC_SPLIT ? nch <= 10 : prec != PREC_FP32 && nch <= 16;
 }
 template <int PREC, int NCH>
 __global__ __launch_bounds__(64 * SCR2_NW) __attribute__((amdgpu_waves_per_eu(2)))
