@@ -347,18 +347,43 @@ void launch_budget_range(const int32_t *users, const int32_t *pos, int64_t nuser
 }
 
 // Step (5) over those ranges, users sorted by the range's end (similar
-// ranges share a wave).  Per tile of S5_TILE positions the items' Eq. (3)
-// data sit in LDS and a wave's lanes (one user each) take the positions in
-// step.  lambda (Eq. 7) is the largest bound over a user's range (-inf if
-// empty).  An item counts for user u and every k with the bound >= A_u^k;
-// per position the wave counts its lanes for each k (ballots), keeping the
-// count for k in lane k - 1, and adds them to the tile's LDS table (row
-// k - 1, no two lanes on one entry).  The table goes to the difference
-// table diff (kmax x m, by item id) as differences of consecutive rows,
-// once per tile.  A^k is compared rounded down to FP32: a lower threshold
-// can only add counts, so uscore_k stays an upper bound (Theorem 3).
+// ranges share a wave).  lambda (Eq. 7) is the largest bound over a user's
+// range (-inf if empty).  An item counts for user u and every k with the
+// bound >= A_u^k, that is from one k0 on: one count in row k0 - 1 of the
+// difference table diff (kmax x m, by item id).  A^k is compared rounded down
+// to FP32: a lower threshold can only add counts, so uscore_k stays an upper
+// bound (Theorem 3).
+//
+// Each lane holds one user; the positions' Eq. (3) data are the same for a
+// wave and come through scalar loads, one position ahead.  A lane that an item
+// counts for adds one to the (position, k0) entry of the tile's LDS table,
+// which goes to diff once per tile of S5_TILE positions; the tiles of a block
+// of users are shared by gridDim.y workgroups (lambda then by an atomic
+// maximum), so that small user sets fill the chip too.  Vector work bounds it:
+// 16 FP64 and up to 2 kmax compare instructions per 64 pairs.  50k users x 10k
+// items, kmax = 25: 1.9 ms (one workgroup per 512 users for all their
+// positions, and a ballot per k for every position that counts: 19.8 ms).
 constexpr int S5_TILE = 256;
 constexpr int S5_THREADS = 512;
+// one position's Eq. (3) data (wave-uniform)
+struct S5Pos {
+    double pl[BUDGET_DP_MAX], nrp, npn;
+};
+typedef const __attribute__((address_space(4))) double *const_f64;
+template <bool FULL>  // dp == BUDGET_DP_MAX
+__device__ __forceinline__ S5Pos s5_load(const_f64 Pl, const_f64 nrp, const_f64 npn, int j,
+                                         int dp) {
+    S5Pos p;
+#pragma unroll
+    for (int t = 0; t < BUDGET_DP_MAX; ++t)
+        p.pl[t] = FULL ? Pl[(int64_t)j * BUDGET_DP_MAX + t]
+                       : (t < dp ? Pl[(int64_t)j * dp + t] : 0.0);
+    p.nrp = nrp[j];
+    p.npn = npn[j];
+    return p;
+}
+// NK: kmax rounded up to a multiple of 4
+template <int NK, bool FULL>
 __global__ __launch_bounds__(S5_THREADS) void k_budget_step5(
     const int32_t *__restrict__ users, const uint32_t *__restrict__ hi_pos,
     const int32_t *__restrict__ pos, int64_t nusers, const double *__restrict__ Av,
@@ -367,103 +392,117 @@ __global__ __launch_bounds__(S5_THREADS) void k_budget_step5(
     const double *__restrict__ nrp, const double *__restrict__ npn,
     const int32_t *__restrict__ order, int64_t m, int kmax, int dp, double *__restrict__ lam,
     int32_t *__restrict__ diff) {
-    __shared__ double t_pl[S5_TILE * BUDGET_DP_MAX];
-    __shared__ double t_nrp[S5_TILE], t_npn[S5_TILE];
-    __shared__ int32_t t_id[S5_TILE];
-    __shared__ int32_t cnt[KMAX * S5_TILE];
-    __shared__ int64_t s_lo, s_hi;
-    const int tid = threadIdx.x, lane = tid & 63;
+    constexpr int ST = NK + 1;  // table row stride (odd: a row's entries on distinct banks)
+    __shared__ int32_t cnt[S5_TILE * ST];
+    __shared__ int s_lo, s_hi;
+    const int tid = threadIdx.x;
     const int64_t w = (int64_t)blockIdx.x * S5_THREADS + tid;
     const bool valid = w < nusers;
-    int64_t u = 0, lo = INT64_MAX, hi = 0;
+    // positions [lo, hi), 1-based
+    int64_t u = 0;
+    int lo = INT32_MAX, hi = 0;
     if (valid) {
         u = users[w];
-        lo = (int64_t)pos[u] + 1;
-        hi = hi_pos[w];
+        lo = pos[u] + 1;
+        hi = (int)hi_pos[w];
     }
     if (tid == 0) {
-        s_lo = INT64_MAX;
+        s_lo = INT32_MAX;
         s_hi = 0;
     }
     __syncthreads();
-    if (valid && lo < hi) {
-        atomicMin((unsigned long long *)&s_lo, (unsigned long long)lo);
-        atomicMax((unsigned long long *)&s_hi, (unsigned long long)hi);
+    if (lo < hi) {
+        atomicMin(&s_lo, lo);
+        atomicMax(&s_hi, hi);
     }
     __syncthreads();
-    const int64_t blo = s_lo, bhi = s_hi;
+    const int blo = s_lo, bhi = s_hi;
+    // the wave's positions: the union of its lanes' ranges
+    int wlo = lo < hi ? lo : INT32_MAX, whi = lo < hi ? hi : 0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        wlo = min(wlo, __shfl_xor(wlo, o));
+        whi = max(whi, __shfl_xor(whi, o));
+    }
+    wlo = __builtin_amdgcn_readfirstlane(wlo);
+    whi = __builtin_amdgcn_readfirstlane(whi);
     double ul[BUDGET_DP_MAX];
 #pragma unroll
     for (int t = 0; t < BUDGET_DP_MAX; ++t) ul[t] = (valid && t < dp) ? Ul[u * dp + t] : 0.0;
     const double nr = valid ? nru[u] : 0.0, nn = valid ? nun[u] : 0.0;
-    float af[KMAX];
+    float af[NK];
 #pragma unroll
-    for (int r = 0; r < KMAX; ++r)
+    for (int r = 0; r < NK; ++r)
         af[r] = (valid && r < kmax) ? __double2float_rd(Av[u * kmax + r]) : -INFINITY;
     const double thk = valid ? Av[u * kmax + kmax - 1] : INFINITY;
+    const const_f64 cPl = (const_f64)(uintptr_t)Pl, cnrp = (const_f64)(uintptr_t)nrp,
+                    cnpn = (const_f64)(uintptr_t)npn;
     double best = -INFINITY;
-    for (int64_t t0 = blo; t0 < bhi; t0 += S5_TILE) {
-        const int tn = (int)min<int64_t>(S5_TILE, m + 1 - t0);
-        for (int i = tid; i < tn; i += S5_THREADS) {
-            const int64_t j = t0 + i - 1;  // 0-based position
-            t_id[i] = order[j];
-            t_nrp[i] = nrp[j];
-            t_npn[i] = npn[j];
-            for (int t = 0; t < dp; ++t) t_pl[i * BUDGET_DP_MAX + t] = Pl[j * dp + t];
-        }
-        for (int e = tid; e < kmax * S5_TILE; e += S5_THREADS) cnt[e] = 0;
+    for (int64_t t0 = blo + (int64_t)blockIdx.y * S5_TILE; t0 < bhi;
+         t0 += (int64_t)gridDim.y * S5_TILE) {
+        const int tb = (int)t0, te = (int)min<int64_t>(bhi, t0 + S5_TILE);
+        for (int e = tid; e < S5_TILE * ST; e += S5_THREADS) cnt[e] = 0;
         __syncthreads();
-        // the wave's positions: the union of its lanes' ranges in the tile
-        int64_t wa = valid ? max(lo, t0) : INT64_MAX, wb = valid ? min(hi, t0 + tn) : 0;
-        for (int o = 32; o > 0; o >>= 1) {
-            wa = min(wa, __shfl_xor(wa, o));
-            wb = max(wb, __shfl_xor(wb, o));
-        }
-        for (int64_t j = wa; j < wb; ++j) {
-            const int i = (int)(j - t0);
-            const bool act = valid && j >= lo && j < hi;
-            int k0 = KMAX + 1;
-            if (act) {
-                const double l =
-                    eq3_bound(ul, nr, nn, t_pl + i * BUDGET_DP_MAX, t_nrp[i], t_npn[i], dp);
-                best = fmax(best, l);
-                if (l >= thk) {
+        const int wa = max(wlo, tb), wb = min(whi, te);
+        if (wa < wb) {
+            S5Pos p = s5_load<FULL>(cPl, cnrp, cnpn, wa - 1, dp);
+            for (int j = wa; j < wb; ++j) {
+                // (the last position again past the end: in bounds)
+                const S5Pos nx = s5_load<FULL>(cPl, cnrp, cnpn, j + 1 < wb ? j : j - 1, dp);
+                const bool act = j >= lo && j < hi;
+                const double l = eq3_bound(ul, nr, nn, p.pl, p.nrp, p.npn, BUDGET_DP_MAX);
+                best = act ? fmax(best, l) : best;
+                const bool hit = act && l >= thk;
+                if (__ballot(hit) != 0ull) {
                     // af[r] > lf >= l: a lower count, so a smaller k0 (safe)
                     const float lf = __double2float_ru(l);
-                    k0 = 1;
+                    int k0 = 0;  // (k0 - 1)
 #pragma unroll
-                    for (int r = 0; r < KMAX; ++r) k0 += (af[r] > lf) ? 1 : 0;
+                    for (int r = 0; r < NK; ++r) k0 += (af[r] > lf) ? 1 : 0;
+                    if (hit) atomicAdd(&cnt[(j - tb) * ST + k0], 1);
                 }
+                p = nx;
             }
-            if (__ballot(k0 <= kmax) == 0) continue;
-            int mine = 0;
-            for (int k = 1; k <= kmax; ++k) {
-                const int c = __popcll(__ballot(k0 <= k));
-                if (lane == k - 1) mine = c;
-            }
-            if (lane < kmax && mine) atomicAdd(&cnt[lane * S5_TILE + i], mine);
         }
         __syncthreads();
         for (int e = tid; e < kmax * S5_TILE; e += S5_THREADS) {
             const int r = e / S5_TILE, i = e - r * S5_TILE;
-            const int c = cnt[e] - (r ? cnt[e - S5_TILE] : 0);
-            if (c && i < tn) atomicAdd(&diff[(int64_t)r * m + t_id[i]], c);
+            const int c = cnt[i * ST + r];
+            if (c) atomicAdd(&diff[(int64_t)r * m + order[tb + i - 1]], c);
         }
         __syncthreads();
     }
-    if (valid) lam[u] = best;
+    if (valid) {
+        if (gridDim.y == 1) lam[u] = best;
+        else if (best > -INFINITY) unsafeAtomicMax(&lam[u], best);
+    }
 }
 
+// lam must hold -inf for every user.
 void launch_budget_step5(const int32_t *users, const uint32_t *hi_pos, const int32_t *pos,
                          int64_t nusers, const double *Av, const double *Ul, const double *nru,
                          const double *nun, const double *Pl, const double *nrp,
                          const double *npn, const int32_t *order, int64_t m, int kmax, int dp,
                          double *lam, int32_t *diff, hipStream_t st) {
     if (nusers <= 0) return;
+    const int64_t blocks = (nusers + S5_THREADS - 1) / S5_THREADS;
+    // tiles shared out so that about 16 workgroups per compute unit are
+    // there whatever the user count (two are resident; four: 2.1 ms, 16: 1.9)
+    const int64_t tiles = (m + S5_TILE - 1) / S5_TILE;
+    const int64_t ys = std::max<int64_t>(1, std::min<int64_t>(tiles, (4096 + blocks - 1) / blocks));
+    const dim3 g((unsigned)blocks, (unsigned)ys);
     RMIPS_PROF(st, "k_budget_step5");
-    k_budget_step5<<<(unsigned)((nusers + S5_THREADS - 1) / S5_THREADS), S5_THREADS, 0, st>>>(
-        users, hi_pos, pos, nusers, Av, Ul, nru, nun, Pl, nrp, npn, order, m, kmax, dp, lam,
-        diff);
+    with_exact<1, KMAX / 4>((kmax + 3) / 4, [&](auto k4) {
+        constexpr int NK = 4 * decltype(k4)::value;
+        if (dp == BUDGET_DP_MAX)
+            k_budget_step5<NK, true><<<g, S5_THREADS, 0, st>>>(users, hi_pos, pos, nusers, Av, Ul,
+                                                               nru, nun, Pl, nrp, npn, order, m,
+                                                               kmax, dp, lam, diff);
+        else
+            k_budget_step5<NK, false><<<g, S5_THREADS, 0, st>>>(users, hi_pos, pos, nusers, Av, Ul,
+                                                                nru, nun, Pl, nrp, npn, order, m,
+                                                                kmax, dp, lam, diff);
+    });
 }
 
 // the first k entries of every list count for uscore_k: entry r counts for

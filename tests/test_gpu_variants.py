@@ -57,3 +57,42 @@ def test_split_rows(d, wide):
     ids, s, _ = rm.topn(_g(U), _g(P), k, 20)
     ri, rs = orc.topn_from_scores(sc, 20)
     assert ids.tolist() == ri.tolist() and s.tolist() == rs.tolist()
+
+
+# Step (5) of the budgeted build: d' = d for d <= 10 (its general and its full
+# width), so that the Eq. (3) bound is v plus 2^-30 |u||p| and rounding far
+# below that; list lengths around the multiples of 4 and user counts around
+# the workgroup's 512, with one and with several workgroups per tile range
+@pytest.mark.parametrize("n,m,d,kmax", [(1, 300, 10, 4), (511, 257, 10, 5), (512, 700, 7, 1),
+                                        (513, 1500, 10, 32), (1025, 513, 3, 9),
+                                        (700, 256, 10, 25)])
+def test_budget_step5(n, m, d, kmax):
+    _say("budget step 5", n, m, d, kmax)
+    rng = np.random.default_rng(n + m)
+    U = synth.isotropic(rng, n, d, 0.3)
+    P = synth.isotropic(rng, m, d, 0.5)
+    bi = _rm().BudgetIndex(_g(U), _g(P), kmax, kmax + 2, 3 * n, "exp")
+    g = {k: v.cpu().numpy() for k, v in bi.state().items()}
+    V = orc.inner_products_c(U, P)
+    nn = np.linalg.norm(U.astype(np.float64), axis=1)[:, None] * \
+        np.linalg.norm(P.astype(np.float64), axis=1)[None, :]
+    hi = V + 2.0 ** -29 * nn
+    posof = np.empty(m, np.int64)
+    posof[g["order"]] = np.arange(1, m + 1)
+    u2 = np.nonzero(g["pos"] > 0)[0]
+    lo_cnt, hi_cnt = np.zeros((kmax, m), np.int64), np.zeros((kmax, m), np.int64)
+    for u in u2:
+        # the range ends where |u||p| falls below the kmax-th value
+        rest = posof > g["pos"][u]
+        inr = rest & (nn[u] >= g["Av"][u, -1] * (1 + 1e-9))
+        if rest.any():
+            assert g["lam"][u] <= hi[u, rest].max()
+        if inr.any():
+            assert g["lam"][u] >= V[u, inr].max()
+        for k in range(kmax):
+            a = g["Av"][u, k]
+            lo_cnt[k] += inr & (V[u] >= a)
+            hi_cnt[k] += rest & (hi[u] >= a - 2.0 ** -22 * abs(a))
+    hist = np.stack([orc.histogram_scores(g["Aj"][:, :k + 1], m) for k in range(kmax)])
+    got = g["uscore"].astype(np.int64) - hist
+    assert np.all(got >= lo_cnt) and np.all(got <= hi_cnt)
