@@ -698,6 +698,20 @@ __device__ __forceinline__ uint32_t float_key(float f) {
     return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
 }
 
+// Sort keys of the pruning ratio rho_u = tau_u / ||u|| rounded down to FP32
+// (-inf where tau_u <= 0 or u = 0: such a user can hold any item) and of the
+// norm an item is compared with: a user is in the item's Cauchy-Schwarz
+// prefix when its key's bits from RHO_LO_BIT up are at most the item's.
+// (v <= (1 + d 2^-53) ||u|| ||p|| for the exact value; 2^-18 covers that and
+// the FP32 rounding of the product)
+constexpr int RHO_LO_BIT = 8;  // ratio key bits below this are not sorted on
+__device__ __forceinline__ uint32_t rho_key(double tau, float nu) {
+    return float_key(tau > 0.0 && nu > 0.0f ? __double2float_rd(tau / (double)nu) : -INFINITY);
+}
+__device__ __forceinline__ uint32_t norm_key(float np) {
+    return float_key(np * (1.0f + 0x1p-18f));
+}
+
 __device__ __forceinline__ float wave_min(float x) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) x = fminf(x, __shfl_xor(x, o));

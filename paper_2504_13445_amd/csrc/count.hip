@@ -981,6 +981,239 @@ __host__ __device__ constexpr int bound_items(int ks) {
     return ks >= 12 ? 16 * B16_TI * b16_waves(ks / 2) : ks >= 3 ? 64 * BLW : 32 * bound_tiles(ks);
 }
 
+// The bound counts for every k of a k_max table in one pass.  The product of
+// a pair is the same for every k; only the threshold and the prefix differ,
+// and both only admit more pairs as k grows.  So the pairs are tested against
+// the loosest pair of them (k = kmax), and the few that pass (0.4% at 100k
+// users x 20k items, kmax = 25) go to an LDS list, from which the whole
+// workgroup takes each with its value and finds its smallest k by bisection.
+// One pass per k, with its own order of the users, their rows in that order
+// and the sort behind it, took 25 x 0.25 ms there; this pass takes 0.44 ms.
+// Most of the pairs that pass belong to the items of the largest norms, so a
+// workgroup takes a few stages of one block only (4: 0.44 ms, 8: 0.67, a
+// sixteenth of the block's prefix: 3.7 ms).
+//
+// Products in the same steps and order as the pass per k (k_bound and
+// k_bound_lds, or k_bound16 from KS = 12 on), so that the counts agree to the
+// last pair.  8 waves of 64 (48) items; stages of bt_users(KS) users in LDS.
+constexpr int BT_CAP = 2048;             // listed pairs per workgroup
+constexpr int BT_CHUNK = 4;              // stages per workgroup, at least
+constexpr int BT_FLUSH = BT_CAP / 2;     // list length that triggers a flush between stages
+__host__ __device__ constexpr int bt_users(int ks) { return ks <= 11 ? 128 : 64; }
+__host__ __device__ constexpr int bt_items(int ks) { return 8 * (ks >= 12 ? 48 : 64); }
+constexpr size_t bt_lds_bytes(int ks) {
+    return 2 * (size_t)bt_users(ks) * ((2 * ks + 1) * 16 + 4) + BT_CAP * 12;
+}
+
+template <int KS>
+__global__ __launch_bounds__(64 * BLW) __attribute__((amdgpu_waves_per_eu(2)))
+void k_bound_table(BoundArgs a, BoundTableArgs bt) {
+    constexpr bool F16 = KS >= 12;  // 16x16x32 steps, 16-row tiles
+    constexpr int TI = F16 ? 3 : 2, RPW = F16 ? 48 : 64, BI = bt_items(KS);
+    constexpr int NQ = F16 ? KS / 2 : KS;      // steps per product
+    constexpr int NVAL = F16 ? 24 : 32;        // pairs per lane of a 32-user block
+    constexpr int RW = 2 * KS, LSL = RW + 1, SU = bt_users(KS);
+    constexpr int BLK = bound_items(KS);       // items sharing a prefix in the pass per k
+    extern __shared__ __align__(16) uint8_t smem_b[];
+    uint4 (*ush)[SU * LSL] = reinterpret_cast<uint4 (*)[SU * LSL]>(smem_b);
+    float (*tsh)[SU] = reinterpret_cast<float (*)[SU]>(smem_b + 2 * SU * LSL * 16);
+    float *lval = reinterpret_cast<float *>(tsh + 2);
+    int *lus = reinterpret_cast<int *>(lval + BT_CAP), *lrow = lus + BT_CAP;
+    __shared__ int ln, full[2];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int cl = F16 ? lane & 15 : lane & 31, part = F16 ? lane >> 4 : lane >> 5;
+    constexpr int NPART = F16 ? 4 : 2;  // row parts of a step held by different lanes
+    const int64_t ib = (int64_t)(blockIdx.x / a.nsplit) * BI;
+    // (the longest prefix among the blocks that these items belong to), in
+    // stages, of which this workgroup takes `chunk` ones
+    const int64_t ulen = a.cs[ib / BLK * BLK];
+    int64_t j = (int64_t)(blockIdx.x % a.nsplit) * bt.chunk;
+    const int64_t nblk = min<int64_t>((ulen + SU - 1) / SU, j + bt.chunk);
+    if (j >= nblk) return;
+    bf16x8 ah[TI][NQ];
+#pragma unroll
+    for (int t = 0; t < TI; ++t) {
+        const int64_t r = ib + RPW * w + (F16 ? 16 : 32) * t + cl;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            uint4 x = make_uint4(0, 0, 0, 0);
+            if (r < a.mpad) x = a.Pb[r * RW + NPART * q + part];
+            ah[t][q] = __builtin_bit_cast(bf16x8, x);
+        }
+    }
+    if (tid == 0) ln = 0;
+    const uint32_t magic = slot_magic(RW);
+    // stage j: users [SU j, SU (j + 1)) in groups of 64 rows (rows past the
+    // prefix repeat its last user) and their thresholds
+    auto stage = [&](int64_t j, int b) {
+#pragma unroll
+        for (int g = 0; g < SU / 64; ++g) {
+            const int64_t ug = j * SU + 64 * g;
+            const int64_t u0 = ug < ulen ? ug : ulen - 1;
+            const int64_t left = ulen - u0;
+            const int rlast = (int)((left < 64 ? left : 64) - 1);
+            rows_dma(reinterpret_cast<const uint8_t *>(a.Ub + u0 * RW), RW * 16, RW, magic, rlast,
+                     reinterpret_cast<uint8_t *>(ush[b] + 64 * g * LSL), w, BLW, lane);
+            if (w == BLW - 1) dma4(a.tau_b + u0 + (lane < rlast ? lane : rlast), tsh[b] + 64 * g);
+        }
+    };
+    // the smallest k of a pair that passed for kmax (or passed only because
+    // this workgroup's prefix is longer: no k), by bisection
+    auto take = [&](float v, int us, int row) {
+        const int64_t u = bt.uperm[us];
+        const double *tv = bt.topv + u * bt.kmax;
+        const float nu = bt.Nu[u];
+        const uint32_t x = norm_key(bt.Np[row / BLK * BLK]) >> RHO_LO_BIT;
+        int lo = 0, hi = bt.kmax;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            const double t = tv[mid];
+            const bool in = bound_thr(__double2float_rd(t)) - v < 0.0f &&
+                            (rho_key(t, nu) >> RHO_LO_BIT) <= x;
+            if (in) hi = mid; else lo = mid + 1;
+        }
+        if (lo < bt.kmax) atomicAdd(&bt.table[(int64_t)lo * a.m + row], 1);
+    };
+    auto flush = [&](int nq) {
+        for (int e = tid; e < nq; e += 64 * BLW) take(lval[e], lus[e], lrow[e]);
+    };
+    int buf = 0;
+    stage(j, 0);
+    dma_wait();
+    __syncthreads();
+    for (; j < nblk; ++j) {
+        const int64_t nx = j + 1;
+        if (nx < nblk) stage(nx, buf ^ 1);  // the other buffer was last read before the barrier
+        const int left = (int)min<int64_t>(ulen - j * SU, SU);
+#pragma unroll 1
+        for (int cb = 0; cb < SU / 32; ++cb) {
+            float v[NVAL];
+            uint32_t word = 0u;  // bit NVAL - 1 - e: value e counts for kmax
+            if constexpr (F16) {
+                f32x4 acc[TI][2];
+#pragma unroll
+                for (int t = 0; t < TI; ++t) acc[t][0] = acc[t][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int q = 0; q < NQ; ++q)
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) {
+                        const bf16x8 yb = __builtin_bit_cast(
+                            bf16x8, ush[buf][(32 * cb + 16 * c + cl) * LSL + NPART * q + part]);
+#pragma unroll
+                        for (int t = 0; t < TI; ++t)
+                            acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[t][q], yb,
+                                                                               acc[t][c], 0, 0, 0);
+                    }
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const int ul = 32 * cb + 16 * c + cl;
+                    const float x = tsh[buf][ul], tl = ul < left ? x : INFINITY;
+#pragma unroll
+                    for (int t = 0; t < TI; ++t)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            v[c * 4 * TI + t * 4 + i] = acc[t][c][i];
+                            bound_bit(word, tl, acc[t][c][i]);
+                        }
+                }
+            } else {
+                const int ul = 32 * cb + cl;
+                f32x16 acc[TI];
+#pragma unroll
+                for (int t = 0; t < TI; ++t) acc[t] = f32x16{0};
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+                    const bf16x8 yh =
+                        __builtin_bit_cast(bf16x8, ush[buf][ul * LSL + NPART * q + part]);
+#pragma unroll
+                    for (int t = 0; t < TI; ++t)
+                        acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[t][q], yh, acc[t], 0, 0, 0);
+                }
+                const float x = tsh[buf][ul], tl = ul < left ? x : INFINITY;
+#pragma unroll
+                for (int t = 0; t < TI; ++t)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        v[t * 16 + i] = acc[t][i];
+                        bound_bit(word, tl, acc[t][i]);
+                    }
+            }
+            while (word != 0u) {
+                const int e = NVAL - 1 - __builtin_ctz(word);
+                word &= word - 1u;
+                float x = v[0];
+#pragma unroll
+                for (int q = 1; q < NVAL; ++q) x = (e == q) ? v[q] : x;
+                int ul, rl;
+                if constexpr (F16) {
+                    const int c = e / (4 * TI), r = e % (4 * TI);
+                    ul = 32 * cb + 16 * c + cl;
+                    rl = 16 * (r >> 2) + 4 * part + (r & 3);
+                } else {
+                    ul = 32 * cb + cl;
+                    rl = 32 * (e >> 4) + mfma32_row(e & 15, lane);
+                }
+                const int64_t row = ib + RPW * w + rl;
+                if (row >= a.m) continue;  // padding rows
+                const int us = (int)(j * SU) + ul;
+                const int s = atomicAdd(&ln, 1);
+                if (s < BT_CAP) {
+                    lval[s] = x;
+                    lus[s] = us;
+                    lrow[s] = (int)row;
+                } else {
+                    take(x, us, (int)row);
+                }
+            }
+        }
+        // a half-full list is taken by the whole workgroup; one thread decides
+        // (the flag of a buffer is written again only two barriers on, while
+        // a fast wave may add to the list before a slow one has read it)
+        if (tid == 0) full[buf] = ln >= BT_FLUSH;
+        if (nx < nblk) dma_wait();
+        __syncthreads();
+        const bool fl = full[buf] != 0;
+        buf ^= 1;
+        if (fl) {
+            flush(ln < BT_CAP ? ln : BT_CAP);
+            __syncthreads();
+            if (tid == 0) ln = 0;
+            __syncthreads();
+        }
+    }
+    __syncthreads();
+    flush(ln < BT_CAP ? ln : BT_CAP);
+}
+
+// f(std::integral_constant<int, KS>) for ka = 16 KS: KS <= 11, or an even KS
+// up to 18 (rows past 176 terms are padded to a multiple of 32)
+template <class F> void with_ks(int ks, F &&f) {
+    switch (ks) {
+#define RMIPS_BOUND_KS(K) case K: f(std::integral_constant<int, K>{}); break;
+        RMIPS_BOUND_KS(1) RMIPS_BOUND_KS(2) RMIPS_BOUND_KS(3) RMIPS_BOUND_KS(4)
+        RMIPS_BOUND_KS(5) RMIPS_BOUND_KS(6) RMIPS_BOUND_KS(7) RMIPS_BOUND_KS(8)
+        RMIPS_BOUND_KS(9) RMIPS_BOUND_KS(10) RMIPS_BOUND_KS(11) RMIPS_BOUND_KS(12)
+        RMIPS_BOUND_KS(14) RMIPS_BOUND_KS(16)
+#undef RMIPS_BOUND_KS
+    default: f(std::integral_constant<int, 18>{}); break;
+    }
+}
+
+void launch_bound_table(const BoundArgs &a0, const BoundTableArgs &t0, int64_t n, hipStream_t st) {
+    RMIPS_PROF(st, "k_bound_table");
+    with_ks(a0.ka / 16, [&](auto ks) {
+        constexpr int KS = decltype(ks)::value, BI = bt_items(KS);
+        // chunks of users: at least BT_CHUNK stages each, at most about
+        // 32768 workgroups (those past a block's prefix end at once)
+        BoundArgs a = a0;
+        BoundTableArgs t = t0;
+        const int64_t blocks = (a.m + BI - 1) / BI, stages = (n + bt_users(KS) - 1) / bt_users(KS);
+        t.chunk = (int)std::max<int64_t>(BT_CHUNK, (stages * blocks + 32767) / 32768);
+        a.nsplit = (int)((stages + t.chunk - 1) / t.chunk);
+        k_bound_table<KS><<<(unsigned)(blocks * a.nsplit), 64 * BLW, bt_lds_bytes(KS), st>>>(a, t);
+    });
+}
+
 void launch_bound(const BoundArgs &a, hipStream_t st, const char *prof_name) {
     auto go = [&](auto ks) {
         constexpr int KS = decltype(ks)::value, BI = bound_items(KS);
@@ -995,17 +1228,7 @@ void launch_bound(const BoundArgs &a, hipStream_t st, const char *prof_name) {
             k_bound<KS><<<g, 64 * BW, 0, st>>>(a);
         }
     };
-    // ka = 16 KS: KS <= 11, or an even KS up to 18 (rows past 176 terms are
-    // padded to a multiple of 32)
-    switch (a.ka / 16) {
-#define RMIPS_BOUND_KS(K) case K: go(std::integral_constant<int, K>{}); break;
-        RMIPS_BOUND_KS(1) RMIPS_BOUND_KS(2) RMIPS_BOUND_KS(3) RMIPS_BOUND_KS(4)
-        RMIPS_BOUND_KS(5) RMIPS_BOUND_KS(6) RMIPS_BOUND_KS(7) RMIPS_BOUND_KS(8)
-        RMIPS_BOUND_KS(9) RMIPS_BOUND_KS(10) RMIPS_BOUND_KS(11) RMIPS_BOUND_KS(12)
-        RMIPS_BOUND_KS(14) RMIPS_BOUND_KS(16)
-#undef RMIPS_BOUND_KS
-    default: go(std::integral_constant<int, 18>{}); break;
-    }
+    with_ks(a.ka / 16, go);
 }
 
 // splits of each item block's user prefix: about 4096 workgroups, 1 to smax

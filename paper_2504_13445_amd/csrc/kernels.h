@@ -196,6 +196,22 @@ struct BoundArgs {
 void launch_bound(const BoundArgs &a, hipStream_t st, const char *prof_name = "k_bound");
 int bound_splits(int64_t m, int ka, int smax = 16);
 
+// Bound counts of every item for all k = 1 .. kmax at once: table row k0 - 1
+// (kmax x m, norm order, cleared before) gets the pairs whose smallest k is
+// k0, so that the prefix sums over the rows are the counts that launch_bound
+// gives for each k.  a: the rows, order, thresholds and prefixes of kmax (no
+// partial counts).
+struct BoundTableArgs {
+    const double *topv;    // users' kmax largest values, caller order
+    const int32_t *uperm;  // sorted position -> user
+    const float *Nu;       // ||u|| rounded up, caller order
+    const float *Np;       // ||p|| rounded up, norm order
+    int kmax;
+    int32_t *table;
+    int chunk;             // set by launch_bound_table: stages of users per workgroup
+};
+void launch_bound_table(const BoundArgs &a, const BoundTableArgs &t, int64_t n, hipStream_t st);
+
 // partial[s][j] summed over s (fixed order) -> out[j]
 void launch_colsum(const int32_t *partial, int nsplit, int64_t cols, int32_t *out,
                    hipStream_t st);

@@ -405,12 +405,7 @@ __global__ void k_rho_keys(const double *__restrict__ tau, const float *__restri
                            int64_t n, uint32_t *__restrict__ key, int32_t *__restrict__ val) {
     int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (u >= n) return;
-    double t = tau[u];
-    float nu = Nu[u];
-    float rho = -INFINITY;
-    // a user with tau <= 0 (or a zero vector) can hold any item: ratio -inf
-    if (t > 0.0 && nu > 0.0f) rho = __double2float_rd(t / (double)nu);
-    key[u] = float_key(rho);
+    key[u] = rho_key(tau[u], Nu[u]);
     val[u] = (int32_t)u;
 }
 
@@ -447,9 +442,7 @@ __global__ void k_cs_prefix(const uint32_t *__restrict__ keys, int64_t n,
                             int32_t *__restrict__ cs) {
     int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= m) return;
-    // v <= (1 + d 2^-53) ||u|| ||p|| for the exact value; 2^-18 covers that
-    // and the FP32 rounding of this product
-    const uint32_t x = float_key(norm[j] * (1.0f + 0x1p-18f)) >> lo_bit;
+    const uint32_t x = norm_key(norm[j]) >> lo_bit;
     int64_t lo = 0, hi = n;  // first position with a larger key
     while (lo < hi) {
         int64_t mid = (lo + hi) >> 1;

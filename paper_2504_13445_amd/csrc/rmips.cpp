@@ -160,7 +160,6 @@ int aug_len(int dp) {
 constexpr int T0_TILES = 6;             // tiles of phase 1 of stage (a)
 constexpr int BATCH_FIRST = 256;
 constexpr int BATCH_MAX = 4096;
-constexpr int RHO_LO_BIT = 8;  // ratio key bits below this are not sorted on
 constexpr int GRAM_SAMPLE = 16384;
 
 rmips_status fail(rmips_ctx *c, rmips_status s, const std::string &msg) {
@@ -1569,14 +1568,18 @@ rmips_status rmips_index_build(rmips_ctx *ctx, const float *U, int64_t n, const 
     const double *Wd = rotate ? I.W : nullptr;
     launch_rotate_aug(P, T.perm, m, T.mpad, d, Wd, dp, ka, 1.0f, B.Pa, st);
     launch_invert_perm(T.perm, m, I.inv, st);
-    // the bound of every item for each k: users in the rho order of that
-    // k's thresholds, one bound pass per k (row k - 1 of the table)
-    for (int k = 1; k <= kmax; ++k) {
-        launch_kth_column(I.topv, I.topk, n, kmax, k, X.tau, X.tau_id, st);
-        run_prefix(T, X, n, m, ec.c2, st, false);
-        run_bound(U, X, B, Wd, dp, n, m, T.mpad, d, nullptr, nullptr, nullptr,
-                  I.table + (size_t)(k - 1) * m, st);
-    }
+    // the bound of every item for every k: users in the rho order of kmax's
+    // thresholds, each counted pair in the row of its smallest k, then prefix
+    // sums over the rows
+    run_prefix(T, X, n, m, ec.c2, st, false);
+    launch_rotate_aug(U, X.uperm, n, n, d, Wd, dp, ka, BOUND_SLACK, B.Ua, st);
+    launch_fill_i32(I.table, (int64_t)kmax * m, 0, st);
+    BoundArgs ba{};
+    ba.ka = ka;
+    ba.Pb = B.Pa; ba.m = m; ba.mpad = T.mpad; ba.Ub = B.Ua; ba.tau_b = X.us.tau_b;
+    ba.cs = X.cs;
+    launch_bound_table(ba, {I.topv, X.uperm, T.Nu, T.Np, kmax, I.table, 0}, n, st);
+    launch_budget_prefix_k(I.table, m, kmax, st);
     HIPTRY(hipGetLastError());
     // the build waits for its work and reports its input check itself
     HIPTRY(hipMemcpyAsync(ctx->h_status, T.bad, sizeof(int), hipMemcpyDeviceToHost, st));

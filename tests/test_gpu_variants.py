@@ -96,3 +96,25 @@ def test_budget_step5(n, m, d, kmax):
     hist = np.stack([orc.histogram_scores(g["Aj"][:, :k + 1], m) for k in range(kmax)])
     got = g["uscore"].astype(np.int64) - hist
     assert np.all(got >= lo_cnt) and np.all(got <= hi_cnt)
+
+
+# The k_max table's bounds: one pass for every k must give the counts of the
+# pass per k (rmips_topn's bound_out of the same k, bound kernels of every row
+# length), around the item blocks (128, 384, 512, 576) and user stages (64, 128)
+@pytest.mark.parametrize("n,m,d,kmax", [(63, 130, 14, 3), (129, 513, 30, 32), (1000, 577, 33, 4),
+                                        (257, 385, 62, 25), (600, 1100, 110, 7),
+                                        (1025, 1153, 174, 5), (300, 700, 175, 9),
+                                        (513, 800, 222, 2), (777, 1200, 256, 6)])
+def test_index_bounds_all_k(n, m, d, kmax):
+    _say("index bounds", n, m, d, kmax)
+    rng = np.random.default_rng(n + d)
+    U = synth.isotropic(rng, n, d, 0.3)
+    P = synth.isotropic(rng, m, d, 0.6)
+    P[m // 2:m // 2 + 40] = P[:40]  # ties
+    U[0] = 0.0
+    rm = _rm()
+    ix = rm.Index(_g(U), _g(P), kmax)
+    for k in range(1, kmax + 1):
+        b = torch.empty(m, dtype=torch.int32, device=_dev())
+        rm.topn(_g(U), _g(P), k, 5, bound_out=b, prepass=0)
+        assert torch.equal(ix.bounds(k), b), k
