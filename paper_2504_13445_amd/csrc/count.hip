@@ -984,7 +984,7 @@ __host__ __device__ constexpr int bound_items(int ks) {
 // The bound counts for every k of a k_max table in one pass.  The product of
 // a pair is the same for every k; only the threshold and the prefix differ,
 // and both only admit more pairs as k grows.  So the pairs are tested against
-// the loosest pair of them (k = kmax), and the few that pass (0.4% at 100k
+// the loosest pair of them (k = kmax), and the few that pass (0.14% at 100k
 // users x 20k items, kmax = 25) go to an LDS list, from which the whole
 // workgroup takes each with its value and finds its smallest k by bisection.
 // One pass per k, with its own order of the users, their rows in that order

@@ -642,6 +642,14 @@ void index_query_plan(int64_t n, int64_t m, const IndexLayout &I, PrefixLayout &
     C.inv = I.inv;
 }
 
+// The k_max index takes the bounds of all k in one pass (launch_bound_table)
+// with d' = d, where few pairs pass the bound of kmax: 100k x 20k x 50, kmax =
+// 25, 0.14% of the pairs: build 7.8 -> 1.8 ms; 300k x 30k x 200, kmax = 3: 6.9 ->
+// 5.7 ms.  A rotation's bound lets too many pass (d' = 10 there: 33%, 6.5 ms by
+// passes per k, 49.9 ms by the one pass), and for one k the pass per k is the
+// shorter one (3.9 against 4.7 ms).
+constexpr int BOUND_TABLE_KMAX = 3;
+
 // splits of the user range of a counting launch: about four rounds of
 // counting workgroups (256 items each, one per compute unit), each split
 // with at least two 64-user chunks
@@ -1568,18 +1576,29 @@ rmips_status rmips_index_build(rmips_ctx *ctx, const float *U, int64_t n, const 
     const double *Wd = rotate ? I.W : nullptr;
     launch_rotate_aug(P, T.perm, m, T.mpad, d, Wd, dp, ka, 1.0f, B.Pa, st);
     launch_invert_perm(T.perm, m, I.inv, st);
-    // the bound of every item for every k: users in the rho order of kmax's
-    // thresholds, each counted pair in the row of its smallest k, then prefix
-    // sums over the rows
-    run_prefix(T, X, n, m, ec.c2, st, false);
-    launch_rotate_aug(U, X.uperm, n, n, d, Wd, dp, ka, BOUND_SLACK, B.Ua, st);
-    launch_fill_i32(I.table, (int64_t)kmax * m, 0, st);
-    BoundArgs ba{};
-    ba.ka = ka;
-    ba.Pb = B.Pa; ba.m = m; ba.mpad = T.mpad; ba.Ub = B.Ua; ba.tau_b = X.us.tau_b;
-    ba.cs = X.cs;
-    launch_bound_table(ba, {I.topv, X.uperm, T.Nu, T.Np, kmax, I.table, 0}, n, st);
-    launch_budget_prefix_k(I.table, m, kmax, st);
+    if (!rotate && kmax >= BOUND_TABLE_KMAX) {
+        // the bound of every item for every k: users in the rho order of
+        // kmax's thresholds, each counted pair in the row of its smallest k,
+        // then prefix sums over the rows
+        run_prefix(T, X, n, m, ec.c2, st, false);
+        launch_rotate_aug(U, X.uperm, n, n, d, Wd, dp, ka, BOUND_SLACK, B.Ua, st);
+        launch_fill_i32(I.table, (int64_t)kmax * m, 0, st);
+        BoundArgs ba{};
+        ba.ka = ka;
+        ba.Pb = B.Pa; ba.m = m; ba.mpad = T.mpad; ba.Ub = B.Ua; ba.tau_b = X.us.tau_b;
+        ba.cs = X.cs;
+        launch_bound_table(ba, {I.topv, X.uperm, T.Nu, T.Np, kmax, I.table, 0}, n, st);
+        launch_budget_prefix_k(I.table, m, kmax, st);
+    } else {
+        // users in the rho order of each k's thresholds, one bound pass per
+        // k (row k - 1 of the table)
+        for (int k = 1; k <= kmax; ++k) {
+            launch_kth_column(I.topv, I.topk, n, kmax, k, X.tau, X.tau_id, st);
+            run_prefix(T, X, n, m, ec.c2, st, false);
+            run_bound(U, X, B, Wd, dp, n, m, T.mpad, d, nullptr, nullptr, nullptr,
+                      I.table + (size_t)(k - 1) * m, st);
+        }
+    }
     HIPTRY(hipGetLastError());
     // the build waits for its work and reports its input check itself
     HIPTRY(hipMemcpyAsync(ctx->h_status, T.bad, sizeof(int), hipMemcpyDeviceToHost, st));

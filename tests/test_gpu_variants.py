@@ -104,7 +104,7 @@ def test_budget_step5(n, m, d, kmax):
 @pytest.mark.parametrize("n,m,d,kmax", [(63, 130, 14, 3), (129, 513, 30, 32), (1000, 577, 33, 4),
                                         (257, 385, 62, 25), (600, 1100, 110, 7),
                                         (1025, 1153, 174, 5), (300, 700, 175, 9),
-                                        (513, 800, 222, 2), (777, 1200, 256, 6)])
+                                        (513, 800, 222, 3), (777, 1200, 256, 6)])
 def test_index_bounds_all_k(n, m, d, kmax):
     _say("index bounds", n, m, d, kmax)
     rng = np.random.default_rng(n + d)
