@@ -698,6 +698,10 @@ __device__ __forceinline__ uint32_t float_key(float f) {
     return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
 }
 
+__device__ __forceinline__ float key_float(uint32_t k) {  // the inverse map
+    return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
+}
+
 // Sort keys of the pruning ratio rho_u = tau_u / ||u|| rounded down to FP32
 // (-inf where tau_u <= 0 or u = 0: such a user can hold any item) and of the
 // norm an item is compared with: a user is in the item's Cauchy-Schwarz

@@ -566,8 +566,8 @@ size_t final_entry_bytes() { return FIN_ENTRY_BYTES; }
 // recomputations per user handed from k_thresh_final to k_thresh_exact;
 // more, up to EXACT_WIDE, go to k_thresh_exact_wide
 constexpr int EXACT_SLOTS = 8;
-constexpr int EXACT_WIDE_J = 16;  // values per lane in k_thresh_exact_wide
-constexpr int EXACT_WIDE = 64 * EXACT_WIDE_J;
+constexpr int EXACT_WIDE = 2048;
+constexpr int EXACT_REGS = 1024;  // values ranked in registers
 
 // Orders this wave's LDS accesses (every list of the final selection is
 // private to one wave, so no workgroup barrier is needed).
@@ -606,48 +606,205 @@ __device__ __forceinline__ int dpp_wave_sum(int x) {
     return __builtin_amdgcn_readlane(x, 63);
 }
 
-// The k-th largest of x[0..n) counting repetitions (-inf when n < k), by
-// rounds of the largest value below the previous round's, each counted with
-// its repetitions, until k values are reached.  Lists of up to 64 KR values
-// are held in registers for the rounds (lane l: values l, l + 64, ...; the
-// -inf padding can only be counted once every value is taken, and then the
-// result is -inf anyway); longer ones are read from LDS in every round.
-constexpr int KTH_KR = 12;
-__device__ float wave_kth_largest(const float *x, int n, int k, int lane) {
-    float prev = INFINITY, v = -INFINITY;
-    int acc = 0;
-    if (n <= 64 * KTH_KR) {
-        float r[KTH_KR];
+__device__ __forceinline__ uint32_t dpp_wave_max_u32(uint32_t x) {
+    x = max(x, (uint32_t)dpp_from<0xB1, 0xf>(0, (int)x));
+    x = max(x, (uint32_t)dpp_from<0x4E, 0xf>(0, (int)x));
+    x = max(x, (uint32_t)dpp_from<0x141, 0xf>(0, (int)x));
+    x = max(x, (uint32_t)dpp_from<0x140, 0xf>(0, (int)x));
+    x = max(x, (uint32_t)dpp_from<0x142, 0xa>(0, (int)x));
+    x = max(x, (uint32_t)dpp_from<0x143, 0xc>(0, (int)x));
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+}
+
+// The k-th largest of the wave's keys (float_key; 0, below every float's, for
+// a slot that holds none), at least k of them: the largest key that k of them
+// reach, bit by bit from the first bit in which the smallest and the largest
+// differ, each bit decided by the number of keys that reach it (a compare and
+// a scalar population count per register).  Once exactly k keys are left they
+// are the k largest, and their smallest is the answer.
+template <int J>
+__device__ __forceinline__ uint32_t wave_kth_key(const uint32_t (&r)[J], int k) {
+    uint32_t mx = 0u, mn = 0u;  // mn: of the complements
 #pragma unroll
-        for (int j = 0; j < KTH_KR; ++j) r[j] = (lane + 64 * j < n) ? x[lane + 64 * j] : -INFINITY;
-        for (int rd = 0; rd < k && acc < k; ++rd) {
-            float mx = -INFINITY;
+    for (int j = 0; j < J; ++j) {
+        mx = max(mx, r[j]);
+        mn = max(mn, r[j] != 0u ? ~r[j] : 0u);
+    }
+    mx = dpp_wave_max_u32(mx);
+    mn = ~dpp_wave_max_u32(mn);
+    if (mx == mn) return mx;
+    int b = 31 - __builtin_clz(mx ^ mn);
+    uint32_t t = b == 31 ? 0u : mn & ~((2u << b) - 1u);  // the common prefix
+    for (; b >= 0; --b) {
+        const uint32_t c = t | (1u << b);
+        int cnt = 0;
 #pragma unroll
-            for (int j = 0; j < KTH_KR; ++j) mx = (r[j] < prev) ? fmaxf(mx, r[j]) : mx;
-            mx = dpp_wave_max(mx);
-            int c = 0;
+        for (int j = 0; j < J; ++j) cnt += __popcll(__ballot(r[j] >= c));
+        if (cnt >= k) t = c;
+        if (cnt == k) {
+            uint32_t m = 0u;
 #pragma unroll
-            for (int j = 0; j < KTH_KR; ++j) c += (r[j] == mx) ? 1 : 0;
-            acc += dpp_wave_sum(c);
-            prev = mx;
-            v = mx;
-        }
-    } else {
-        for (int rd = 0; rd < k && acc < k; ++rd) {
-            float mx = -INFINITY;
-            for (int e = lane; e < n; e += 64) {
-                const float y = x[e];
-                mx = (y < prev) ? fmaxf(mx, y) : mx;
-            }
-            mx = dpp_wave_max(mx);
-            int c = 0;
-            for (int e = lane; e < n; e += 64) c += (x[e] == mx) ? 1 : 0;
-            acc += dpp_wave_sum(c);
-            prev = mx;
-            v = mx;
+            for (int j = 0; j < J; ++j) m = max(m, r[j] >= c ? ~r[j] : 0u);
+            return ~dpp_wave_max_u32(m);
         }
     }
-    return acc >= k ? v : -INFINITY;
+    return t;
+}
+
+// The k-th largest of the list x[0..n) in LDS, counting repetitions (-inf
+// when n < k); lists past 1024 values are read again for every bit.
+template <int J>
+__device__ __forceinline__ float wave_kth_regs(const float *x, int n, int k, int lane) {
+    uint32_t r[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) r[j] = lane + 64 * j < n ? float_key(x[lane + 64 * j]) : 0u;
+    return key_float(wave_kth_key(r, k));
+}
+__device__ float wave_kth_largest(const float *x, int n, int k, int lane) {
+    if (n < k) return -INFINITY;
+    if (n <= 64) return wave_kth_regs<1>(x, n, k, lane);
+    if (n <= 128) return wave_kth_regs<2>(x, n, k, lane);
+    if (n <= 256) return wave_kth_regs<4>(x, n, k, lane);
+    if (n <= 512) return wave_kth_regs<8>(x, n, k, lane);
+    if (n <= 1024) return wave_kth_regs<16>(x, n, k, lane);
+    uint32_t t = 0u;
+    for (int b = 31; b >= 0; --b) {
+        const uint32_t c = t | (1u << b);
+        int cnt = 0;
+        for (int e = lane; e < n; e += 64) cnt += float_key(x[e]) >= c ? 1 : 0;
+        if (dpp_wave_sum(cnt) >= k) t = c;
+    }
+    return key_float(t);
+}
+
+// The selection where a user's lists hold at most SEL_MAX entries
+// (k_thresh_final takes the others): as k_thresh_final, but with the joined
+// list in registers (J entries per lane) from its load to the ids left for
+// the recomputation, so that no LDS limits the waves in flight.  Latency and
+// the selection's instructions bound it: 500k users, e4m3 lists of 429
+// entries 2.5 ms (in LDS, the k-th largest by rounds of the next largest:
+// 9.9 ms); BF16 lists of 32 entries 0.64 ms (0.72 ms).
+constexpr int SEL_MAX = 2048;
+// lists up to SEL_SHORT leave registers for four waves per SIMD, up to
+// SEL_MID (e4m3, k = 20) for three, longer ones for two
+constexpr int SEL_SHORT = 1024, SEL_MID = 1280;
+struct SelOut {
+    float Lstar;      // k-th largest lower bound of the stored entries (-inf: fewer than k)
+    int nrec, ns;     // entries left to recompute, survivors
+};
+template <int J>
+__device__ __forceinline__ SelOut select_regs(const ThreshArgs &a, int64_t u, int pre, int stored,
+                                              bool over, int lane) {
+    uint32_t lo[J], hi[J];  // keys of the bounds vh -/+ E, 0 past the end
+    int ci[J];
+#pragma unroll
+    for (int t = 0; t < J; ++t) {
+        // entry g of the joined list: split = number of inclusive prefixes <= g
+        const int g = 64 * t + lane;
+        int sp = 0, before = 0;
+        for (int q = 0; q < a.nsplit; ++q) {
+            const int pq = __builtin_amdgcn_readlane(pre, q);
+            if (pq <= g) {
+                sp = q + 1;
+                before = pq;
+            }
+        }
+        float2 cv = make_float2(0.0f, 0.0f);
+        ci[t] = 0;
+        if (g < stored) {
+            const int64_t e = (u * a.nsplit + sp) * a.cap + (g - before);
+            cv = a.cand[e];
+            ci[t] = a.cand_id[e];
+        }
+        lo[t] = g < stored ? float_key(cv.x - cv.y) : 0u;
+        hi[t] = g < stored ? float_key(cv.x + cv.y) : 0u;
+    }
+    SelOut o{-INFINITY, 0, 0};
+    const uint32_t L = stored >= a.k ? wave_kth_key(lo, a.k) : 0u;
+    if (stored >= a.k) o.Lstar = key_float(L);
+    if (over) return o;
+    // survivors: upper bound reaches L*; left to recompute: those whose lower
+    // bound is at most H_k, the k-th largest upper bound (all of them where
+    // the whole of S_k is asked for)
+#pragma unroll
+    for (int t = 0; t < J; ++t) {
+        if (hi[t] < L) hi[t] = 0u;
+        o.ns += __popcll(__ballot(hi[t] != 0u));
+    }
+    const uint32_t Hk = a.topk ? ~0u : wave_kth_key(hi, a.k);
+    const int64_t c0 = u * a.nsplit * (int64_t)a.cap;
+#pragma unroll
+    for (int t = 0; t < J; ++t) {
+        const bool unc = hi[t] != 0u && lo[t] <= Hk;
+        const uint64_t bal = __ballot(unc);
+        const int q = o.nrec + __popcll(bal & ((lane == 0) ? 0ull : (~0ull >> (64 - lane))));
+        // (every entry of the list is in a register by now)
+        if (unc) a.cand_id[c0 + q] = ci[t];
+        o.nrec += __popcll(bal);
+    }
+    return o;
+}
+
+template <int MAX>  // longest list
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MAX <= SEL_SHORT ? 4 : MAX <= SEL_MID ? 3 : 2)))
+void k_thresh_select(ThreshArgs a) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    const int64_t nlist = (int64_t)*a.ulist_cnt;
+    unsigned long long *cs = a.cstats ? a.cstats + (blockIdx.x & (CSTAT_SLOTS - 1)) * 4 : nullptr;
+    unsigned long long st_cand = 0, st_rec = 0;
+    const int64_t step = (int64_t)gridDim.x * nw;
+    int64_t pos = (int64_t)blockIdx.x * nw + w;
+    // the split counts of a user, one per lane, are read one user ahead
+    int64_t u = pos < nlist ? (int64_t)a.ulist[pos] : 0;
+    int cl = (pos < nlist && lane < a.nsplit) ? a.cand_cnt[u * a.nsplit + lane] : 0;
+    for (; pos < nlist; pos += step) {
+        const int64_t np = pos + step;
+        const int64_t un = np < nlist ? (int64_t)a.ulist[np] : 0;
+        const int cn = (np < nlist && lane < a.nsplit) ? a.cand_cnt[un * a.nsplit + lane] : 0;
+        const bool over = __ballot(cl > a.cap) != 0ull;
+        int pre = cl < a.cap ? cl : a.cap;  // inclusive prefix of the stored counts
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int y = __shfl_up(pre, o);
+            if (lane >= o) pre += y;
+        }
+        const int stored = __builtin_amdgcn_readlane(pre, 63);
+        SelOut o;
+        if (stored <= 64) o = select_regs<1>(a, u, pre, stored, over, lane);
+        else if (stored <= 128) o = select_regs<2>(a, u, pre, stored, over, lane);
+        else if (stored <= 256) o = select_regs<4>(a, u, pre, stored, over, lane);
+        else if (stored <= 512) o = select_regs<8>(a, u, pre, stored, over, lane);
+        else if (MAX == SEL_SHORT || stored <= SEL_SHORT)
+            o = select_regs<SEL_SHORT / 64>(a, u, pre, stored, over, lane);
+        else o = select_regs<MAX / 64>(a, u, pre, stored, over, lane);
+        if (over) {
+            // screened again from a tighter bound, or the exact fallback
+            if (lane == 0) {
+                const float Lprev = a.Luse[u];
+                const float Lnew = fmaxf(o.Lstar, Lprev);
+                if (a.rlist && Lnew > Lprev) {
+                    a.Luse[u] = Lnew;
+                    a.rlist[atomicAdd(a.rcnt, 1)] = (int)u;
+                    if (cs) atomicAdd(cs + 3, 1ull);
+                } else {
+                    a.flist[atomicAdd(a.fcnt, 1)] = (int)u;
+                    if (cs) atomicAdd(cs + 2, 1ull);
+                }
+            }
+        } else {
+            st_cand += (unsigned long long)stored;  // (no list overflowed)
+            st_rec += (unsigned long long)o.nrec;
+        }
+        // rank of tau among the values to recompute, and their count (-1: none)
+        if (lane == 0)
+            a.cand_cnt[u * a.nsplit] = over ? -1 : (a.k - 1 - (o.ns - o.nrec)) | (o.nrec << 8);
+        u = un;
+        cl = cn;
+    }
+    if (cs && lane == 0) {
+        if (st_cand) atomicAdd(cs, st_cand);
+        if (st_rec) atomicAdd(cs + 1, st_rec);
+    }
 }
 
 // One wave per user.  The lists of the user's splits are gathered into
@@ -924,172 +1081,350 @@ void k_thresh_final(ThreshArgs a, int capT, int capP) {
     }
 }
 
-// u . p (ip64's arithmetic, term by term) with the user's row staged in LDS
-// (ul, 16-byte aligned): 32 values of the item row per step, so that a
-// lane's loads of a step cover whole 128-byte blocks of it.  Rows that are
-// not 16-byte vectors go through ip64 with the user's row from memory.
-__device__ __forceinline__ double ip64_lds_user(const float *ul, const float *ug,
-                                                const float *__restrict__ p, int d) {
-    if ((d & 3) != 0 || (reinterpret_cast<uintptr_t>(p) & 15) != 0) return ip64<16>(ug, p, d);
-    constexpr int RV = 8;
-    const float4 *u4 = reinterpret_cast<const float4 *>(ul);
-    const float4 *p4 = reinterpret_cast<const float4 *>(p);
-    const int d4 = d >> 2;
+// Rows for exact products.  A lane's value is a sequential FP64 sum over its
+// own item row, but 64 lanes that each read their own row take 64 cache lines
+// per load, one a cycle: that, and not the memory behind it, bounded the
+// recomputations (L2 hit rate 0.98).  Here the wave copies a block of 32
+// values of all 64 rows into LDS with whole-line loads (8 lanes a row, 8 rows
+// a load; 32 lanes a row where rows are not whole aligned 16-byte vectors) and
+// each lane reads its row from there (the first nrows lanes' rows).  The rows are permuted within their 128
+// bytes so that the lanes' reads fall on distinct banks: 16-byte vector c of
+// row r lies at c ^ (r / 2 mod 8), single values e at e ^ (r mod 32).
+constexpr int XB = 32;             // values per block
+constexpr int XB_FLOATS = 64 * XB;  // LDS floats of a staged block
+template <bool VEC>
+__device__ __forceinline__ void stage_rows(const float *X, int row, int nrows, int d, int e0,
+                                           float *dst, int lane) {
+    if constexpr (VEC) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            if (8 * i >= nrows) break;
+            const int r = 8 * i + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
+            const int64_t src = __shfl(row, r);
+            const int e = e0 + 4 * c;  // (past the row: its last vector again)
+            dma16(X + src * d + (e < d ? e : d - 4), dst + 256 * i);
+        }
+    } else {
+#pragma unroll 8
+        for (int i = 0; i < 32; ++i) {
+            if (2 * i >= nrows) break;
+            const int r = 2 * i + (lane >> 5), c = (lane & 31) ^ (r & 31);
+            const int64_t src = __shfl(row, r);
+            const int e = e0 + c;
+            dma4(X + src * d + (e < d ? e : d - 1), dst + 64 * i);
+        }
+    }
+}
+template <bool VEC> __device__ __forceinline__ f32x4 staged_vec(const float *s, int row, int c) {
+    if constexpr (VEC)
+        return *reinterpret_cast<const f32x4 *>(s + row * XB + 4 * (c ^ ((row >> 1) & 7)));
+    f32x4 v;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = s[row * XB + ((4 * c + q) ^ (row & 31))];
+    return v;
+}
+// The exact value (ip64's arithmetic, term by term) of every lane's item row
+// (prow, staged in sp) and user row: row myr of the nu rows of U that lanes 0,
+// 1, ... name (urow), staged in ul, or (ONE) the one row ul of all lanes, in
+// LDS, 16-byte aligned.
+template <bool VEC, bool ONE>
+__device__ __forceinline__ double ip64_rows(const float *P, int prow, int nrows, const float *U,
+                                            int urow, int nu, int myr, float *ul, int d, float *sp,
+                                            int lane) {
     double acc = 0.0;
-    for (int i = 0; i < d4; i += RV) {
-        float4 y[RV];
+    for (int e0 = 0; e0 < d; e0 += XB) {
+        // the reads of the previous block are done before its place is written
+        __builtin_amdgcn_s_waitcnt(0xc07f);  // (LDS operations only)
+        wave_sync();
+        stage_rows<VEC>(P, prow, nrows, d, e0, sp, lane);
+        if constexpr (!ONE) stage_rows<VEC>(U, urow, nu, d, e0, ul, lane);
+        dma_wait();
+        wave_sync();
+        const int left = d - e0;
 #pragma unroll
-        for (int j = 0; j < RV; ++j) y[j] = p4[i + j < d4 ? i + j : d4 - 1];
+        for (int c = 0; c < XB / 4; ++c) {
+            if (4 * c >= left) break;
+            const f32x4 y = staged_vec<VEC>(sp, lane, c);
+            f32x4 x;
+            if constexpr (ONE) x = *reinterpret_cast<const f32x4 *>(ul + e0 + 4 * c);
+            else x = staged_vec<VEC>(ul, myr, c);
 #pragma unroll
-        for (int j = 0; j < RV; ++j) {
-            const bool ok = i + j < d4;
-            const float4 x = u4[ok ? i + j : d4 - 1];
-            acc = __fma_rn((double)(ok ? x.x : 0.f), (double)(ok ? y[j].x : 0.f), acc);
-            acc = __fma_rn((double)(ok ? x.y : 0.f), (double)(ok ? y[j].y : 0.f), acc);
-            acc = __fma_rn((double)(ok ? x.z : 0.f), (double)(ok ? y[j].z : 0.f), acc);
-            acc = __fma_rn((double)(ok ? x.w : 0.f), (double)(ok ? y[j].w : 0.f), acc);
+            for (int q = 0; q < 4; ++q)
+                if (VEC || 4 * c + q < left) acc = __fma_rn((double)x[q], (double)y[q], acc);
         }
     }
     return acc;
 }
+__device__ __forceinline__ bool rows_vec(const float *U, const float *P, int d) {
+    return (d & 3) == 0 &&
+           ((reinterpret_cast<uintptr_t>(U) | reinterpret_cast<uintptr_t>(P)) & 15) == 0;
+}
 
-// The recomputations left by k_thresh_final: EXACT_SLOTS lanes per user,
-// 64 / EXACT_SLOTS users per wave over the same list.  Lane q of a user with
-// n <= EXACT_SLOTS values to recompute takes the q-th id; the value of rank
-// tgt among the n, in the order (value desc, id asc), is tau_u.  Each user's
-// row is staged in LDS once for its lanes (workgroups of four waves).
+// The recomputations left by the selection, users with at most EXACT_SLOTS
+// values: a wave takes 64 users of the list, joins their values and computes
+// 64 of them at a time, one per lane; then lane u ranks user u's values: the
+// one of rank tgt in the order (value desc, id asc) is tau_u.  2M users x 200
+// with one value each 0.66 ms (8 lanes and their own loads per user: 1.45 ms).
+constexpr int EXACT_WAVES = 2;  // per workgroup (LDS: 24 KB per wave)
 template <bool LISTED>
-__global__ __launch_bounds__(256) void k_thresh_exact(ThreshArgs a) {
-    constexpr int UPW = 64 / EXACT_SLOTS;  // users per wave
-    __shared__ __align__(16) float urow_s[4][UPW][DMAX];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int grp = lane / EXACT_SLOTS, q = lane % EXACT_SLOTS;
-    const int nw = blockDim.x >> 6;
+__global__ __launch_bounds__(64 * EXACT_WAVES) void k_thresh_exact(ThreshArgs a) {
+    __shared__ __align__(16) float sp_s[EXACT_WAVES][XB_FLOATS], su_s[EXACT_WAVES][XB_FLOATS];
+    __shared__ double val_s[EXACT_WAVES][64 * EXACT_SLOTS];
+    __shared__ int id_s[EXACT_WAVES][64 * EXACT_SLOTS];
+    __shared__ uint8_t own_s[EXACT_WAVES][64 * EXACT_SLOTS];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int64_t nlist = LISTED ? (int64_t)*a.ulist_cnt : a.n;
-    for (int64_t b0 = ((int64_t)blockIdx.x * nw + w) * UPW; b0 < nlist;
-         b0 += (int64_t)gridDim.x * nw * UPW) {
-        const int64_t pos = b0 + grp;
-        const bool valid = pos < nlist;
-        const int64_t u = valid ? (LISTED ? (int64_t)a.ulist[pos] : pos) : 0;
-        const int meta = valid ? a.cand_cnt[u * a.nsplit] : -1;
+    const int64_t capU = (int64_t)a.nsplit * a.cap;
+    double *val = val_s[w];
+    int *ids = id_s[w];
+    uint8_t *own = own_s[w];
+    const bool vec = rows_vec(a.U, a.P, a.d);
+    for (int64_t b0 = ((int64_t)blockIdx.x * EXACT_WAVES + w) * 64; b0 < nlist;
+         b0 += (int64_t)gridDim.x * EXACT_WAVES * 64) {
+        const int64_t pos = b0 + lane;
+        int u = 0, meta = -1;
+        if (pos < nlist) {
+            u = LISTED ? a.ulist[pos] : (int)pos;
+            meta = a.cand_cnt[(int64_t)u * a.nsplit];
+        }
         // (longer lists are k_thresh_exact_wide's)
         const int nrec = (meta < 0 || (meta >> 8) > EXACT_SLOTS) ? 0 : meta >> 8;
-        const int tgt = meta & 255;
-        const bool have = q < nrec;
-        const float *ug = a.U + u * a.d;
-        float *ul = urow_s[w][grp];
-        wave_sync();  // the previous users' rows are no longer read
-        if (nrec > 0)
-            for (int i = q; i < a.d; i += EXACT_SLOTS) ul[i] = ug[i];
-        wave_sync();
-        int id = 0;
-        double v = 0.0;
-        if (have) {
-            id = a.cand_id[u * a.nsplit * (int64_t)a.cap + q];
-            v = ip64_lds_user(ul, ug, a.P + (int64_t)id * a.d, a.d);
-        }
-        // rank among the user's values: the lanes of its group
-        int rank = 0;
+        int off = nrec;  // inclusive prefix
 #pragma unroll
-        for (int j = 0; j < EXACT_SLOTS; ++j) {
-            const int src = grp * EXACT_SLOTS + j;
-            const double y = __shfl(v, src);
-            const int yi = __shfl(id, src);
-            rank += (j < nrec && ((y > v) || (y == v && yi < id))) ? 1 : 0;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int y = __shfl_up(off, o);
+            if (lane >= o) off += y;
         }
-        if (have && rank == tgt) {
-            a.tau[u] = v;
-            a.tau_id[u] = id;
+        const int total = __builtin_amdgcn_readlane(off, 63);
+        off -= nrec;
+        wave_sync();  // the previous users' lists are no longer read
+        for (int q = 0; q < nrec; ++q) {
+            ids[off + q] = a.cand_id[(int64_t)u * capU + q];
+            own[off + q] = (uint8_t)lane;
+        }
+        wave_sync();
+        for (int e0 = 0; e0 < total; e0 += 64) {
+            const int e = e0 + lane;
+            const int id = e < total ? ids[e] : 0;
+            // the users of these values: lanes o0 .. o0 + nu - 1
+            const int le = min(e0 + 63, total - 1);
+            const int o0 = __builtin_amdgcn_readfirstlane((int)own[e0]);
+            const int nu = __builtin_amdgcn_readfirstlane((int)own[le]) - o0 + 1;
+            const int ur = __shfl(u, min(o0 + lane, 63));
+            const int myr = (e < total ? own[e] : o0) - o0;
+            const int nr = total - e0;
+            const double v =
+                vec ? ip64_rows<true, false>(a.P, id, nr, a.U, ur, nu, myr, su_s[w], a.d, sp_s[w], lane)
+                    : ip64_rows<false, false>(a.P, id, nr, a.U, ur, nu, myr, su_s[w], a.d, sp_s[w], lane);
+            if (e < total) val[e] = v;
+        }
+        wave_sync();
+        const int tgt = meta & 255;
+        for (int q = 0; q < nrec; ++q) {
+            const double v = val[off + q];
+            const int id = ids[off + q];
+            int rank = 0;
+            for (int j = 0; j < nrec; ++j) {
+                const double y = val[off + j];
+                rank += (y > v || (y == v && ids[off + j] < id)) ? 1 : 0;
+            }
+            if (rank == tgt) {
+                a.tau[u] = v;
+                a.tau_id[u] = id;
+            }
+            if (a.topk && rank < a.k) a.topk[(int64_t)u * a.k + rank] = id;
+            if (a.topv && rank < a.k) a.topv[(int64_t)u * a.k + rank] = v;
         }
     }
 }
 
-// The recomputations of users with more than EXACT_SLOTS (at most
-// EXACT_WIDE) values: a wave per user, lane l computing values l, l + 64,
-// ... (up to EXACT_WIDE_J of them) into the wave's LDS slice; tau_u, the value
-// of rank tgt in the order (value desc, id asc), by tgt + 1 rounds of a
-// wave-wide maximum over the values not yet taken.  Each wave reads the
-// metadata of 64 users at a time and takes the wide ones in turn.
+// Sort key of a double (ascending; the sums never are -0 or NaN here).
+__device__ __forceinline__ uint64_t double_key(double x) {
+    const uint64_t b = (uint64_t)__double_as_longlong(x);
+    return (b >> 63) ? ~b : (b | 0x8000000000000000ull);
+}
+__device__ __forceinline__ double key_double(uint64_t k) {
+    return __longlong_as_double((long long)((k >> 63) ? (k & 0x7fffffffffffffffull) : ~k));
+}
+// The value of rank tgt (from 0) in the order (value desc, id asc) among the
+// wave's values, J per lane (key 0: none): the largest key that tgt + 1 keys
+// reach, bit by bit as in wave_kth_key, then the ids of the keys equal to it.
+template <int J>
+__device__ __forceinline__ void wave_rank64(const uint64_t (&r)[J], const int (&id)[J], int tgt,
+                                            double &v, int &vid) {
+    uint64_t t = 0;
+    int above = 0;  // keys larger than the answer
+    for (int b = 63; b >= 0; --b) {
+        const uint64_t c = t | (1ull << b);
+        int cnt = 0;
+#pragma unroll
+        for (int j = 0; j < J; ++j) cnt += __popcll(__ballot(r[j] >= c));
+        if (cnt > tgt) t = c;
+        else above = cnt;
+        if (cnt == tgt + 1) {
+            // exactly tgt + 1 keys: the smallest of them
+            uint64_t m = ~0ull;
+#pragma unroll
+            for (int j = 0; j < J; ++j) m = r[j] >= c ? min(m, r[j]) : m;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) m = min(m, (uint64_t)__shfl_xor((unsigned long long)m, o));
+            t = m;
+            int eq = 0;
+#pragma unroll
+            for (int j = 0; j < J; ++j) eq += __popcll(__ballot(r[j] == t));
+            above = tgt + 1 - eq;
+            break;
+        }
+    }
+    v = key_double(t);
+    // the (tgt - above)-th smallest id among the keys equal to t
+    int last = -1;
+    for (int q = above; q <= tgt; ++q) {
+        int m = 0x7fffffff;
+#pragma unroll
+        for (int j = 0; j < J; ++j) m = (r[j] == t && id[j] > last) ? min(m, id[j]) : m;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) m = min(m, __shfl_xor(m, o));
+        last = m;
+    }
+    vid = last;
+}
+
+// The recomputations of users with more than EXACT_SLOTS (at most EXACT_WIDE)
+// values: a wave per user, 64 values at a time (the user's row in LDS, the item
+// rows through stage_rows), more than 64 by way of the user's candidate slots;
+// tau_u by wave_rank64.  Each wave reads the metadata of its share of the list
+// (at most 64 users at a time) and takes the wide ones in turn.  500k users x
+// 100 with 156 values each 3.7 ms (each lane its own loads, the rank by rounds
+// of maxima: 6.9 ms).
 template <bool LISTED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
 void k_thresh_exact_wide(ThreshArgs a) {
+    __shared__ __align__(16) float sp_s[4][XB_FLOATS];
     __shared__ __align__(16) float urow_s[4][DMAX];
-    __shared__ double val_s[4][EXACT_WIDE];
-    __shared__ int id_s[4][EXACT_WIDE];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int nw = blockDim.x >> 6;
+    __shared__ double topv_s[4][KMAX];
+    __shared__ int topi_s[4][KMAX];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int64_t nlist = LISTED ? (int64_t)*a.ulist_cnt : a.n;
     const int64_t capU = (int64_t)a.nsplit * a.cap;
-    float *ul = urow_s[w];
-    double *vw = val_s[w];
-    int *iw = id_s[w];
-    for (int64_t c0 = ((int64_t)blockIdx.x * nw + w) * 64; c0 < nlist;
-         c0 += (int64_t)gridDim.x * nw * 64) {
+    float *ul = urow_s[w], *sp = sp_s[w];
+    const bool vec = rows_vec(a.U, a.P, a.d);
+    // users of a wave at a time: few when the list is short, so that it
+    // spreads over all waves
+    const int64_t waves = (int64_t)gridDim.x * 4;
+    const int per = (int)min<int64_t>(64, max<int64_t>(1, (nlist + waves - 1) / waves));
+    for (int64_t c0 = ((int64_t)blockIdx.x * 4 + w) * per; c0 < nlist; c0 += waves * per) {
         const int64_t pos = c0 + lane;
-        int64_t myu = 0;
-        int meta = -1;
-        if (pos < nlist) {
-            myu = LISTED ? (int64_t)a.ulist[pos] : pos;
-            meta = a.cand_cnt[myu * a.nsplit];
+        int myu = 0, meta = -1;
+        if (lane < per && pos < nlist) {
+            myu = LISTED ? a.ulist[pos] : (int)pos;
+            meta = a.cand_cnt[(int64_t)myu * a.nsplit];
         }
         uint64_t wide = __ballot(meta >= 0 && (meta >> 8) > EXACT_SLOTS);
         while (wide != 0ull) {
             const int src = __builtin_ctzll(wide);
             wide &= wide - 1ull;
-            // (wave-uniform)
-            const int64_t u = __builtin_amdgcn_readfirstlane((int)__shfl(myu, src));
-            const int mt = __builtin_amdgcn_readfirstlane(__shfl(meta, src));
+            const int64_t u = __builtin_amdgcn_readlane(myu, src);
+            const int mt = __builtin_amdgcn_readlane(meta, src);
             const int nrec = mt >> 8, tgt = mt & 255;
             const int32_t *ids = a.cand_id + u * capU;
+            double *slots = reinterpret_cast<double *>(a.cand + u * capU);
             const float *urow = a.U + u * a.d;
-            wave_sync();  // the previous user's row and values are no longer read
+            wave_sync();  // the previous user's row is no longer read
             for (int i = lane; i < a.d; i += 64) ul[i] = urow[i];
             wave_sync();
-            uint32_t avail = 0u;  // bit j: value lane + 64 j held and not yet taken
-            for (int j = 0; j < EXACT_WIDE_J && 64 * j < nrec; ++j) {
-                const int q = lane + 64 * j;
-                if (q < nrec) {
-                    const int id = ids[q];
-                    vw[q] = ip64_lds_user(ul, urow, a.P + (int64_t)id * a.d, a.d);
-                    iw[q] = id;
-                    avail |= 1u << j;
+            double v = 0.0;
+            int id = 0;
+            for (int q0 = 0; q0 < nrec; q0 += 64) {
+                const int q = q0 + lane;
+                id = q < nrec ? ids[q] : 0;
+                v = vec ? ip64_rows<true, true>(a.P, id, nrec - q0, nullptr, 0, 0, 0, ul, a.d, sp, lane)
+                        : ip64_rows<false, true>(a.P, id, nrec - q0, nullptr, 0, 0, 0, ul, a.d, sp, lane);
+                if (nrec > 64 && q < nrec) slots[q] = v;
+            }
+            double tv;
+            int ti;
+            // (each lane reads back only the values it wrote)
+            auto rank_of = [&](auto jc) {
+                constexpr int J = decltype(jc)::value;
+                uint64_t r[J];
+                int ri[J];
+#pragma unroll
+                for (int j = 0; j < J; ++j) {
+                    const int q = lane + 64 * j;
+                    r[j] = q < nrec ? double_key(J == 1 ? v : slots[q]) : 0ull;
+                    ri[j] = q < nrec ? (J == 1 ? id : ids[q]) : 0x7fffffff;
+                }
+                wave_rank64(r, ri, tgt, tv, ti);
+            };
+            if (nrec <= 64) {
+                rank_of(std::integral_constant<int, 1>{});
+            } else if (nrec <= 256) {
+                rank_of(std::integral_constant<int, 4>{});
+            } else if (nrec <= EXACT_REGS) {
+                rank_of(std::integral_constant<int, EXACT_REGS / 64>{});
+            } else {
+                // (rare) rounds of the next value in the order
+                tv = INFINITY;
+                ti = -1;
+                for (int r = 0; r <= tgt; ++r) {
+                    double bv = -INFINITY;
+                    int bi = 0x7fffffff;
+                    for (int q = lane; q < nrec; q += 64) {
+                        const double x = slots[q];
+                        const int xi = ids[q];
+                        if ((x < tv || (x == tv && xi > ti)) && (x > bv || (x == bv && xi < bi))) {
+                            bv = x;
+                            bi = xi;
+                        }
+                    }
+#pragma unroll
+                    for (int o = 32; o > 0; o >>= 1) {
+                        const double ov = __shfl_xor(bv, o);
+                        const int oi = __shfl_xor(bi, o);
+                        if (ov > bv || (ov == bv && oi < bi)) {
+                            bv = ov;
+                            bi = oi;
+                        }
+                    }
+                    tv = bv;
+                    ti = bi;
                 }
             }
-            // (each lane reads back only the values it wrote)
-            const int jn = (nrec + 63) / 64;
-            double bv = -INFINITY;
-            int bi = 0x7fffffff;
-            for (int r = 0; r <= tgt; ++r) {
-                // this lane's best value not yet taken, then the wave's
-                double lv = -INFINITY;
-                int li = 0x7fffffff, lj = -1;
-                for (int j = 0; j < jn; ++j) {
-                    if (!((avail >> j) & 1u)) continue;
-                    const double x = vw[lane + 64 * j];
-                    const int xi = iw[lane + 64 * j];
-                    if (lj < 0 || x > lv || (x == lv && xi < li)) {
-                        lv = x;
-                        li = xi;
-                        lj = j;
+            if (a.topk) {
+                // the k values up to tau in the order (tgt = k - 1), then
+                // their places among themselves
+                int nt = 0;
+                for (int q0 = 0; q0 < nrec; q0 += 64) {
+                    const int q = q0 + lane;
+                    const double x = q < nrec ? (nrec > 64 ? slots[q] : v) : -INFINITY;
+                    const int xi = q < nrec ? ids[q] : 0x7fffffff;
+                    const bool in = q < nrec && (x > tv || (x == tv && xi <= ti));
+                    const uint64_t bal = __ballot(in);
+                    const int p = nt + __popcll(bal & ((lane == 0) ? 0ull : (~0ull >> (64 - lane))));
+                    if (in) {
+                        topv_s[w][p] = x;
+                        topi_s[w][p] = xi;
                     }
+                    nt += __popcll(bal);
                 }
-                bv = lv;
-                bi = li;
-#pragma unroll
-                for (int o = 32; o > 0; o >>= 1) {
-                    const double ov = __shfl_xor(bv, o);
-                    const int oi = __shfl_xor(bi, o);
-                    if (ov > bv || (ov == bv && oi < bi)) {
-                        bv = ov;
-                        bi = oi;
+                wave_sync();
+                if (lane < a.k) {
+                    const double x = topv_s[w][lane];
+                    const int xi = topi_s[w][lane];
+                    int rank = 0;
+                    for (int j = 0; j < a.k; ++j) {
+                        const double y = topv_s[w][j];
+                        rank += (y > x || (y == x && topi_s[w][j] < xi)) ? 1 : 0;
                     }
+                    a.topk[u * a.k + rank] = xi;
+                    if (a.topv) a.topv[u * a.k + rank] = x;
                 }
-                // the ids are distinct: the lane holding the maximum takes it
-                if (lj >= 0 && li == bi) avail &= ~(1u << lj);
+                wave_sync();
             }
             if (lane == 0) {
-                a.tau[u] = bv;
-                a.tau_id[u] = bi;
+                a.tau[u] = tv;
+                a.tau_id[u] = ti;
             }
         }
     }
@@ -1216,12 +1551,10 @@ void launch_thresh(const ThreshArgs &a0, hipStream_t st) {
     const int64_t fres =
         256 * std::max<int64_t>(1, std::min<int64_t>(FIN_WPE * 4 / fw, (160 * 1024) / lds_fin));
     const int64_t fblocks = std::min<int64_t>((a0.n + fw - 1) / fw, fres);
-    // (four 4-wave workgroups per CU are resident)
-    const int64_t eblocks = std::min<int64_t>(
-        (a0.n + 4 * (64 / EXACT_SLOTS) - 1) / (4 * (64 / EXACT_SLOTS)), 4 * 256);
-    // a wave per 64 users of the list, four per workgroup, a few resident
-    // rounds
-    const int64_t wblocks = std::min<int64_t>((a0.n + 255) / 256, 8 * 256);
+    // (a wave per 64 users; three 2-wave workgroups per CU are resident)
+    const int64_t eblocks = std::min<int64_t>((a0.n + 64 * EXACT_WAVES - 1) / (64 * EXACT_WAVES), 6 * 256);
+    // one resident round (four 4-wave workgroups per CU)
+    const int64_t wblocks = std::min<int64_t>((a0.n + 3) / 4, 4 * 256);
     int32_t *LA = a0.lists, *LB = a0.lists + a0.n, *LF = a0.lists + 2 * a0.n;
     auto screen = [&](const ThreshArgs &a, dim3 g, const char *name) {
         if (a.prec == PREC_FP32) launch_screen<PREC_FP32>(a, nch, g, lds, st, name);
@@ -1239,13 +1572,20 @@ void launch_thresh(const ThreshArgs &a0, hipStream_t st) {
         ThreshArgs h = a;
         h.nsplit = 2 * a.nsplit;
         h.cap = a.cap / 2;
-        {
+        const unsigned sblocks = (unsigned)std::min<int64_t>((a0.n + 3) / 4, 4 * 256);
+        if (capT <= SEL_MAX) {
+            RMIPS_PROF(st, nf);
+            // one resident round
+            if (capT <= SEL_SHORT) k_thresh_select<SEL_SHORT><<<sblocks, 256, 0, st>>>(h);
+            else if (capT <= SEL_MID) k_thresh_select<SEL_MID><<<sblocks, 256, 0, st>>>(h);
+            else k_thresh_select<SEL_MAX><<<sblocks, 256, 0, st>>>(h);
+        } else {
             RMIPS_PROF(st, nf);
             k_thresh_final<true><<<(unsigned)fblocks, 64 * fw, lds_fin, st>>>(h, capT, capP);
         }
         {
             RMIPS_PROF(st, ne);
-            k_thresh_exact<true><<<(unsigned)eblocks, 256, 0, st>>>(h);
+            k_thresh_exact<true><<<(unsigned)eblocks, 64 * EXACT_WAVES, 0, st>>>(h);
         }
         RMIPS_PROF(st, nw);
         k_thresh_exact_wide<true><<<(unsigned)wblocks, 256, 0, st>>>(h);

@@ -118,3 +118,50 @@ def test_index_bounds_all_k(n, m, d, kmax):
         b = torch.empty(m, dtype=torch.int32, device=_dev())
         rm.topn(_g(U), _g(P), k, 5, bound_out=b, prepass=0)
         assert torch.equal(ix.bounds(k), b), k
+
+
+# Selection and recomputation by list length: nearly equal items keep every
+# candidate to the end, so that m sets the list (registers per lane, and the
+# lists past 1024 and 2048 entries) and the values to recompute (the users of
+# a wave joined up to 8 values, one wave per user to 64, 256, 1024 and more);
+# rows of whole 16-byte vectors and not, exact ties, S_k asked for and not
+@pytest.mark.parametrize("prec,m,d,k", [("fp32", 3, 20, 2), ("fp32", 9, 21, 9), ("fp32", 64, 36, 10),
+                                        ("bf16", 65, 33, 32), ("bf16", 200, 20, 10),
+                                        ("fp8", 257, 75, 1), ("fp8", 520, 40, 16),
+                                        ("fp8", 1000, 13, 10), ("fp8", 1200, 24, 20),
+                                        ("fp4", 1500, 20, 16), ("fp4", 2000, 31, 3),
+                                        ("fp6", 1900, 132, 4), ("fp4", 3000, 16, 32)])
+def test_selection_lengths(prec, m, d, k):
+    _say("selection", prec, m, d, k)
+    rng = np.random.default_rng(m)
+    n = 131
+    U = synth.isotropic(rng, n, d, 0.3)
+    base = synth.isotropic(rng, 1, d, 0.0)
+    P = (base + 1e-6 * rng.standard_normal((m, d))).astype(np.float32)
+    P[m // 2:m // 2 + m // 8] = P[:m // 8]  # exact ties
+    t, j, tk = orc.kmips_c(U, P, k)
+    for topk in (False, True):
+        r = _rm().thresholds(_g(U), _g(P), k, prec, with_topk=topk)
+        assert np.array_equal(r[0].cpu().numpy().view(np.uint64), t.view(np.uint64)), topk
+        assert np.array_equal(r[1].cpu().numpy(), j), topk
+        if topk:
+            assert np.array_equal(r[2].cpu().numpy(), tk)
+
+
+# The same with an unaligned catalogue (rows of whole vectors off 16 bytes)
+def test_recompute_unaligned_rows():
+    _say("unaligned rows")
+    rng = np.random.default_rng(5)
+    n, m, d, k = 300, 700, 24, 12
+    U = synth.isotropic(rng, n, d, 0.3)
+    P = synth.isotropic(rng, m, d, 0.1)
+    t, j, tk = orc.kmips_c(U, P, k)
+    buf = torch.zeros(m * d + 1, dtype=torch.float32, device=_dev())
+    Pg = buf[1:].view(m, d)
+    Pg.copy_(_g(P))
+    for prec in ("fp32", "fp8"):
+        tau, tid, topk = _rm().thresholds(_g(U), Pg, k, prec, with_topk=True)
+        assert np.array_equal(tau.cpu().numpy().view(np.uint64), t.view(np.uint64))
+        assert np.array_equal(tid.cpu().numpy(), j) and np.array_equal(topk.cpu().numpy(), tk)
+        tau, tid = _rm().thresholds(_g(U), Pg, k, prec)
+        assert np.array_equal(tau.cpu().numpy().view(np.uint64), t.view(np.uint64))
