@@ -50,10 +50,12 @@ void launch_gather_rows(const float *P, const int32_t *perm, const float *norm_b
 void launch_invert_perm(const int32_t *perm, int64_t m, int32_t *inv, hipStream_t st);
 
 // Padded, quantized copy of rows (see k_quant): Xq holds rows_pad rows of
-// D elements of the precision's type; group rows share a scale.
+// D elements of the precision's type; group rows share a scale.  tmax_nh and
+// tmax_r (may be NULL): the largest Nh and R of every 64 rows.
 void launch_quant(int prec, const float *X, const int32_t *order, int64_t rows,
                   int64_t rows_pad, int d, int D, int group, void *Xq, float *N, float *Nh,
-                  float *R, float *sc, unsigned int *rmax, int *flag, hipStream_t st);
+                  float *R, float *sc, unsigned int *rmax, float *tmax_nh, float *tmax_r,
+                  int *flag, hipStream_t st);
 
 // Per-user data of the counting stage, in an order given by `order`
 // (sorted position -> user id; NULL = identity).

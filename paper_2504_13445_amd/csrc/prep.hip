@@ -50,8 +50,7 @@ void launch_rows_prep(const float *X, int64_t rows, int d, int D, float *Xpad, f
                                                             val, flag);
 }
 
-// Padded, quantized copy of rows, 64 rows per block (wave w takes rows w,
-// w+4, ...).  Row r of the output is row order[r] of X (identity if NULL);
+// Padded, quantized copy of rows, 64 rows per block.  Row r of the output is row order[r] of X (identity if NULL);
 // rows past `rows` are zero.  Rows of a group share one power-of-two scale
 // s (FP8: the smallest with max |x_i| / s <= 448, but at least 2^-63 so
 // that 1/s and the product of two scales' reciprocals stay finite; split
@@ -70,9 +69,268 @@ void launch_rows_prep(const float *X, int64_t rows, int d, int D, float *Xpad, f
 // large part of a row with two exponent bits): the f8f6f4 instruction
 // decodes every code of both formats exactly on gfx950 (measured over all
 // codes, no difference from the decoded products).
-template <int PREC>
+//
+// 16 lanes take a row, four rows a wave at a time and 16 rows a wave in all,
+// every row's loads issued before the first is used: lane j the values 8j ..
+// 8j + 7 (and 128 further on past D = 128), two 16-byte loads and one or two
+// 16-byte stores, where the rows are whole aligned vectors (VEC), else the
+// values j, j + 16, ...  The row sums are four DPP steps for four rows at once.
+// Memory bounds it: 500k rows x 100 to BF16 0.10 ms (a wave per row, a value
+// per lane, six shuffled steps per row: 0.26 ms), 2M x 200 split 0.73 ms
+// (1.09 ms; 3.3 GB moved).
+template <int CTRL> __device__ __forceinline__ double dpp_row_f64(double x) {
+    const uint64_t b = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xf, 0xf, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xf, 0xf, false);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+// sum and maximum over the 16 lanes of a DPP row, in every lane (row_ror 8, 4, 2, 1)
+__device__ __forceinline__ double row16_sum(double x) {
+    x += dpp_row_f64<0x128>(x);
+    x += dpp_row_f64<0x124>(x);
+    x += dpp_row_f64<0x122>(x);
+    x += dpp_row_f64<0x121>(x);
+    return x;
+}
+template <int CTRL> __device__ __forceinline__ float dpp_row_f32(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float row16_max(float x) {
+    x = fmaxf(x, dpp_row_f32<0x128>(x));
+    x = fmaxf(x, dpp_row_f32<0x124>(x));
+    x = fmaxf(x, dpp_row_f32<0x122>(x));
+    return fmaxf(x, dpp_row_f32<0x121>(x));
+}
+// The smallest power of two s >= 2^-63 with m / s <= the format's largest value.
+template <int PREC> __device__ __forceinline__ float pow2_scale(float m) {
+    if (!(m > 0.0f)) return 1.0f;
+    constexpr float FMAX = mx_max(PREC);
+    int e;
+    frexpf(m / FMAX, &e);  // m/FMAX = f * 2^e, f in [0.5, 1)
+    float s = ldexpf(1.0f, e);
+    if (m / ldexpf(1.0f, e - 1) <= FMAX) s = ldexpf(1.0f, e - 1);
+    return fmaxf(s, 0x1p-63f);
+}
+
+// NG: 128-value parts of a row (D <= 128 NG)
+template <int PREC, int NG, bool VEC>
 __global__ __launch_bounds__(256) void k_quant(const float *__restrict__ X,
                                                const int32_t *__restrict__ order, int64_t rows,
+                                               int64_t rows_pad, int d, int D, int group,
+                                               uint8_t *__restrict__ Xq, float *__restrict__ N,
+                                               float *__restrict__ Nh, float *__restrict__ R,
+                                               float *__restrict__ sc,
+                                               unsigned int *__restrict__ rmax,
+                                               float *__restrict__ tmax_nh,
+                                               float *__restrict__ tmax_r,
+                                               int *__restrict__ flag) {
+    __shared__ float rowmax[64];
+    __shared__ float wmx[3][4];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int j16 = lane & 15, rq = lane >> 4;
+    const int64_t r0 = (int64_t)blockIdx.x * 64;
+    // value e of part p of this lane's share of a row
+    auto col = [&](int p, int e) { return 128 * p + (VEC ? 8 * j16 + e : 16 * e + j16); };
+    float v[4][NG][8];
+    bool bad = false;
+    float mx[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        const int64_t r = r0 + 16 * g + 4 * w + rq;
+        const int64_t src = r < rows ? (order ? (int64_t)order[r] : r) : -1;
+        const float *x = X + (src >= 0 ? src : 0) * d;
+#pragma unroll
+        for (int p = 0; p < NG; ++p) {
+            if constexpr (VEC) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int c = col(p, 4 * h);
+                    const float4 t = (src >= 0 && c < d) ? *reinterpret_cast<const float4 *>(x + c)
+                                                         : make_float4(0.f, 0.f, 0.f, 0.f);
+                    v[g][p][4 * h] = t.x;
+                    v[g][p][4 * h + 1] = t.y;
+                    v[g][p][4 * h + 2] = t.z;
+                    v[g][p][4 * h + 3] = t.w;
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int c = col(p, e);
+                    v[g][p][e] = (src >= 0 && c < d) ? x[c] : 0.0f;
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        mx[g] = 0.0f;
+#pragma unroll
+        for (int p = 0; p < NG; ++p)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                bad |= !isfinite(v[g][p][e]);
+                mx[g] = fmaxf(mx[g], fabsf(v[g][p][e]));
+            }
+    }
+    if (__ballot(bad) != 0ull && lane == 0) *flag = 1;
+    if constexpr (scaled_prec(PREC)) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) mx[g] = row16_max(mx[g]);
+        if (group > 1) {  // rows of a group share a scale
+            if (j16 == 0)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) rowmax[16 * g + 4 * w + rq] = mx[g];
+            __syncthreads();
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int g0 = (16 * g + 4 * w + rq) / group * group;
+                float m = 0.0f;
+                for (int t = g0; t < g0 + group && t < 64; ++t) m = fmaxf(m, rowmax[t]);
+                mx[g] = m;
+            }
+        }
+    }
+    float rrmax = 0.0f, nhmax = 0.0f, rmxv = 0.0f;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        const int64_t r = r0 + 16 * g + 4 * w + rq;
+        const bool live = r < rows_pad;
+        const float s = scaled_prec(PREC) ? pow2_scale<PREC>(mx[g]) : 1.0f;
+        const float inv = 1.0f / s;  // exact: s is a power of two
+        double sx = 0.0, sq = 0.0, sr = 0.0;
+#pragma unroll
+        for (int p = 0; p < NG; ++p) {
+            uint32_t code[8], lo[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float t = v[g][p][e];
+                // (values below 2^-126 are zero in the copy)
+                const bool sub = fabsf(t) < 0x1p-126f;
+                float qv;
+                lo[e] = 0u;
+                if constexpr (PREC == PREC_FP32) {
+                    qv = sub ? 0.0f : t;
+                    code[e] = __float_as_uint(qv);
+                } else if constexpr (PREC == PREC_BF16) {
+                    code[e] = to_bf16(t, qv);
+                    if (sub) {
+                        code[e] = 0u;
+                        qv = 0.0f;
+                    }
+                } else if constexpr (PREC == PREC_FP8) {
+                    float yq;
+                    code[e] = to_e4m3(t * inv, yq);
+                    if ((code[e] & 0x78u) == 0u) {  // zero or an e4m3 subnormal code
+                        code[e] = 0u;
+                        yq = 0.0f;
+                    }
+                    qv = yq * s;
+                } else {
+                    float yq;
+                    uint16_t l;
+                    code[e] = to_split(sub ? 0.0f : t * inv, l, yq);
+                    lo[e] = l;
+                    qv = yq * s;
+                }
+                sx = __fma_rn((double)t, (double)t, sx);
+                sq = __fma_rn((double)qv, (double)qv, sq);
+                const double df = (double)t - (double)qv;  // exact: both are FP32
+                sr = __fma_rn(df, df, sr);
+            }
+            // the codes of 8 consecutive values (VEC) or of 8 values 16 apart
+            if constexpr (VEC && PREC != PREC_FP32) {
+                const int c = col(p, 0);
+                if (live && c < D) {
+                    if constexpr (PREC == PREC_FP8) {
+                        uint2 o;
+                        o.x = code[0] | code[1] << 8 | code[2] << 16 | code[3] << 24;
+                        o.y = code[4] | code[5] << 8 | code[6] << 16 | code[7] << 24;
+                        *reinterpret_cast<uint2 *>(Xq + r * D + c) = o;
+                    } else {
+                        const uint4 o = make_uint4(code[0] | code[1] << 16, code[2] | code[3] << 16,
+                                                   code[4] | code[5] << 16, code[6] | code[7] << 16);
+                        if constexpr (PREC == PREC_BF16) {
+                            *reinterpret_cast<uint4 *>(Xq + (r * D + c) * 2) = o;
+                        } else {
+                            uint8_t *q = Xq + r * 4 * D + split_off(c, D);
+                            *reinterpret_cast<uint4 *>(q) = o;
+                            *reinterpret_cast<uint4 *>(q + 16) =
+                                make_uint4(lo[0] | lo[1] << 16, lo[2] | lo[3] << 16,
+                                           lo[4] | lo[5] << 16, lo[6] | lo[7] << 16);
+                        }
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int c = col(p, e);
+                    if (!live || c >= D) continue;
+                    if constexpr (PREC == PREC_FP32) {
+                        reinterpret_cast<uint32_t *>(Xq)[r * D + fp32_slot(c, d, D)] = code[e];
+                    } else if constexpr (PREC == PREC_BF16) {
+                        reinterpret_cast<uint16_t *>(Xq)[r * D + c] = (uint16_t)code[e];
+                    } else if constexpr (PREC == PREC_FP8) {
+                        Xq[r * D + c] = (uint8_t)code[e];
+                    } else {
+                        uint8_t *q = Xq + r * 4 * D + split_off(c, D);
+                        *reinterpret_cast<uint16_t *>(q) = (uint16_t)code[e];
+                        *reinterpret_cast<uint16_t *>(q + 16) = (uint16_t)lo[e];
+                    }
+                }
+            }
+        }
+        sx = row16_sum(sx);
+        sq = row16_sum(sq);
+        sr = row16_sum(sr);
+        const double up = 1.0 + 0x1p-40;
+        const float nx = __double2float_ru(sqrt(sx) * up);
+        const float nh = __double2float_ru(sqrt(sq) * up);
+        // (FP32: R is zero unless the row holds subnormal values)
+        const float rr = __double2float_ru(sqrt(sr) * up);
+        if (live) {
+            if (j16 == 0) {
+                if (!(nx <= 0x1p60f)) *flag = 1;
+                N[r] = nx;
+                Nh[r] = nh;
+                R[r] = rr;
+                sc[r] = s;
+            }
+            nhmax = fmaxf(nhmax, nh);
+            rmxv = fmaxf(rmxv, rr);
+            if (rmax && nx > 0.0f && rr > 0.0f)
+                rrmax = fmaxf(rrmax, __double2float_ru((double)rr / (double)nx));
+        }
+    }
+    // the block's largest Nh and R (tmax), and its largest R / N: one atomic
+    // per block (non-negative floats order like their bit patterns)
+    if (rmax || tmax_nh) {
+#pragma unroll
+        for (int o = 16; o < 64; o <<= 1) {
+            nhmax = fmaxf(nhmax, __shfl_xor(nhmax, o));
+            rmxv = fmaxf(rmxv, __shfl_xor(rmxv, o));
+            rrmax = fmaxf(rrmax, __shfl_xor(rrmax, o));
+        }
+        if (lane == 0) {
+            wmx[0][w] = nhmax;
+            wmx[1][w] = rmxv;
+            wmx[2][w] = rrmax;
+        }
+        __syncthreads();
+        if (threadIdx.x < 3) {
+            const float *q = wmx[threadIdx.x];
+            const float m = fmaxf(fmaxf(q[0], q[1]), fmaxf(q[2], q[3]));
+            if (threadIdx.x == 0 && tmax_nh) tmax_nh[blockIdx.x] = m;
+            if (threadIdx.x == 1 && tmax_r) tmax_r[blockIdx.x] = m;
+            if (threadIdx.x == 2 && rmax && m > 0.0f) atomicMax(rmax, __float_as_uint(m));
+        }
+    }
+}
+
+// The same for FP6 and FP4: a wave per row (wave w takes rows w, w + 4, ...), a
+// value per lane, because a block's codes are packed across 32 lanes.
+template <int PREC>
+__global__ __launch_bounds__(256) void k_quant_mx(const float *__restrict__ X,
+                                                  const int32_t *__restrict__ order, int64_t rows,
                                                int64_t rows_pad, int d, int D, int group,
                                                uint8_t *__restrict__ Xq, float *__restrict__ N,
                                                float *__restrict__ Nh, float *__restrict__ R,
@@ -117,7 +375,7 @@ __global__ __launch_bounds__(256) void k_quant(const float *__restrict__ X,
         }
     }
     if (__ballot(bad) != 0ull && lane == 0) *flag = 1;
-    if (scaled_prec(PREC)) {
+    {
         // the 16 row maxima reduced together (a maximum in any order)
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1)
@@ -142,7 +400,7 @@ __global__ __launch_bounds__(256) void k_quant(const float *__restrict__ X,
             const int i = w + 4 * j;
             const int64_t r = r0 + i;
             float s = 1.0f;
-            if (scaled_prec(PREC)) {
+            {
                 const int g0 = (i / group) * group;
                 float m = 0.0f;
                 for (int t = g0; t < g0 + group && t < 64; ++t) m = fmaxf(m, rowmax[t]);
@@ -168,38 +426,7 @@ __global__ __launch_bounds__(256) void k_quant(const float *__restrict__ X,
                 if (c < D) {
                     const float t = v[j][q];
                     float qv;
-                    // (values below 2^-126 are zero in the copy)
-                    const bool sub = fabsf(t) < 0x1p-126f;
-                    if (PREC == PREC_FP32) {
-                        qv = sub ? 0.0f : t;
-                        if (live) reinterpret_cast<float *>(Xq)[r * D + fp32_slot(c, d, D)] = qv;
-                    } else if (PREC == PREC_BF16) {
-                        uint16_t h = to_bf16(t, qv);
-                        if (sub) {
-                            h = 0;
-                            qv = 0.0f;
-                        }
-                        if (live) reinterpret_cast<uint16_t *>(Xq)[r * D + c] = h;
-                    } else if (PREC == PREC_FP8) {
-                        float yq;
-                        uint8_t b8 = to_e4m3(t * inv, yq);
-                        if ((b8 & 0x78u) == 0u) {  // zero or an e4m3 subnormal code
-                            b8 = 0;
-                            yq = 0.0f;
-                        }
-                        if (live) Xq[r * D + c] = b8;
-                        qv = yq * s;
-                    } else if (PREC == PREC_SPLIT) {
-                        float yq;
-                        uint16_t lo;
-                        const uint16_t hi = to_split(sub ? 0.0f : t * inv, lo, yq);
-                        if (live) {
-                            uint8_t *o = Xq + r * 4 * D + split_off(c, D);
-                            *reinterpret_cast<uint16_t *>(o) = hi;
-                            *reinterpret_cast<uint16_t *>(o + 16) = lo;
-                        }
-                        qv = yq * s;
-                    } else {
+                    {
                         // FP6 / FP4: the 32 codes of a block (held by 32
                         // consecutive lanes) packed from the slot's first
                         // bit, code e at bits [B e, B e + B); lane e < B of
@@ -275,28 +502,40 @@ __global__ __launch_bounds__(256) void k_quant(const float *__restrict__ X,
 
 void launch_quant(int prec, const float *X, const int32_t *order, int64_t rows,
                   int64_t rows_pad, int d, int D, int group, void *Xq, float *N, float *Nh,
-                  float *R, float *sc, unsigned int *rmax, int *flag, hipStream_t st) {
+                  float *R, float *sc, unsigned int *rmax, float *tmax_nh, float *tmax_r,
+                  int *flag, hipStream_t st) {
     const unsigned g = (unsigned)((rows_pad + 63) / 64);
     uint8_t *q = reinterpret_cast<uint8_t *>(Xq);
+    if (prec == PREC_FP6 || prec == PREC_FP4) {
+        {
+            RMIPS_PROF(st, "k_quant");
+            if (prec == PREC_FP6)
+                k_quant_mx<PREC_FP6><<<g, 256, 0, st>>>(X, order, rows, rows_pad, d, D, group, q, N,
+                                                        Nh, R, sc, rmax, flag);
+            else
+                k_quant_mx<PREC_FP4><<<g, 256, 0, st>>>(X, order, rows, rows_pad, d, D, group, q, N,
+                                                        Nh, R, sc, rmax, flag);
+        }
+        if (tmax_nh) launch_tile_max(Nh, R, (int)g, tmax_nh, tmax_r, st);
+        return;
+    }
     RMIPS_PROF(st, "k_quant");
-    if (prec == PREC_FP32)
-        k_quant<PREC_FP32><<<g, 256, 0, st>>>(X, order, rows, rows_pad, d, D, group, q, N, Nh, R,
-                                              sc, rmax, flag);
-    else if (prec == PREC_SPLIT)
-        k_quant<PREC_SPLIT><<<g, 256, 0, st>>>(X, order, rows, rows_pad, d, D, group, q, N, Nh, R,
-                                               sc, rmax, flag);
-    else if (prec == PREC_BF16)
-        k_quant<PREC_BF16><<<g, 256, 0, st>>>(X, order, rows, rows_pad, d, D, group, q, N, Nh, R,
-                                              sc, rmax, flag);
-    else if (prec == PREC_FP8)
-        k_quant<PREC_FP8><<<g, 256, 0, st>>>(X, order, rows, rows_pad, d, D, group, q, N, Nh, R,
-                                             sc, rmax, flag);
-    else if (prec == PREC_FP6)
-        k_quant<PREC_FP6><<<g, 256, 0, st>>>(X, order, rows, rows_pad, d, D, group, q, N, Nh, R,
-                                             sc, rmax, flag);
-    else
-        k_quant<PREC_FP4><<<g, 256, 0, st>>>(X, order, rows, rows_pad, d, D, group, q, N, Nh, R,
-                                             sc, rmax, flag);
+    const bool vec = (d & 3) == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0;
+    auto go = [&](auto pc, auto ng, auto vc) {
+        k_quant<decltype(pc)::value, decltype(ng)::value, decltype(vc)::value><<<g, 256, 0, st>>>(
+            X, order, rows, rows_pad, d, D, group, q, N, Nh, R, sc, rmax, tmax_nh, tmax_r, flag);
+    };
+    auto go2 = [&](auto pc) {
+        using One = std::integral_constant<int, 1>;
+        using Two = std::integral_constant<int, 2>;
+        if (D <= 128) vec ? go(pc, One{}, std::true_type{}) : go(pc, One{}, std::false_type{});
+        else if constexpr (decltype(pc)::value != PREC_FP32)  // (shorter rows only)
+            vec ? go(pc, Two{}, std::true_type{}) : go(pc, Two{}, std::false_type{});
+    };
+    if (prec == PREC_FP32) go2(std::integral_constant<int, PREC_FP32>{});
+    else if (prec == PREC_SPLIT) go2(std::integral_constant<int, PREC_SPLIT>{});
+    else if (prec == PREC_BF16) go2(std::integral_constant<int, PREC_BF16>{});
+    else go2(std::integral_constant<int, PREC_FP8>{});
 }
 
 __global__ void k_tile_max(const float *__restrict__ Nh, const float *__restrict__ R, int ntiles,
@@ -640,61 +879,84 @@ void k_rotate_aug(const float *__restrict__ X, const int32_t *__restrict__ order
 // The same rows when W is the identity (dp = d <= 256, ka <= 288): y = x
 // exactly, and ||W x||^2 is the same FP64 sum as ||x||^2, so the tail is the
 // widening alone.  Up to the FP64 summation order of the norm (both rounded
-// up) these are the rows k_rotate_aug gives with W = I.  One wave per row:
-// lane j holds values 8j .. 8j + 7 of the augmented row and writes its
-// 16-byte word j (at most 36 words).
-constexpr int AUG_ROWS = 4;  // rows (waves) per workgroup
-__global__ __launch_bounds__(64 * AUG_ROWS) void k_aug_ident(const float *__restrict__ X,
-                                                            const int32_t *__restrict__ order,
-                                                            int64_t rows, int64_t rows_pad, int d,
-                                                            int ka, float scale,
-                                                            uint4 *__restrict__ out) {
-    const int lane = threadIdx.x & 63;
-    const int64_t r = (int64_t)blockIdx.x * AUG_ROWS + (threadIdx.x >> 6);
-    if (r >= rows_pad) return;
+// up) these are the rows k_rotate_aug gives with W = I.  16 lanes per row, two
+// rows each: lane j holds the 16-byte words j, j + 16 and j + 32 of the
+// augmented row (kw <= 16 NW words of 8 values).  Memory bounds it: 500k rows x
+// 100 gathered 0.08 ms (a wave per row with 14 of 64 lanes at work: 0.24 ms).
+template <int NW, bool VEC>
+__global__ __launch_bounds__(256) void k_aug_ident(const float *__restrict__ X,
+                                                   const int32_t *__restrict__ order, int64_t rows,
+                                                   int64_t rows_pad, int d, int ka, float scale,
+                                                   uint4 *__restrict__ out) {
+    constexpr int AR = 2;  // rows per 16 lanes
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int j16 = lane & 15, rq = lane >> 4;
+    const int64_t r0 = (int64_t)blockIdx.x * (16 * AR) + 4 * w + rq;
     const int kw = ka / 8;
-    uint4 *o = out + r * kw;
-    if (r >= rows) {
-        if (lane < kw) o[lane] = make_uint4(0, 0, 0, 0);
-        return;
-    }
-    const float *x = X + (int64_t)(order ? order[r] : r) * d;
-    float v[8];
-    if ((d & 3) == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0) {  // 16-byte vectors: two loads per lane
-        const float4 *x4 = reinterpret_cast<const float4 *>(x);
-        const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-        const float4 y0 = 8 * lane < d ? x4[2 * lane] : z;
-        const float4 y1 = 8 * lane + 4 < d ? x4[2 * lane + 1] : z;
-        v[0] = y0.x; v[1] = y0.y; v[2] = y0.z; v[3] = y0.w;
-        v[4] = y1.x; v[5] = y1.y; v[6] = y1.z; v[7] = y1.w;
-    } else {
+    float v[AR][NW][8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = 8 * lane + e < d ? x[8 * lane + e] : 0.0f;
-    }
-    double s = 0.0;
+    for (int g = 0; g < AR; ++g) {
+        const int64_t r = r0 + 16 * g;
+        const int64_t src = r < rows ? (order ? (int64_t)order[r] : r) : -1;
+        const float *x = X + (src >= 0 ? src : 0) * d;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) s = fma((double)v[e], (double)v[e], s);
+        for (int p = 0; p < NW; ++p) {
+            const int c = 8 * (j16 + 16 * p);
+            if constexpr (VEC) {
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-    const float tail = __double2float_ru(sqrt(0.0 + 1e-12 * s));
-    const float nrm = scale * __double2float_ru(sqrt(s) * (1.0 + 0x1p-40));
-    if (lane >= kw) return;
-    uint32_t hw[4];
+                for (int h = 0; h < 2; ++h) {
+                    const float4 t = (src >= 0 && c + 4 * h < d)
+                                         ? *reinterpret_cast<const float4 *>(x + c + 4 * h)
+                                         : make_float4(0.f, 0.f, 0.f, 0.f);
+                    v[g][p][4 * h] = t.x;
+                    v[g][p][4 * h + 1] = t.y;
+                    v[g][p][4 * h + 2] = t.z;
+                    v[g][p][4 * h + 3] = t.w;
+                }
+            } else {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        uint16_t b[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int c = 8 * lane + 2 * e + h;
-            float y = v[2 * e + h];
-            y = (c == d) ? tail : y;
-            y = (c == d + 1) ? nrm : y;
-            float q;
-            b[h] = to_bf16(y, q);
+                for (int e = 0; e < 8; ++e) v[g][p][e] = (src >= 0 && c + e < d) ? x[c + e] : 0.0f;
+            }
         }
-        hw[e] = (uint32_t)b[0] | ((uint32_t)b[1] << 16);
     }
-    o[lane] = make_uint4(hw[0], hw[1], hw[2], hw[3]);
+#pragma unroll
+    for (int g = 0; g < AR; ++g) {
+        const int64_t r = r0 + 16 * g;
+        double s = 0.0;
+#pragma unroll
+        for (int p = 0; p < NW; ++p) {
+            double t = 0.0;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) t = fma((double)v[g][p][e], (double)v[g][p][e], t);
+            s += t;
+        }
+        s = row16_sum(s);
+        const float tail = __double2float_ru(sqrt(0.0 + 1e-12 * s));
+        const float nrm = scale * __double2float_ru(sqrt(s) * (1.0 + 0x1p-40));
+        if (r >= rows_pad) continue;
+        const bool live = r < rows;  // (padding rows are zero)
+#pragma unroll
+        for (int p = 0; p < NW; ++p) {
+            const int word = j16 + 16 * p;
+            if (word >= kw) continue;
+            uint32_t hw[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                uint32_t b[2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int c = 8 * word + 2 * e + h;
+                    float y = v[g][p][2 * e + h];
+                    y = (c == d) ? tail : y;
+                    y = (c == d + 1) ? nrm : y;
+                    float q;
+                    b[h] = to_bf16(y, q);
+                }
+                hw[e] = live ? b[0] | (b[1] << 16) : 0u;
+            }
+            out[r * kw + word] = make_uint4(hw[0], hw[1], hw[2], hw[3]);
+        }
+    }
 }
 
 size_t rotate_lds_bytes(int d) { return (size_t)4 * ((d + 3) / 4) * 64 * sizeof(double); }
@@ -704,8 +966,15 @@ void launch_rotate_aug(const float *X, const int32_t *order, int64_t rows, int64
                        hipStream_t st) {
     if (W == nullptr) {  // the identity, dp = d
         RMIPS_PROF(st, "k_aug_ident");
-        k_aug_ident<<<(unsigned)((rows_pad + AUG_ROWS - 1) / AUG_ROWS), 64 * AUG_ROWS, 0, st>>>(
-            X, order, rows, rows_pad, d, ka, scale, out);
+        const unsigned g = (unsigned)((rows_pad + 31) / 32);
+        const bool vec = (d & 3) == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0;
+        with_exact<1, 3>((ka / 8 + 15) / 16, [&](auto nw) {
+            constexpr int NW = decltype(nw)::value;
+            if (vec)
+                k_aug_ident<NW, true><<<g, 256, 0, st>>>(X, order, rows, rows_pad, d, ka, scale, out);
+            else
+                k_aug_ident<NW, false><<<g, 256, 0, st>>>(X, order, rows, rows_pad, d, ka, scale, out);
+        });
         return;
     }
     // persistent: W is staged once per workgroup, one workgroup per compute

@@ -359,10 +359,9 @@ rmips_status run_thresholds(rmips_ctx *ctx, const float *U, int64_t n, const flo
     launch_rows_prep(P, m, d, L.D, nullptr, L.Npid, L.keys, L.perm, L.bad, st);
     HIPTRY(radix_sort_u32(L.keys, L.perm, m, L.sort_scratch, st));
     launch_quant(L.prec, P, L.perm, m, L.mpad, d, L.D, TILE_ITEMS, L.Pq, L.Np, L.Nhp, L.Rp,
-                 L.sp, L.rmax, L.bad, st);
-    launch_tile_max(L.Nhp, L.Rp, L.ntiles, L.tmax_nh, L.tmax_r, st);
+                 L.sp, L.rmax, L.tmax_nh, L.tmax_r, L.bad, st);
     launch_quant(L.prec, U, nullptr, n, n, d, L.D, 1, L.Uq, L.Nu, L.Nhu, L.Ru, L.su, nullptr,
-                 L.bad, st);
+                 nullptr, nullptr, L.bad, st);
     HIPTRY(hipGetLastError());
     // (the caller reads L.bad later, in stream order; the kernels below stay
     // in bounds whatever the values)
@@ -1270,9 +1269,9 @@ rmips_status rmips_scores(rmips_ctx *ctx, const float *U, int64_t n, const doubl
     scores_plan(prec, n, nq, d, L, cv);
     HIPTRY(hipMemsetAsync(L.bad, 0, sizeof(int), st));
     launch_quant(L.prec, U, nullptr, n, n, d, L.D, 1, L.Uq, L.Nu, L.Nhu, L.Ru, L.su, nullptr,
-                 L.bad, st);
+                 nullptr, nullptr, L.bad, st);
     launch_quant(L.prec, Q, nullptr, nq, nq, d, L.D, 1, L.Qq, L.Nq, L.Nhq, L.Rq, L.sq, nullptr,
-                 L.bad, st);
+                 nullptr, nullptr, L.bad, st);
     HIPTRY(hipGetLastError());
     // (the input flag is read by rmips_sync; the kernels below stay in
     // bounds whatever the values)

@@ -165,3 +165,29 @@ def test_recompute_unaligned_rows():
         assert np.array_equal(tid.cpu().numpy(), j) and np.array_equal(topk.cpu().numpy(), tk)
         tau, tid = _rm().thresholds(_g(U), Pg, k, prec)
         assert np.array_equal(tau.cpu().numpy().view(np.uint64), t.view(np.uint64))
+
+
+# Screening copies and augmented rows: whole vectors and not, one part of a row
+# and two (D past 128), row words in one to three rounds of 16 lanes, users off
+# 16 bytes, row counts around a block's 64 and 32
+@pytest.mark.parametrize("prec", ["fp32", "bf16", "fp8"])
+@pytest.mark.parametrize("n,m,d", [(63, 65, 4), (65, 64, 128), (129, 127, 130), (31, 33, 132),
+                                   (97, 96, 256), (64, 129, 255)])
+@pytest.mark.parametrize("off", [0, 1])
+def test_row_copies(prec, n, m, d, off):
+    _say("row copies", prec, n, m, d, off)
+    rng = np.random.default_rng(n * d)
+    U = synth.isotropic(rng, n, d, 0.3)
+    P = synth.isotropic(rng, m, d, 0.6)
+    P[-1] = 0.0
+    buf = torch.zeros(n * d + off, dtype=torch.float32, device=_dev())
+    Ug = buf[off:].view(n, d)
+    Ug.copy_(_g(U))
+    k = min(8, m)
+    _, _, tk = orc.kmips_c(U, P, k)
+    sc = orc.histogram_scores(tk, m)
+    b = torch.empty(m, dtype=torch.int32, device=_dev())
+    ids, s, _ = _rm().topn(Ug, _g(P), k, 10, prec, bound_out=b)
+    ri, rs = orc.topn_from_scores(sc, 10)
+    assert ids.tolist() == ri.tolist() and s.tolist() == rs.tolist()
+    assert np.all(b.cpu().numpy() >= sc)
