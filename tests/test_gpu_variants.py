@@ -191,3 +191,25 @@ def test_row_copies(prec, n, m, d, off):
     ri, rs = orc.topn_from_scores(sc, 10)
     assert ids.tolist() == ri.tolist() and s.tolist() == rs.tolist()
     assert np.all(b.cpu().numpy() >= sc)
+
+
+# Sorts by length: one workgroup (up to 1,024 elements per round of 1, 2, 4 or 8),
+# blocks of 1,024 and 4,096 without scans, blocks of 1,024 with scans; the norm
+# order (stable: equal norms stay in id order) and the users' orders show in the
+# results
+@pytest.mark.parametrize("n,m", [(1, 1024), (1024, 1025), (1025, 2048), (2049, 4097), (4096, 8192),
+                                 (8193, 8193), (131072, 300), (131073, 64), (524288, 40),
+                                 (524289, 33)])
+def test_sort_lengths(n, m):
+    _say("sort lengths", n, m)
+    rng = np.random.default_rng(n + m)
+    d, k = 8, 3
+    U = synth.isotropic(rng, n, d, 0.3)
+    P = synth.isotropic(rng, m, d, 0.5)
+    P[1::2] = P[0:m - m % 2:2][:P[1::2].shape[0]]  # every norm twice
+    _, _, tk = orc.kmips_c(U, P, k)
+    sc = orc.histogram_scores(tk, m)
+    N = min(m, 50)
+    ri, rs = orc.topn_from_scores(sc, N)
+    ids, s, _ = _rm().topn(_g(U), _g(P), k, N)
+    assert ids.tolist() == ri.tolist() and s.tolist() == rs.tolist()
