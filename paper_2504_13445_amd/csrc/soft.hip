@@ -84,7 +84,7 @@ void k_soft(const float *__restrict__ U, int64_t n, const float *__restrict__ ta
     const int r16 = lane & 15, k4 = lane >> 4;
     const int64_t q0 = (int64_t)blockIdx.x * (64 * QB) + w * (16 * QB);  // the wave's queries
     const int split = blockIdx.y, nsplit = gridDim.y;
-    const int64_t per = (n + nsplit - 1) / nsplit;
+    const int64_t per = ((n + SUC - 1) / SUC + nsplit - 1) / nsplit * SUC;  // whole chunks
     const int64_t ubeg = (int64_t)split * per;
     const int64_t uend = (ubeg + per < n) ? ubeg + per : n;
 
@@ -253,22 +253,32 @@ void k_soft(const float *__restrict__ U, int64_t n, const float *__restrict__ ta
     }
 }
 
-// out[q][c] = scale_q * (sum over slices k of P[k][q][c]) in FP64, for
-// c < width.  One workgroup per query and 64 columns: each of its four waves
-// adds a quarter of the slices in slice order (loads in batches of 8), then
-// the four partial sums are added in wave order, a fixed order in every call.
-__global__ __launch_bounds__(256) void k_soft_reduce(const float *__restrict__ P, int nsplit,
-                                                     int64_t cols, int64_t ld_in, int64_t width,
-                                                     const float *__restrict__ dS,
-                                                     float *__restrict__ out, int64_t ld_out) {
-    __shared__ double part[4][64];
+// out[q][c] = scale_q * (sum over slices k of P[k][q][c]) in FP64, c < width
+// (G), and for the last column of workgroups out_s[q] = the sum of S's slices.
+// One workgroup per query and 64 columns: each of its SR_WAVES waves adds its
+// share of the slices in slice order (loads in batches of 8; S: 64 slices at a
+// time across the lanes), then the partial sums are added in wave order, a
+// fixed order in every call.  The chain of loads bounds it: 16 waves instead of
+// 4, 235 slices of 40 x 64 values 6 us (10 us).
+constexpr int SR_WAVES = 16;
+__global__ __launch_bounds__(64 * SR_WAVES) void k_soft_reduce(
+    const float *__restrict__ P, int nsplit, int64_t cols, int64_t ld_in, int64_t width,
+    const float *__restrict__ dS, float *__restrict__ out, int64_t ld_out,
+    const float *__restrict__ Sp, float *__restrict__ out_s, int gcols) {
+    __shared__ double part[SR_WAVES][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int64_t q = blockIdx.x;
+    const bool is_s = (int)blockIdx.y == gcols;
     const int64_t c = (int64_t)blockIdx.y * 64 + lane;
-    const bool ok = c < width;
-    const int per = (nsplit + 3) / 4, k0 = w * per, k1 = min(nsplit, k0 + per);
+    const bool ok = is_s || c < width;
     double s = 0.0;
-    if (ok) {
+    if (is_s) {
+        for (int k = w * 64 + lane; k < nsplit; k += 64 * SR_WAVES) s += (double)Sp[(int64_t)k * cols + q];
+        // (the lanes in a fixed tree)
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    } else if (ok) {
+        const int per = (nsplit + SR_WAVES - 1) / SR_WAVES, k0 = w * per, k1 = min(nsplit, k0 + per);
         const float *p = P + q * ld_in + c;
         const int64_t step = cols * ld_in;
         int k = k0;
@@ -284,9 +294,12 @@ __global__ __launch_bounds__(256) void k_soft_reduce(const float *__restrict__ P
     part[w][lane] = s;
     __syncthreads();
     if (w == 0 && ok) {
-        double t = part[0][lane] + part[1][lane];
-        t += part[2][lane];
-        t += part[3][lane];
+        double t = part[0][lane];
+        for (int v = 1; v < SR_WAVES; ++v) t += part[v][lane];
+        if (is_s) {
+            if (lane == 0) out_s[q] = (float)t;
+            return;
+        }
         if (dS) t *= (double)dS[q];
         out[q * ld_out + c] = (float)t;
     }
@@ -351,8 +364,9 @@ void launch_soft(const float *U, int64_t n, const float *tau, const float *Q, in
     const SoftDims sd = soft_dims(d);
     const float invT = 1.0f / T;
     const bool ws_ = S != nullptr, wg = G != nullptr || dQ != nullptr;
-    // two query blocks per wave up to d = 128, one above (registers)
-    const int qb = sd.kq <= 32 ? 2 : 1;
+    // two query blocks per wave up to d = 128, one above (registers) and for
+    // at most 64 queries (one tile of either kind, its waves' work halved)
+    const int qb = sd.kq <= 32 && nq > 64 ? 2 : 1;
     const int64_t tiles = (nq + 64 * qb - 1) / (64 * qb);
     // slices: one resident round of workgroups (each has one wave per SIMD,
     // so as many per compute unit as the registers give waves per SIMD, at
@@ -362,8 +376,11 @@ void launch_soft(const float *U, int64_t n, const float *tau, const float *Q, in
     const int resident =
         std::max(1, std::min(soft_wpe(qn, qb), (int)((size_t)(160 * 1024) / soft_lds(d))));
     int64_t ns = (256 * (int64_t)resident + tiles - 1) / tiles;
-    ns = std::min<int64_t>(ns, std::min<int64_t>(max_splits, (n + SUC - 1) / SUC));
-    const int nsplit = (int)std::max<int64_t>(1, ns);
+    const int64_t chunks = (n + SUC - 1) / SUC;
+    ns = std::max<int64_t>(1, std::min<int64_t>(ns, std::min<int64_t>(max_splits, chunks)));
+    // (whole chunks per slice, and no slice without users)
+    ns = (chunks + (chunks + ns - 1) / ns - 1) / ((chunks + ns - 1) / ns);
+    const int nsplit = (int)ns;
     dim3 g((unsigned)tiles, (unsigned)nsplit);
     float *gpart = reinterpret_cast<float *>(ws);
     float *spart = gpart + (size_t)max_splits * nq * sd.Dg;
@@ -373,28 +390,43 @@ void launch_soft(const float *U, int64_t n, const float *tau, const float *Q, in
         // QN = kq rounded up to 8 registers of the query operand, NCB = QN / 4
         // dim blocks (>= Dg / 16)
         with_exact<1, 8>((sd.kq + 7) / 8, [&](auto q8) {
-            constexpr int QN = 8 * decltype(q8)::value, NCB = QN / 4, QB = QN <= 32 ? 2 : 1;
-            if (ws_ && wg)
-                k_soft<QN, NCB, QB, true, true><<<g, 256, lds, st>>>(U, n, tau, Q, nq, d, invT,
-                                                                     spart, gpart);
-            else if (wg)
-                k_soft<QN, NCB, QB, false, true><<<g, 256, lds, st>>>(U, n, tau, Q, nq, d, invT,
-                                                                      nullptr, gpart);
-            else
-                k_soft<QN, NCB, QB, true, false><<<g, 256, lds, st>>>(U, n, tau, Q, nq, d, invT,
-                                                                      spart, nullptr);
+            constexpr int QN = 8 * decltype(q8)::value, NCB = QN / 4;
+            auto go = [&](auto qc) {
+                constexpr int QB = decltype(qc)::value;
+                if (ws_ && wg)
+                    k_soft<QN, NCB, QB, true, true><<<g, 256, lds, st>>>(U, n, tau, Q, nq, d, invT,
+                                                                         spart, gpart);
+                else if (wg)
+                    k_soft<QN, NCB, QB, false, true><<<g, 256, lds, st>>>(U, n, tau, Q, nq, d,
+                                                                          invT, nullptr, gpart);
+                else
+                    k_soft<QN, NCB, QB, true, false><<<g, 256, lds, st>>>(U, n, tau, Q, nq, d,
+                                                                          invT, spart, nullptr);
+            };
+            if constexpr (QN <= 32) {
+                if (qb == 2) {
+                    go(std::integral_constant<int, 2>{});
+                    return;
+                }
+            }
+            go(std::integral_constant<int, 1>{});
         });
     }
     RMIPS_PROF(st, "k_soft_reduce");
-    if (G)
-        k_soft_reduce<<<dim3((unsigned)nq, (unsigned)((d + 63) / 64)), 256, 0, st>>>(
-            gpart, nsplit, nq, sd.Dg, d, nullptr, G, d);
-    if (dQ)
-        k_soft_reduce<<<dim3((unsigned)nq, (unsigned)((d + 63) / 64)), 256, 0, st>>>(
-            gpart, nsplit, nq, sd.Dg, d, dS, dQ, d);
-    if (S)
-        k_soft_reduce<<<dim3((unsigned)nq, 1u), 256, 0, st>>>(spart, nsplit, nq, 1, 1, nullptr,
-                                                              S, 1);
+    // (S with G or dQ, in a column of workgroups of its own)
+    const int gc = (d + 63) / 64;
+    if (wg) {
+        const bool both = G && dQ;
+        k_soft_reduce<<<dim3((unsigned)nq, (unsigned)(gc + (S ? 1 : 0))), 64 * SR_WAVES, 0, st>>>(
+            gpart, nsplit, nq, sd.Dg, d, G ? nullptr : dS, G ? G : dQ, d, spart, S, gc);
+        if (both)
+            k_soft_reduce<<<dim3((unsigned)nq, (unsigned)gc), 64 * SR_WAVES, 0, st>>>(
+                gpart, nsplit, nq, sd.Dg, d, dS, dQ, d, nullptr, nullptr, gc);
+    } else {
+        k_soft_reduce<<<dim3((unsigned)nq, 1u), 64 * SR_WAVES, 0, st>>>(nullptr, nsplit, nq, 0, 0,
+                                                                        nullptr, nullptr, 0, spart,
+                                                                        S, 0);
+    }
 }
 
 // dQ[i][:] = dS[i] * G[i][:]

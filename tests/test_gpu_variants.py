@@ -213,3 +213,33 @@ def test_sort_lengths(n, m):
     ri, rs = orc.topn_from_scores(sc, N)
     ids, s, _ = _rm().topn(_g(U), _g(P), k, N)
     assert ids.tolist() == ri.tolist() and s.tolist() == rs.tolist()
+
+
+# Relaxed score: one and two query blocks per wave (up to 64 queries and more),
+# slices of whole 64-user chunks up to the 384 slices and past them, the three
+# passes (S, gradient, both) and their reductions.  Tolerance: the calls' 1e-4
+# of the FP64 values, at a temperature where z stays small (|z| < 40: FP32 z
+# within 40 * 2^-21, S and G within 2e-5)
+@pytest.mark.parametrize("n,d,nq", [(1, 5, 1), (63, 61, 63), (64, 100, 64), (65, 128, 65),
+                                    (24576, 16, 17), (24577, 33, 40), (49217, 61, 64),
+                                    (50000, 20, 129)])
+def test_soft_slices(n, d, nq):
+    _say("soft slices", n, d, nq)
+    rng = np.random.default_rng(n + nq)
+    U = synth.isotropic(rng, n, d, 0.25)
+    Q = (rng.standard_normal((nq, d)) / np.sqrt(d)).astype(np.float32)
+    tau = rng.uniform(0.2, 0.6, n).astype(np.float32)
+    T = 0.1
+    dS = np.linspace(0.5, 1.5, nq).astype(np.float32)
+    S64 = orc.soft_score(U, tau.astype(np.float64), Q, T)
+    G64 = orc.soft_grad(U, tau.astype(np.float64), Q, T)
+    rm = _rm()
+    a = (_g(U), _g(tau), _g(Q), T)
+    S, G = rm.soft_fwd_grad(*a)
+    assert torch.equal(rm.soft_fwd(*a), S)
+    dQ = rm.soft_bwd(*a, _g(dS)).cpu().numpy().astype(np.float64)
+    S, G = S.cpu().numpy().astype(np.float64), G.cpu().numpy().astype(np.float64)
+    assert np.all(np.abs(S - S64) <= 1e-4 * S64)
+    den = np.linalg.norm(G64, axis=1)
+    assert np.all(np.linalg.norm(G - G64, axis=1) <= 1e-4 * den)
+    assert np.all(np.linalg.norm(dQ - G64 * dS[:, None], axis=1) <= 1e-4 * den * dS)
