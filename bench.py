@@ -237,7 +237,7 @@ def kernel_table(prof, stats, steps, n, m, d, k, prec):
 
     # bytes per element slot and padded width (FP6/FP4 use FP8's 32-byte block slots)
     eb = {"fp32": 4, "bf16": 2}.get(prec, 1)
-    D = {"fp32": (d + 7) // 8 * 8, "bf16": (d + 15) // 16 * 16}.get(prec, (d + 63) // 64 * 64)
+    D = {"fp32": (d + 15) // 16 * 16 if d >= 32 else (d + 7) // 8 * 8, "bf16": (d + 15) // 16 * 16}.get(prec, (d + 63) // 64 * 64)
     # d' of the first bound: the rotated pre-pass where the library takes one
     # (d >= 111 by default), else d; the items it leaves open get d' = d
     dpre = int(avg("prepass_dprime"))
@@ -247,13 +247,17 @@ def kernel_table(prof, stats, steps, n, m, d, k, prec):
     # rows given identity (d' = d) augmented rows: all, or the users and the
     # re-bounded items
     aug_rows = (n + avg("rebound_items"), n + avg("rebound_items")) if dpre > 0 else (n + m, n + mpad)
-    t0 = min(6, mpad // 64)
+    # phase-1 tiles of stage (a), as the library takes them
+    nt = mpad // 64
+    t0 = min(nt, max(6, nt // 4), max(6, (10 if eb == 1 else 5) + k // 2))
+    # FP32 screening of rows from 32 dimensions on: three FP16 products
+    peak = PEAK["bf16"] / 3 if prec == "fp32" and d >= 32 else PEAK[prec]
     # per step: (work, unit, peak, bound)
     work = {
-        "k_thresh_screen/main": (2.0 * d * avg("thresh_pairs"), "flop", PEAK[prec], "mfma"),
-        "k_thresh_screen/bounds": (2.0 * d * n * 64 * t0, "flop", PEAK[prec], "mfma"),
-        "k_thresh_screen/refine": (2.0 * d * avg("refine_pairs"), "flop", PEAK[prec], "mfma"),
-        "k_count": (2.0 * d * avg("count_pairs"), "flop", PEAK[prec], "mfma"),
+        "k_thresh_screen/main": (2.0 * d * avg("thresh_pairs"), "flop", peak, "mfma"),
+        "k_thresh_screen/bounds": (2.0 * d * n * 64 * t0, "flop", peak, "mfma"),
+        "k_thresh_screen/refine": (2.0 * d * avg("refine_pairs"), "flop", peak, "mfma"),
+        "k_count": (2.0 * d * avg("count_pairs"), "flop", peak, "mfma"),
         "k_bound": (2.0 * (dp + 2) * avg("bound_pairs"), "flop", PEAK["bf16"], "mfma"),
         "k_bound/rebound": (2.0 * (d + 2) * avg("rebound_pairs"), "flop", PEAK["bf16"], "mfma"),
         # FP32 rows read, the bound's BF16 rows (ka values) written

@@ -157,7 +157,20 @@ int aug_len(int dp) {
     const int k16 = (dp + 2 + 15) & ~15;
     return k16 > 176 ? (dp + 2 + 31) & ~31 : k16;
 }
-constexpr int T0_TILES = 6;             // tiles of phase 1 of stage (a)
+// Tiles of phase 1 of stage (a), the bounds-only pass over the first items.
+// More of them give a starting bound nearer the k-th value, which spares
+// candidates and tiles in the main pass, and cost a pass over as many tiles:
+// more with k (the bound is the k-th of 64 slot maxima) and with the wide bands
+// of the 8-, 6- and 4-bit formats, at most a quarter of the catalogue.
+// Measured at 6, 9, 14 and 20 tiles: 500k x 50k x 100, k = 20, e4m3 16.7, 14.8,
+// 14.0, 13.7 ms, BF16 5.71, 5.67, 5.65, 5.80; 2M x 100k x 200, k = 10, split
+// 77.9, 77.0, 77.6, 78.4; 100k x 20k x 50, k = 32, split 2.46, 2.15, 1.95, 1.91;
+// small k is fastest at 6 to 9.
+constexpr int T0_MIN = 6;
+int t0_tiles(int prec, int k, int ntiles) {
+    const bool wide = prec == RMIPS_FP8_E4M3 || prec == RMIPS_FP6_E2M3 || prec == RMIPS_FP4_E2M1;
+    return std::min(std::max(T0_MIN, (wide ? 10 : 5) + k / 2), std::max(T0_MIN, ntiles / 4));
+}
 constexpr int BATCH_FIRST = 256;
 constexpr int BATCH_MAX = 4096;
 constexpr int GRAM_SAMPLE = 16384;
@@ -374,7 +387,7 @@ rmips_status run_thresholds(rmips_ctx *ctx, const float *U, int64_t n, const flo
     a.tmax_nh = L.tmax_nh; a.tmax_r = L.tmax_r; a.rmax_bits = L.rmax;
     a.perm = L.perm; a.m = m; a.ntiles = L.ntiles;
     a.U = U; a.P = P; a.d = d;
-    a.D = L.D; a.k = k; a.t0tiles = T0_TILES; a.nsplit = L.nsplit; a.cap = L.cap;
+    a.D = L.D; a.k = k; a.t0tiles = t0_tiles(L.prec, k, L.ntiles); a.nsplit = L.nsplit; a.cap = L.cap;
     a.c_err = ec.c; a.c2 = ec.c2; a.e_abs = E_ABS; a.g64 = ec.g64;
     a.cand = L.cand; a.cand_id = L.cand_id; a.cand_cnt = L.cand_cnt;
     a.lists = L.lists; a.lcnt = L.lcnt; a.refine = 2; a.Luse = L.Luse;

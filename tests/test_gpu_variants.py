@@ -243,3 +243,18 @@ def test_soft_slices(n, d, nq):
     den = np.linalg.norm(G64, axis=1)
     assert np.all(np.linalg.norm(G - G64, axis=1) <= 1e-4 * den)
     assert np.all(np.linalg.norm(dQ - G64 * dS[:, None], axis=1) <= 1e-4 * den * dS)
+
+
+# Phase-1 tiles by precision, k and catalogue: 6 up to 24 tiles of 64 items,
+# then 5 + k / 2 (10 + k / 2 with the wide bands) up to a quarter of the tiles
+@pytest.mark.parametrize("prec,m,k", [("fp32", 6 * 64 + 1, 32), ("fp32", 28 * 64, 32),
+                                      ("bf16", 84 * 64 + 1, 32), ("bf16", 30 * 64, 1),
+                                      ("fp8", 25 * 64, 1), ("fp8", 104 * 64 + 1, 32)])
+def test_phase1_tiles(prec, m, k):
+    _say("phase 1", prec, m, k)
+    rng = np.random.default_rng(m)
+    U, P = synth.isotropic(rng, 300, 40, 0.3), synth.isotropic(rng, m, 40, 0.3)
+    t, j, tk = orc.kmips_c(U, P, k)
+    r = _rm().thresholds(_g(U), _g(P), k, prec, with_topk=True)
+    assert np.array_equal(r[0].cpu().numpy().view(np.uint64), t.view(np.uint64))
+    assert np.array_equal(r[1].cpu().numpy(), j) and np.array_equal(r[2].cpu().numpy(), tk)
