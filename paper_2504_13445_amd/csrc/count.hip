@@ -22,6 +22,16 @@ __device__ __forceinline__ int half_sum(int x) {
     return x;
 }
 
+// Inclusive prefix sum over the wave's lanes.
+__device__ __forceinline__ int wave_prefix(int x) {
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(x, o);
+        x += (int)(threadIdx.x & 63) >= o ? y : 0;
+    }
+    return x;
+}
+
 // Counting workgroup: 8 waves, each owning 32 items (the row operand, kept
 // in registers for the whole kernel); users stream through LDS 64 at a time
 // (two column blocks), double-buffered where LDS allows, so the next chunk
@@ -39,54 +49,130 @@ constexpr int AMB_FLUSH = AMB_CAP / 2;   // list length that triggers a flush be
 constexpr int CNT_NW = 8;  // at most
 __host__ __device__ constexpr int count_waves(int nch) { return nch <= 16 ? 8 : 4; }
 
-// The wide-band precisions (e4m3, e2m3, e2m1) leave a large share of the
-// pairs ambiguous (about one in six at d = 200): their rechecks are taken
-// chunk by chunk with the chunk's FP32 user rows staged in LDS once, instead
-// of one user-row gather per pair.  A lane's ambiguous pairs of a chunk are
-// one 32-bit word (16 rows x two user columns) in LDS.
+// The wide-band formats (e4m3, e2m3, e2m1) leave a large share of the pairs
+// ambiguous (one in six at d = 100): they are rechecked every few chunks of
+// users (a window), whose pairs are listed in LDS: the FP32 rows of the
+// window's users and of the workgroup's 256 items go through LDS in slices of
+// RC_W dims, from which each thread takes up to RC_PP pairs of the list.  A row
+// is read by whole lines and once per window, and the pairs are spread evenly;
+// where each thread took the pairs of its own lane and read the item rows from
+// memory, with a line per lane and load (64 address cycles each), 128 M pairs
+// with 20 M rechecks (500k users x 256 items, d = 100, e4m3) took 2.38 ms, now
+// 0.72.  BF16 and FP32 (one pair in 85 and in 300 there, far fewer for items
+// that few users would take) keep the deferred list below: with BF16 a window
+// of few pairs costs more than it saves (1000 new items, d = 200: 0.31 to 0.68
+// ms, though 0.43 to 0.28 ms for the 256 items of the largest bounds).
 __host__ __device__ constexpr bool count_staged(int prec) {
     return prec >= PREC_FP8 && prec <= PREC_FP4;
 }
-__host__ __device__ inline int staged_stride(int D) { return D + 4; }  // floats per staged row
+constexpr int RC_W = 32;            // dims per slice
+constexpr int RC_S = RC_W + 4;      // floats per staged row: an odd count of 16-byte vectors
+constexpr int RC_CAP = 4096;        // pairs per round (16-bit codes in the deferred list's place)
+constexpr int RC_PP = RC_CAP / 512; // pairs per thread and round
+constexpr int RC_WIN = 4;           // chunks of users a list may cover (8-bit columns)
+constexpr int RC_FLUSH = RC_CAP / 4; // pairs that end a window
 
 size_t count_lds(int prec, int D) {
     const int ls = lds_row_bytes(prec, D);
     size_t b = 2 * (size_t)(CNT_USERS * ls + LDS_GUARD) + AMB_CAP * sizeof(int2) +
                32 * CNT_NW * sizeof(int) + 32;
     if (count_staged(prec))
-        b += 64 * CNT_NW * sizeof(uint32_t) + (size_t)CNT_USERS * staged_stride(D) * sizeof(float) +
-             2 * 32 * CNT_NW * sizeof(int);
+        b += (size_t)(32 * CNT_NW + RC_WIN * CNT_USERS) * RC_S * sizeof(float) + 3 * 32 * CNT_NW * sizeof(int) +
+             RC_WIN * CNT_USERS * (sizeof(double) + 2 * sizeof(int));
     return b;
 }
 
-// u . p (ip64's arithmetic: FP64 fused multiply-adds in index order) with
-// u staged in LDS, 16-byte aligned; p's 16-byte vectors are read four at a
-// time.  Rows that are not whole vectors take one value at a time.
-__device__ __forceinline__ double ip64_staged(const float *ul, const float *__restrict__ p, int d) {
-    double acc = 0.0;
-    if ((d & 3) == 0 && (reinterpret_cast<uintptr_t>(p) & 15) == 0) {
-        constexpr int RV = 4;
-        const float4 *u4 = reinterpret_cast<const float4 *>(ul);
-        const float4 *p4 = reinterpret_cast<const float4 *>(p);
-        const int d4 = d >> 2;
-        for (int i = 0; i < d4; i += RV) {
-            float4 y[RV];
+// 16 bytes of an FP32 row from dim e, zeros past the row's d values; vec: rows
+// of whole 16-byte vectors
+__device__ __forceinline__ float4 row_vec(const float *__restrict__ r, int e, int d, bool vec) {
+    if (vec)
+        return e < d ? *reinterpret_cast<const float4 *>(r + e) : make_float4(0.f, 0.f, 0.f, 0.f);
+    float4 v;
+    v.x = e < d ? r[e] : 0.f;
+    v.y = e + 1 < d ? r[e + 1] : 0.f;
+    v.z = e + 2 < d ? r[e + 2] : 0.f;
+    v.w = e + 3 < d ? r[e + 3] : 0.f;
+    return v;
+}
+
+// One round of a window's rechecks by a workgroup of 512: the np listed pairs
+// (codes: item row | user column << 8), ip64's arithmetic (FP64 fused
+// multiply-adds in index order; the zeros past d leave the sum unchanged).
+// rows: FP32 slices of 256 items, then of the users of the window's nwin chunks
+// (their tau, tau_id and rows in tau_s, tid_s, uid_s); this thread stages rows
+// tid / 8 + 64 j.
+__device__ __forceinline__ void recheck_round(const CountArgs &a, const uint16_t *codes, int np, float *rows,
+                              const int *orow_s, const int *tie_s, int *cntl,
+                              const double *tau_s, const int *tid_s, const int *uid_s, int nwin,
+                              bool vec, int tid) {
+    constexpr int NI = 4;  // staged item rows per thread
+    asm volatile("" : "+v"(tid));   // (no address below is formed, and held, outside the window's end)
+    const int rr = tid >> 3, c4 = (tid & 7) * 4;
+    const int w64 = tid & ~63;
+    const float *prow[NI], *urow[RC_WIN];
 #pragma unroll
-            for (int j = 0; j < RV; ++j) y[j] = p4[i + j < d4 ? i + j : d4 - 1];
+    for (int j = 0; j < NI; ++j) prow[j] = a.Porig + (int64_t)orow_s[rr + 64 * j] * a.d;
 #pragma unroll
-            for (int j = 0; j < RV; ++j) {
-                const bool ok = i + j < d4;
-                const float4 x = u4[ok ? i + j : d4 - 1];
-                acc = __fma_rn((double)(ok ? x.x : 0.f), (double)(ok ? y[j].x : 0.f), acc);
-                acc = __fma_rn((double)(ok ? x.y : 0.f), (double)(ok ? y[j].y : 0.f), acc);
-                acc = __fma_rn((double)(ok ? x.z : 0.f), (double)(ok ? y[j].z : 0.f), acc);
-                acc = __fma_rn((double)(ok ? x.w : 0.f), (double)(ok ? y[j].w : 0.f), acc);
-            }
-        }
-        return acc;
+    for (int j = 0; j < RC_WIN; ++j)
+        urow[j] = a.Uorig + (int64_t)uid_s[j < nwin ? rr + 64 * j : rr] * a.d;
+    int code[RC_PP];
+    double acc[RC_PP];
+#pragma unroll
+    for (int q = 0; q < RC_PP; ++q) {
+        code[q] = tid + 512 * q < np ? codes[tid + 512 * q] : 0;
+        acc[q] = 0.0;
     }
-    for (int i = 0; i < d; ++i) acc = __fma_rn((double)ul[i], (double)p[i], acc);
-    return acc;
+    float4 x[NI], y[RC_WIN];
+    auto fetch = [&](int e) {
+#pragma unroll
+        for (int j = 0; j < NI; ++j) x[j] = row_vec(prow[j], e + c4, a.d, vec);
+#pragma unroll
+        for (int j = 0; j < RC_WIN; ++j)
+            if (j < nwin) y[j] = row_vec(urow[j], e + c4, a.d, vec);
+    };
+    fetch(0);
+    float *us = rows + 32 * CNT_NW * RC_S;
+    for (int e0 = 0; e0 < a.d; e0 += RC_W) {
+        __syncthreads();  // the previous slice is done with
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+            *reinterpret_cast<float4 *>(rows + (rr + 64 * j) * RC_S + c4) = x[j];
+#pragma unroll
+        for (int j = 0; j < RC_WIN; ++j)
+            if (j < nwin) *reinterpret_cast<float4 *>(us + (rr + 64 * j) * RC_S + c4) = y[j];
+        if (e0 + RC_W < a.d) fetch(e0 + RC_W);
+        __syncthreads();
+        const int nv = a.d - e0 < RC_W ? (a.d - e0 + 3) >> 2 : RC_W / 4;
+#pragma unroll
+        for (int q = 0; q < RC_PP; ++q) {
+            if (512 * q + w64 >= np) break;  // the same for the whole wave
+            const float4 *pi = reinterpret_cast<const float4 *>(rows + (code[q] & 255) * RC_S);
+            const float4 *ui = reinterpret_cast<const float4 *>(us + (code[q] >> 8) * RC_S);
+            double s = acc[q];
+            auto term = [&](const float4 &u, const float4 &p) {
+                s = __fma_rn((double)u.x, (double)p.x, s);
+                s = __fma_rn((double)u.y, (double)p.y, s);
+                s = __fma_rn((double)u.z, (double)p.z, s);
+                s = __fma_rn((double)u.w, (double)p.w, s);
+            };
+            if (nv == RC_W / 4) {
+#pragma unroll
+                for (int j = 0; j < RC_W / 4; ++j) term(ui[j], pi[j]);
+            } else {
+                for (int j = 0; j < nv; ++j) term(ui[j], pi[j]);
+            }
+            acc[q] = s;
+            __builtin_amdgcn_sched_barrier(0);  // (one pair's rows in registers at a time)
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < RC_PP; ++q) {
+        if (tid + 512 * q < np) {
+            const int rl = code[q] & 255;
+            const int col = code[q] >> 8;
+            if (in_topk(acc[q], tie_s[rl], tau_s[col], tid_s[col])) atomicAdd(&cntl[rl], 1);
+        }
+    }
 }
 
 // FP64 decision of one (item row, user) pair by the tie rule.
@@ -121,16 +207,22 @@ void k_count(CountArgs a) {
     int2 *amb = reinterpret_cast<int2 *>(Ush0 + 2 * bstride);
     int *cntl = reinterpret_cast<int *>(amb + AMB_CAP);
     int *ambn = cntl + CNT_ITEMS;
-    // (wide bands) the lanes' ambiguity words and the chunk's FP32 user
-    // rows, after the fixed part of count_lds (16-byte aligned)
+    // (rechecks by window) pair codes in the deferred list's place; after the
+    // fixed part of count_lds the FP32 slices (16-byte aligned) and each item
+    // row's original row, tie id and scale
     constexpr bool STAGED = count_staged(PREC);
-    uint32_t *ambw = reinterpret_cast<uint32_t *>(smem8 + (2 * (size_t)bstride + AMB_CAP * sizeof(int2) +
-                                                           32 * CNT_NW * sizeof(int) + 32));
-    float *urow_s = reinterpret_cast<float *>(ambw + 64 * CNT_NW);
-    const int ustride = staged_stride(D);
-    // (wide bands) each item row's original row and tie id
-    int *orow_s = reinterpret_cast<int *>(urow_s + (size_t)CNT_USERS * ustride);
+    static_assert(!STAGED || NW == CNT_NW, "recheck_round takes 8 waves");
+    uint16_t *codes = reinterpret_cast<uint16_t *>(amb);
+    static_assert(RC_CAP * sizeof(uint16_t) <= AMB_CAP * sizeof(int2), "codes");
+    float *rc_rows = reinterpret_cast<float *>(smem8 + (2 * (size_t)bstride + AMB_CAP * sizeof(int2) +
+                                                        32 * CNT_NW * sizeof(int) + 32));
+    int *orow_s = reinterpret_cast<int *>(rc_rows + (32 * CNT_NW + RC_WIN * CNT_USERS) * RC_S);
     int *tie_s = orow_s + CNT_NW * 32;
+    float *sc_s = reinterpret_cast<float *>(tie_s + CNT_NW * 32);
+    // and tau, tau_id and row of each user of the window
+    double *tau_s = reinterpret_cast<double *>(sc_s + CNT_NW * 32);
+    int *tid_s = reinterpret_cast<int *>(tau_s + RC_WIN * CNT_USERS);
+    int *uid_s = tid_s + RC_WIN * CNT_USERS;
 
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     // item-block-major order: the blocks of the longest prefixes start first
@@ -140,28 +232,34 @@ void k_count(CountArgs a) {
     // this lane's half of its item's row (row lane & 31 of the wave's 32),
     // kept in registers for the whole kernel
     uint4 ia[NCH];
-    {
-        const int64_t it = ib + w * 32 + (lane & 31);
+    auto load_items = [&](int ln) {
+        const int64_t it = ib + w * 32 + (ln & 31);
         const bool ok = it < a.nb;
         const int64_t row = ok ? (a.rows ? a.rows[it] : it) : 0;
-        load_half_row<NCH>(ia, reinterpret_cast<const uint8_t *>(a.Pq), row, ok, rowb, nch, lane);
-    }
+        load_half_row<NCH>(ia, reinterpret_cast<const uint8_t *>(a.Pq), row, ok, rowb, nch, ln);
+    };
+    load_items(lane);
     if (tid < CNT_ITEMS) cntl[tid] = 0;
     if constexpr (STAGED) {
         if (tid < CNT_ITEMS) {
             const int64_t it = ib + tid;
             int orow = 0, tie = 0x7fffffff;
+            float sc = 1.0f;
             if (it < a.nb) {
                 const int64_t row = a.rows ? a.rows[it] : it;
                 orow = (int)(a.item_orig ? a.item_orig[row] : row);
                 tie = a.item_tie ? a.item_tie[row] : -1;
                 if (tie < 0) tie = 0x7fffffff;  // outside P: after every item of P
+                if (scaled_prec(PREC)) sc = a.sp[row];
             }
+            sc_s[tid] = sc;
             orow_s[tid] = orow;
             tie_s[tid] = tie;
         }
     }
-    if (tid == 0) *ambn = 0;
+    // ambn[0]: pairs listed, ambn[1..2]: its value at a barrier (rechecks by
+    // window: three counters in turn)
+    if (tid < 3) ambn[tid] = 0;
     if (tid < 2 * LDS_GUARD / 16) {
         const int g = tid / (LDS_GUARD / 16), e = tid % (LDS_GUARD / 16);
         reinterpret_cast<uint4 *>(Ush0 + g * bstride + CNT_USERS * ls)[e] = make_uint4(0, 0, 0, 0);
@@ -243,7 +341,27 @@ void k_count(CountArgs a) {
         }
     };
     int nall = 0;  // pairs listed (statistics)
-    int nst = 0;   // (wide bands) this thread's rechecks from staged rows
+    // (rechecks by window) rows of whole 16-byte vectors
+    const bool vec = (a.d & 3) == 0 && ((reinterpret_cast<uintptr_t>(a.Uorig) |
+                                         reinterpret_cast<uintptr_t>(a.Porig)) & 15) == 0;
+    // (rechecks by window) the present chunk's counter, this lane's pairs of the
+    // chunk (bit i: register i & 15 of column block i >> 4) and the place of
+    // the first of them in the chunk's list
+    int cq = 0, place = 0;
+    // pairs and chunks of the window before the present chunk
+    int wbase = 0, wn = 0;
+    uint32_t word = 0u;
+    // the codes of this lane's pairs that fall in places [from, from + RC_CAP)
+    auto list_codes = [&](int from) {
+        uint32_t bits = word;
+        for (int s = place - from; bits != 0u; ++s) {
+            const int i = __builtin_ctz(bits);
+            bits &= bits - 1u;
+            if (s >= 0 && s < RC_CAP)
+                codes[s] = (uint16_t)((w * 32 + mfma32_row(i & 15, lane)) |
+                                      ((wn * 64 + (lane & 31) + (i >= 16 ? 32 : 0)) << 8));
+        }
+    };
 
     // Phases: the two waves that share a SIMD work in opposite order
     // between the barriers.  An early wave multiplies chunk c and then
@@ -251,7 +369,7 @@ void k_count(CountArgs a) {
     // from the previous iteration) and then multiplies chunk c.  So one
     // wave's matrix products overlap the other's vector work.  Roles come
     // from the hardware SIMD id, one ticket per wave.
-    int *simdc = ambn + 1;
+    int *simdc = ambn + 3;
     if (tid < 4) simdc[tid] = 0;
 
     int64_t ch = split;
@@ -264,8 +382,8 @@ void k_count(CountArgs a) {
         int t = 0;
         if (lane == 0) t = atomicAdd(&simdc[simd_id()], 1);
         late = (__builtin_amdgcn_readfirstlane(t) & 1) != 0;  // uniform in the wave
-        // (wide bands: every wave classifies its chunk before the barrier,
-        // so that all the words of a chunk are there after it)
+        // (rechecks by window: every wave classifies its chunk before the
+        // barrier, so that the chunk's whole list is there after it)
         if (STAGED) late = false;
     }
     // the pending classification: products acc0/acc1 of the user columns
@@ -294,9 +412,8 @@ void k_count(CountArgs a) {
             anyamb |= (v0 == e0) | (v1 == e1);
         }
         if constexpr (STAGED) {
-            // this lane's ambiguous pairs as one word, rechecked after the
-            // chunk's barrier (bit i: register i & 15 of block i >> 4)
-            uint32_t word = 0u;
+            // this lane's ambiguous pairs, rechecked after the chunk's barrier
+            word = 0u;
             if (__ballot(anyamb) != 0ull) {
                 uint32_t ambm0 = 0, ambm1 = 0;
 #pragma unroll
@@ -309,8 +426,12 @@ void k_count(CountArgs a) {
                 ambm0 = c0 ? (ambm0 & rvalid) : 0u;
                 ambm1 = c1 ? (ambm1 & rvalid) : 0u;
                 word = ambm0 | (ambm1 << 16);
+                const int np = __popc(word), inc = wave_prefix(np);
+                int at = 0;
+                if (lane == 63) at = atomicAdd(&ambn[cq], inc);
+                place = wbase + __builtin_amdgcn_readlane(at, 63) + inc - np;
+                list_codes(0);
             }
-            ambw[w * 64 + lane] = word;
         } else if (__ballot(anyamb) != 0ull) {
             uint32_t ambm0 = 0, ambm1 = 0;
 #pragma unroll
@@ -354,6 +475,14 @@ void k_count(CountArgs a) {
         if (us0 < ulen) thresholds(uq0, uqs0, tin0, tout0);
         if (us1 < ulen) thresholds(uq1, uqs1, tin1, tout1);
         user_fetch(nxt);
+        double utau = 0.0;
+        int utid = 0, uuid = 0;
+        if (STAGED && w == 0) {
+            const int64_t us = ch * CNT_USERS + lane, v = us < ulen ? us : ulen - 1;
+            utau = a.us.tau[v];
+            utid = a.us.tau_id[v];
+            uuid = a.us.uid[v];
+        }
         // rows: this wave's items (shared); columns: the two user blocks
         auto multiply = [&]() {
             acc0 = f32x16{0};
@@ -369,55 +498,80 @@ void k_count(CountArgs a) {
         if (!late) multiply();
         if (pending) classify();
         if (late) multiply();
+        if (STAGED && w == 0) {
+            tau_s[wn * CNT_USERS + lane] = utau;
+            tid_s[wn * CNT_USERS + lane] = utid;
+            uid_s[wn * CNT_USERS + lane] = uuid;
+        }
+        // the list's length as one thread sees it before the barrier, so that
+        // all decide alike on a flush: after it a fast wave may list more
+        // pairs while a slow one reads (two slots in turn)
+        if (!STAGED && tid == 0) ambn[1 + buf] = *reinterpret_cast<volatile int *>(ambn);
         if (nxt < nchunks) dma_wait();
         __syncthreads();
+        const int seen = STAGED ? 0 : ambn[1 + buf];
         buf ^= 1;
         if constexpr (STAGED) {
-            // the chunk's rechecks: its users' FP32 rows staged once (a wave
-            // per row at a time), then each thread takes the word of the lane
-            // with its index, its items' original rows and tie ids from LDS
-            const uint32_t myw = ambw[tid];
-            if (__syncthreads_or(myw != 0u)) {
-                const int64_t u0 = ch * CNT_USERS;
-                for (int sl = w; sl < CNT_USERS; sl += NW) {
-                    if (u0 + sl >= ulen) break;
-                    const float *src = a.Uorig + (int64_t)a.us.uid[u0 + sl] * a.d;
-                    for (int i = lane; i < a.d; i += 64) urow_s[sl * ustride + i] = src[i];
-                }
-                __syncthreads();
-                uint32_t bits = myw;
-                const int wv = tid >> 6, ln = tid & 63;
-                while (bits != 0u) {
-                    const int i = __builtin_ctz(bits);
-                    bits &= bits - 1u;
-                    const int rl = wv * 32 + mfma32_row(i & 15, ln);
-                    const int sl = (ln & 31) + (i >= 16 ? 32 : 0);
-                    const int64_t usr = u0 + sl;
-                    const double v = ip64_staged(urow_s + sl * ustride,
-                                                 a.Porig + (int64_t)orow_s[rl] * a.d, a.d);
-                    if (in_topk(v, tie_s[rl], a.us.tau[usr], a.us.tau_id[usr]))
-                        atomicAdd(&cntl[rl], 1);
-                    ++nst;
-                }
-                __syncthreads();  // (the words and rows of the next chunk)
+            const int np = wbase + ambn[cq];
+            cq = cq == 2 ? 0 : cq + 1;
+            // the counter of the chunk after the next (the last reads of it
+            // were before this chunk's barrier, its next use is after the next)
+            if (tid == 0) ambn[cq == 2 ? 0 : cq + 1] = 0;
+            if (np < RC_FLUSH && wn + 1 < RC_WIN && nxt < nchunks) {
+                wbase = np;
+                ++wn;
+                continue;
             }
-        }
-        // a long list is rechecked by the whole workgroup now, so that the
-        // list rarely fills and rechecks rarely run inside one wave
-        const int nq = *ambn;  // the same for all threads after the barrier
-        if (nq >= AMB_FLUSH) {
-            flush(nq < AMB_CAP ? nq : AMB_CAP);
-            nall += nq;
-            __syncthreads();
-            if (tid == 0) *ambn = 0;
-            __syncthreads();
+            int ln = lane;
+            asm volatile("" : "+v"(ln));  // (as in recheck_round)
+            // The counts so far go to LDS, and the items' rows and scales are
+            // read again afterwards: kept in registers across the rechecks,
+            // they would make the chunk loop spill
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int s = half_sum(cnt[i]);
+                if ((ln & 31) == 0) atomicAdd(&cntl[w * 32 + mfma32_row(i, ln)], s);
+            }
+            for (int r0 = 0; r0 < np; r0 += RC_CAP) {
+                if (r0 > 0) {
+                    // (places from RC_CAP > RC_FLUSH on are this chunk's)
+                    __syncthreads();
+                    list_codes(r0);
+                    __syncthreads();
+                }
+                const int nr = np - r0 < RC_CAP ? np - r0 : RC_CAP;
+                recheck_round(a, codes, nr, rc_rows, orow_s, tie_s, cntl, tau_s, tid_s,
+                              uid_s, wn + 1, vec, tid);
+            }
+            nall += np;
+            wbase = 0;
+            wn = 0;
+            if (nxt >= nchunks) break;
+            __syncthreads();  // (the window's users' fields are read)
+            load_items(ln);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                cnt[i] = 0;
+                if (scaled_prec(PREC)) srow[i] = sc_s[w * 32 + mfma32_row(i, ln)];
+            }
+        } else {
+            // a long list is rechecked by the whole workgroup now, so that the
+            // list rarely fills and rechecks rarely run inside one wave
+            if (seen >= AMB_FLUSH) {
+                const int nq = *ambn;  // no wave lists any more pairs now
+                flush(nq < AMB_CAP ? nq : AMB_CAP);
+                nall += nq;
+                __syncthreads();
+                if (tid == 0) *ambn = 0;
+                __syncthreads();
+            }
         }
     }
     // a late wave's last chunk
-    if (pending) classify();
+    if (!STAGED && pending) classify();
     __syncthreads();
     // deferred FP64 rechecks, spread over the whole workgroup
-    {
+    if constexpr (!STAGED) {
         const int nq = *ambn;
         flush(nq < AMB_CAP ? nq : AMB_CAP);
         nall += nq;
@@ -425,18 +579,13 @@ void k_count(CountArgs a) {
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-        const int s = half_sum(cnt[i]);
+        const int s = STAGED ? 0 : half_sum(cnt[i]);
         const int rl = w * 32 + mfma32_row(i, lane);
         if ((lane & 31) == 0 && ib + rl < a.nb)
             a.partial[(int64_t)split * a.nb + ib + rl] = s + cntl[rl];
     }
     if (a.rechecks && tid == 0 && nall > 0)
         atomicAdd(reinterpret_cast<unsigned long long *>(a.rechecks), (unsigned long long)nall);
-    if constexpr (STAGED) {
-        const int ws = wave_sum(nst);
-        if (a.rechecks && lane == 0 && ws > 0)
-            atomicAdd(reinterpret_cast<unsigned long long *>(a.rechecks), (unsigned long long)ws);
-    }
 }
 
 template <int PREC>

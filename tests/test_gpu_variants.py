@@ -258,3 +258,26 @@ def test_phase1_tiles(prec, m, k):
     r = _rm().thresholds(_g(U), _g(P), k, prec, with_topk=True)
     assert np.array_equal(r[0].cpu().numpy().view(np.uint64), t.view(np.uint64))
     assert np.array_equal(r[1].cpu().numpy(), j) and np.array_equal(r[2].cpu().numpy(), tk)
+
+
+# Rechecks by window with the wide bands: nearly equal items leave every pair
+# open (16384 per chunk: rounds of 4096), single chunks and ragged ones, items
+# past one workgroup's 256, rows of whole 16-byte vectors and not, one to
+# eight slices of 32 dims
+@pytest.mark.parametrize("prec,n,q,d,noise", [("fp8", 1, 1, 3, 0.0), ("fp8", 63, 256, 32, 0.0),
+                                              ("fp8", 65, 257, 33, 1e-6), ("fp6", 700, 300, 100, 1e-6),
+                                              ("fp4", 1025, 31, 67, 1e-6), ("fp8", 5000, 260, 61, 0.3),
+                                              ("fp4", 3001, 513, 128, 0.3), ("fp8", 300, 256, 256, 1e-6)])
+def test_recheck_windows(prec, n, q, d, noise):
+    _say("windows", prec, n, q, d, noise)
+    rng = np.random.default_rng(n)
+    m, k = 40, 7
+    U = synth.isotropic(rng, n, d, 0.2)
+    P = synth.isotropic(rng, 1, d, 0.0) + noise * rng.standard_normal((m, d))
+    Q = synth.isotropic(rng, 1, d, 0.0) + noise * rng.standard_normal((q, d))
+    P = P.astype(np.float32)
+    Q = np.where((np.arange(q) % 3 == 0)[:, None], P[np.arange(q) % m], Q).astype(np.float32)
+    t, j, _ = orc.kmips_c(U, P, k)
+    rm = _rm()
+    got = rm.scores(_g(U), _g(t), _g(j), _g(Q), prec=prec)
+    assert np.array_equal(got.cpu().numpy(), orc.reverse_counts_c(U, t, j, Q))
