@@ -266,8 +266,9 @@ def kernel_table(prof, stats, steps, n, m, d, k, prec):
         "k_quant": ((n + m) * (4.0 * d + D * eb + 16.0), "byte", HBM_PEAK, "hbm"),
         # candidate lists read (value, bound, id: 12 B each), tau and id written
         "k_thresh_final/main": (12.0 * avg("cand_listed") + 12.0 * n, "byte", HBM_PEAK, "hbm"),
-        # users' screening rows in rho order: gathered once
-        "k_gather_padded": (2.0 * n * D * eb, "byte", HBM_PEAK, "hbm"),
+        # users' screening rows in rho order, gathered once, and their records
+        # (28 bytes read, 40 written)
+        "k_user_order": (n * (2.0 * D * eb + 68.0), "byte", HBM_PEAK, "hbm"),
     }
     table = {}
     # (the stage (a) recomputations, cand_pairs FP32 item rows gathered, are

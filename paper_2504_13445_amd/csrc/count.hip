@@ -598,23 +598,6 @@ void launch_count_p(const CountArgs &a, size_t lds, hipStream_t st) {
     });
 }
 
-__global__ __launch_bounds__(256) void k_max_i32(const int32_t *__restrict__ x, int64_t n,
-                                                 int32_t *__restrict__ out) {
-    __shared__ int32_t wm[4];
-    int32_t v = 0;
-    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) v = max(v, x[i]);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o));
-    if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = v;
-    __syncthreads();
-    if (threadIdx.x == 0) *out = max(max(wm[0], wm[1]), max(wm[2], wm[3]));
-}
-
-void launch_max_i32(const int32_t *x, int64_t n, int32_t *out, hipStream_t st) {
-    RMIPS_PROF(st, "k_max_i32");
-    k_max_i32<<<1, 256, 0, st>>>(x, n, out);
-}
-
 void launch_count(const CountArgs &a, hipStream_t st) {
     if (a.nb <= 0) return;
     const size_t lds = count_lds(a.prec, a.D);
@@ -631,11 +614,28 @@ void launch_count(const CountArgs &a, hipStream_t st) {
 // norms, and the error band it takes from their largest N, Nh and R is close
 // to each item's own (fewer pairs to recheck in FP64).  Rows and caller ids
 // move together, so each count still goes with its item.  One workgroup,
-// a bitonic sort of at most BATCH_ORDER_MAX (row, id) pairs in LDS.
+// a bitonic sort of at most BATCH_ORDER_MAX (row, id) pairs in LDS (more slots
+// keep the visit order).  With ulen also the largest of the slots' prefixes.
 constexpr int BATCH_ORDER_MAX = 4096;
 __global__ __launch_bounds__(1024) void k_batch_order(int32_t *__restrict__ rows,
-                                                      int32_t *__restrict__ cid, int nb) {
+                                                      int32_t *__restrict__ cid, int nb,
+                                                      const int32_t *__restrict__ cs,
+                                                      int32_t *__restrict__ ulen) {
     __shared__ uint64_t kv[BATCH_ORDER_MAX];
+    __shared__ int32_t wm[16];
+    if (ulen) {
+        int32_t v = 0;
+        for (int i = threadIdx.x; i < nb; i += blockDim.x) v = max(v, cs[i]);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o));
+        if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = v;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int q = 1; q < 16; ++q) v = max(v, wm[q]);
+            *ulen = v;
+        }
+    }
+    if (nb > BATCH_ORDER_MAX) return;
     int P2 = 1;
     while (P2 < nb) P2 <<= 1;
     for (int i = threadIdx.x; i < P2; i += blockDim.x)
@@ -661,10 +661,11 @@ __global__ __launch_bounds__(1024) void k_batch_order(int32_t *__restrict__ rows
     }
 }
 
-void launch_batch_order(int32_t *rows, int32_t *cid, int64_t nb, hipStream_t st) {
-    if (nb < 2 || nb > BATCH_ORDER_MAX) return;  // (larger batches keep the visit order)
+void launch_batch_order(int32_t *rows, int32_t *cid, int64_t nb, const int32_t *cs, int32_t *ulen,
+                        hipStream_t st) {
+    if (!ulen && (nb < 2 || nb > BATCH_ORDER_MAX)) return;
     RMIPS_PROF(st, "k_batch_order");
-    k_batch_order<<<1, 1024, 0, st>>>(rows, cid, (int)nb);
+    k_batch_order<<<1, 1024, 0, st>>>(rows, cid, (int)nb, cs, ulen);
 }
 
 // Eq. (3)/(6) bound count over the users of the item block's Cauchy-Schwarz

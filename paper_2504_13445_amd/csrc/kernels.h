@@ -82,13 +82,20 @@ void launch_kth_column(const double *topv, const int32_t *topk, int64_t n, int k
 // (-inf when tau_u <= 0 or ||u|| = 0), as ascending uint32 keys; val = user id.
 void launch_rho_keys(const double *tau, const float *Nu, int64_t n, uint32_t *key,
                      int32_t *val, hipStream_t st);
-// Y[r] = X[order[r]], rows of row_bytes (a multiple of 16)
-void launch_gather_padded(const void *X, const int32_t *order, int64_t rows, int row_bytes,
-                          void *Y, hipStream_t st);
+// What follows from the users' ratio order (keys sorted by their bits from
+// lo_bit up, order: sorted position -> user), in one launch:
 // cs[j] = number of sorted ratio keys whose bits from lo_bit up are at most
-// those of norm[j] * (1 + 2^-18) (keys sorted by those bits)
-void launch_cs_prefix(const uint32_t *rho_sorted_keys, int64_t n, const float *norm,
-                      int64_t m, int lo_bit, int32_t *cs, hipStream_t st);
+// those of norm[j] * (1 + 2^-18); inv[perm[j]] = j where inv is given; the
+// users' records (as launch_user_side); Y[r] = X[order[r]], rows of row_bytes
+// (a multiple of 16), where Y is given
+struct OrderArgs {
+    const uint32_t *keys; int64_t n; const float *norm; int64_t m; int lo_bit; int32_t *cs;
+    const int32_t *perm; int32_t *inv;
+    const double *tau; const int32_t *tau_id; const float *Nu, *Nhu, *Ru, *su;
+    const int32_t *order; float c2; UserSide us;
+    const void *X; int row_bytes; void *Y;
+};
+void launch_user_order(const OrderArgs &a, hipStream_t st);
 // G = sum over sampled rows x x^T (FP64, d x d), rows u = s*stride, s < ns;
 // scratch holds gram_scratch_bytes(d) bytes of per-slice partial sums
 size_t gram_scratch_bytes(int d);
@@ -118,6 +125,7 @@ struct ThreshArgs {
     const int32_t *perm; int64_t m; int ntiles;
     const float *U; const float *P; int d;      // original FP32 rows (recheck)
     int D; int k; int t0tiles; int nsplit; int cap;
+    int wide_from;  // (set per pass by launch_thresh) k_thresh_exact_wide takes the users with more values than this
     float c_err; float c2; float e_abs; float g64;
     // candidate lists: (screened value, its error bound E) and the caller's id
     float2 *cand; int32_t *cand_id; int32_t *cand_cnt;
@@ -180,10 +188,10 @@ struct CountArgs {
 };
 void launch_count(const CountArgs &a, hipStream_t st);
 // a batch's slots (rows of the norm-ordered item arrays and their caller ids)
-// in row order, nb <= 4096
-void launch_batch_order(int32_t *rows, int32_t *cid, int64_t nb, hipStream_t st);
-// *out = max(x[0], ..., x[n-1]) (0 when n = 0), one workgroup
-void launch_max_i32(const int32_t *x, int64_t n, int32_t *out, hipStream_t st);
+// in row order (up to 4096 slots, larger batches keep theirs); ulen (may be
+// NULL): the largest of the slots' prefixes cs (not reordered)
+void launch_batch_order(int32_t *rows, int32_t *cid, int64_t nb, const int32_t *cs, int32_t *ulen,
+                        hipStream_t st);
 size_t count_lds(int prec, int D);
 
 struct BoundArgs {

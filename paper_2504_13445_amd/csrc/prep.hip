@@ -596,13 +596,14 @@ void launch_invert_perm(const int32_t *perm, int64_t m, int32_t *inv, hipStream_
     k_invert_perm<<<(unsigned)((m + 255) / 256), 256, 0, st>>>(perm, m, inv);
 }
 
-__global__ void k_user_side(const double *__restrict__ tau, const int32_t *__restrict__ tau_id,
-                            const float *__restrict__ Nu, const float *__restrict__ Nhu,
-                            const float *__restrict__ Ru, const float *__restrict__ su,
-                            const int32_t *__restrict__ order, int64_t n, float c2,
-                            UserSide out) {
-    int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= n) return;
+__device__ __forceinline__ void user_side(const double *__restrict__ tau,
+                                          const int32_t *__restrict__ tau_id,
+                                          const float *__restrict__ Nu,
+                                          const float *__restrict__ Nhu,
+                                          const float *__restrict__ Ru,
+                                          const float *__restrict__ su,
+                                          const int32_t *__restrict__ order, int64_t r, float c2,
+                                          const UserSide &out) {
     int64_t u = order ? order[r] : r;
     double t = tau[u];
     out.sinv[r] = 1.0f / su[u];  // exact: su is a power of two
@@ -612,6 +613,15 @@ __global__ void k_user_side(const double *__restrict__ tau, const int32_t *__res
     out.uid[r] = (int32_t)u;
     out.thr[r] = make_float4(__double2float_ru(t), __double2float_rd(t), fmaf(c2, Nu[u], Ru[u]),
                              Nhu[u]);
+}
+
+__global__ void k_user_side(const double *__restrict__ tau, const int32_t *__restrict__ tau_id,
+                            const float *__restrict__ Nu, const float *__restrict__ Nhu,
+                            const float *__restrict__ Ru, const float *__restrict__ su,
+                            const int32_t *__restrict__ order, int64_t n, float c2,
+                            UserSide out) {
+    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (r < n) user_side(tau, tau_id, Nu, Nhu, Ru, su, order, r, c2, out);
 }
 
 void launch_user_side(const double *tau, const int32_t *tau_id, const float *Nu,
@@ -654,47 +664,45 @@ void launch_rho_keys(const double *tau, const float *Nu, int64_t n, uint32_t *ke
     k_rho_keys<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(tau, Nu, n, key, val);
 }
 
-__global__ void k_gather_padded(const uint4 *__restrict__ X, const int32_t *__restrict__ order,
-                                int64_t rows, int W16, uint4 *__restrict__ Y) {
-    int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= rows * W16) return;
-    int64_t r = e / W16, c = e - r * W16;
-    Y[e] = X[(int64_t)order[r] * W16 + c];
-}
-
-// Ys[r] = Xs[order[r]], rows of row_bytes (a multiple of 16)
-void launch_gather_padded(const void *X, const int32_t *order, int64_t rows, int row_bytes,
-                          void *Y, hipStream_t st) {
-    const int W16 = row_bytes / 16;
-    int64_t tot = rows * W16;
-    RMIPS_PROF(st, "k_gather_padded");
-    k_gather_padded<<<(unsigned)((tot + 255) / 256), 256, 0, st>>>(
-        reinterpret_cast<const uint4 *>(X), order, rows, W16, reinterpret_cast<uint4 *>(Y));
-}
-
+// Three passes over the sorted users that do not depend on each other, in one
+// launch (and the items' inverse permutation, which is due by then): for few
+// rows each of them was a launch of its own, about 5 us.  The first blocks take
+// the items, then the users' records, then the users' rows, 256 each.
 // The keys are ordered by their bits from lo_bit up only: the prefix then
 // takes every user whose key agrees with the item's in those bits or is
 // below, a superset of the users of Eq. (2) (ratios up to 2^(lo_bit-23)
 // relative above the item's norm also come in).
-__global__ void k_cs_prefix(const uint32_t *__restrict__ keys, int64_t n,
-                            const float *__restrict__ norm, int64_t m, int lo_bit,
-                            int32_t *__restrict__ cs) {
-    int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= m) return;
-    const uint32_t x = norm_key(norm[j]) >> lo_bit;
-    int64_t lo = 0, hi = n;  // first position with a larger key
-    while (lo < hi) {
-        int64_t mid = (lo + hi) >> 1;
-        if ((keys[mid] >> lo_bit) <= x) lo = mid + 1; else hi = mid;
+__global__ __launch_bounds__(256) void k_user_order(OrderArgs a, int64_t bm, int64_t bn, int W16) {
+    const int64_t b = blockIdx.x;
+    if (b < bm) {
+        const int64_t j = b * 256 + threadIdx.x;
+        if (j >= a.m) return;
+        const uint32_t x = norm_key(a.norm[j]) >> a.lo_bit;
+        int64_t lo = 0, hi = a.n;  // first position with a larger key
+        while (lo < hi) {
+            const int64_t mid = (lo + hi) >> 1;
+            if ((a.keys[mid] >> a.lo_bit) <= x) lo = mid + 1; else hi = mid;
+        }
+        a.cs[j] = (int32_t)lo;
+        if (a.inv) a.inv[a.perm[j]] = (int32_t)j;
+    } else if (b < bm + bn) {
+        const int64_t r = (b - bm) * 256 + threadIdx.x;
+        if (r < a.n) user_side(a.tau, a.tau_id, a.Nu, a.Nhu, a.Ru, a.su, a.order, r, a.c2, a.us);
+    } else {
+        const int64_t e = (b - bm - bn) * 256 + threadIdx.x;
+        if (e >= a.n * W16) return;
+        const int64_t r = e / W16, c = e - r * W16;
+        reinterpret_cast<uint4 *>(a.Y)[e] =
+            reinterpret_cast<const uint4 *>(a.X)[(int64_t)a.order[r] * W16 + c];
     }
-    cs[j] = (int32_t)lo;
 }
 
-void launch_cs_prefix(const uint32_t *rho_sorted_keys, int64_t n, const float *norm,
-                      int64_t m, int lo_bit, int32_t *cs, hipStream_t st) {
-    RMIPS_PROF(st, "k_cs_prefix");
-    k_cs_prefix<<<(unsigned)((m + 255) / 256), 256, 0, st>>>(rho_sorted_keys, n, norm, m, lo_bit,
-                                                             cs);
+void launch_user_order(const OrderArgs &a, hipStream_t st) {
+    const int W16 = a.row_bytes / 16;
+    const int64_t bm = (a.m + 255) / 256, bn = (a.n + 255) / 256;
+    const int64_t bg = a.Y ? (a.n * W16 + 255) / 256 : 0;
+    RMIPS_PROF(st, "k_user_order");
+    k_user_order<<<(unsigned)(bm + bn + bg), 256, 0, st>>>(a, bm, bn, W16);
 }
 
 // 32x32 tile of G per block over one slice of the sampled rows (blockIdx.z),

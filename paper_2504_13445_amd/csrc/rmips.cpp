@@ -679,12 +679,16 @@ int count_splits(int64_t nb, int64_t ulen, int maxs) {
 // count then test; the counting stage's per-user records and screening
 // rows in that order.  X.tau / X.tau_id hold the thresholds.
 void run_prefix(const ThreshLayout &T, PrefixLayout &X, int64_t n, int64_t m, float c2,
-                hipStream_t st, bool with_rows = true) {
+                hipStream_t st, bool with_rows = true, int32_t *inv = nullptr) {
     launch_rho_keys(X.tau, T.Nu, n, X.ukeys, X.uperm, st);
     (void)radix_sort_u32(X.ukeys, X.uperm, n, X.usort, st, RHO_LO_BIT, 32);
-    launch_cs_prefix(X.ukeys, n, T.Np, m, RHO_LO_BIT, X.cs, st);
-    launch_user_side(X.tau, X.tau_id, T.Nu, T.Nhu, T.Ru, T.su, X.uperm, n, c2, X.us, st);
-    if (with_rows) launch_gather_padded(T.Uq, X.uperm, n, T.rowb, X.Us, st);
+    OrderArgs a{};
+    a.keys = X.ukeys; a.n = n; a.norm = T.Np; a.m = m; a.lo_bit = RHO_LO_BIT; a.cs = X.cs;
+    a.perm = T.perm; a.inv = inv;
+    a.tau = X.tau; a.tau_id = X.tau_id; a.Nu = T.Nu; a.Nhu = T.Nhu; a.Ru = T.Ru; a.su = T.su;
+    a.order = X.uperm; a.c2 = c2; a.us = X.us;
+    a.X = T.Uq; a.row_bytes = T.rowb; a.Y = with_rows ? X.Us : nullptr;
+    launch_user_order(a, st);
 }
 
 // Relative slack s of the Eq. (3) bound, in units of ||u|| ||p||: each
@@ -862,14 +866,14 @@ rmips_status run_count_topn(rmips_ctx *ctx, const float *U, const float *P,
         const bool first = cr.batches == 0;
         int64_t ulen = 0;
         if (first) {
-            launch_max_i32(C.vis_cs, nb, C.ulen_dev, st);
             ulen = n;
         } else {
             for (int64_t r = r0; r < r1; ++r) ulen = std::max<int64_t>(ulen, h_cs[r]);
         }
         // the batch's slots in norm order (the host's copies of the bounds
         // and prefixes stay in visit order; the batch is a set)
-        launch_batch_order(C.visit + r0, C.vis_cid + r0, nb, st);
+        launch_batch_order(C.visit + r0, C.vis_cid + r0, nb, C.vis_cs + r0,
+                           first ? C.ulen_dev : nullptr, st);
         CountArgs a{};
         a.prec = T.prec;
         a.Pq = T.Pq; a.Np = T.Np; a.Nhp = T.Nhp; a.Rp = T.Rp; a.sp = T.sp;
@@ -1407,13 +1411,12 @@ rmips_status rmips_topn(rmips_ctx *ctx, const float *U, int64_t n, const float *
     }
 
     // ---- stage (c): Cauchy-Schwarz prefix and Eq. (3)/(6) bound counts
-    run_prefix(L.T, L.X, n, m, ec.c2, st);
+    run_prefix(L.T, L.X, n, m, ec.c2, st, true, L.C.inv);
     if (rotate)
         HIPTRY(hipMemcpyAsync(L.W, W.data(), sizeof(double) * dp * d, hipMemcpyHostToDevice, st));
     const double *Wd = rotate ? L.W : nullptr;  // nullptr: the identity
     launch_rotate_aug(P, L.T.perm, m, L.T.mpad, d, Wd, dp, ka, 1.0f, L.B.Pa, st);
     run_bound(U, L.X, L.B, Wd, dp, n, m, L.T.mpad, d, ctr + 2, ev[6], ev[7], L.uscore, st);
-    launch_invert_perm(L.T.perm, m, L.C.inv, st);
     HIPTRY(hipGetLastError());
 
     // ---- stage (b): exact scores in bound order, running top-N, stop rule

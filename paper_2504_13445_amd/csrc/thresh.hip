@@ -1290,8 +1290,8 @@ __device__ __forceinline__ void wave_rank64(const uint64_t (&r)[J], const int (&
     vid = last;
 }
 
-// The recomputations of users with more than EXACT_SLOTS (at most EXACT_WIDE)
-// values: a wave per user, 64 values at a time (the user's row in LDS, the item
+// The recomputations of users with more than wide_from (EXACT_SLOTS, or 0
+// where k_thresh_exact is left out) and at most EXACT_WIDE values: a wave per user, 64 values at a time (the user's row in LDS, the item
 // rows through stage_rows), more than 64 by way of the user's candidate slots;
 // tau_u by wave_rank64.  Each wave reads the metadata of its share of the list
 // (at most 64 users at a time) and takes the wide ones in turn.  500k users x
@@ -1320,7 +1320,7 @@ void k_thresh_exact_wide(ThreshArgs a) {
             myu = LISTED ? a.ulist[pos] : (int)pos;
             meta = a.cand_cnt[(int64_t)myu * a.nsplit];
         }
-        uint64_t wide = __ballot(meta >= 0 && (meta >> 8) > EXACT_SLOTS);
+        uint64_t wide = __ballot(meta >= 0 && (meta >> 8) > a.wide_from);
         while (wide != 0ull) {
             const int src = __builtin_ctzll(wide);
             wide &= wide - 1ull;
@@ -1554,7 +1554,8 @@ void launch_thresh(const ThreshArgs &a0, hipStream_t st) {
     // (a wave per 64 users; three 2-wave workgroups per CU are resident)
     const int64_t eblocks = std::min<int64_t>((a0.n + 64 * EXACT_WAVES - 1) / (64 * EXACT_WAVES), 6 * 256);
     // one resident round (four 4-wave workgroups per CU)
-    const int64_t wblocks = std::min<int64_t>((a0.n + 3) / 4, 4 * 256);
+    constexpr int64_t wblocks_max = 4 * 256;
+    const int64_t wblocks = std::min<int64_t>((a0.n + 3) / 4, wblocks_max);
     int32_t *LA = a0.lists, *LB = a0.lists + a0.n, *LF = a0.lists + 2 * a0.n;
     auto screen = [&](const ThreshArgs &a, dim3 g, const char *name) {
         if (a.prec == PREC_FP32) launch_screen<PREC_FP32>(a, nch, g, lds, st, name);
@@ -1583,7 +1584,12 @@ void launch_thresh(const ThreshArgs &a0, hipStream_t st) {
             RMIPS_PROF(st, nf);
             k_thresh_final<true><<<(unsigned)fblocks, 64 * fw, lds_fin, st>>>(h, capT, capP);
         }
-        {
+        // A launch costs about 5 us whatever it does.  The refinement passes'
+        // lists are empty or hold many values, and up to 4096 users find a
+        // wave each: there k_thresh_exact_wide takes all lists (2000 users x
+        // 1000 items: the call 293 -> 274 us together with k_user_order)
+        h.wide_from = a.n <= 4 * wblocks_max || ne == nullptr ? 0 : EXACT_SLOTS;
+        if (h.wide_from > 0) {
             RMIPS_PROF(st, ne);
             k_thresh_exact<true><<<(unsigned)eblocks, 64 * EXACT_WAVES, 0, st>>>(h);
         }
@@ -1640,7 +1646,7 @@ void launch_thresh(const ThreshArgs &a0, hipStream_t st) {
         // are usually empty, and the workgroups loop over long ones
         const int64_t gx = ublocks < 256 / nsr ? ublocks : 256 / nsr;
         screen(b, dim3((unsigned)gx, (unsigned)nsr), "k_thresh_screen/refine");
-        final(b, b.nsplit * b.cap, "k_thresh_final/refine", "k_thresh_exact/refine",
+        final(b, b.nsplit * b.cap, "k_thresh_final/refine", nullptr,
               "k_thresh_exact_wide/refine");
     }
     int64_t fb = (a0.n + FB_WAVES - 1) / FB_WAVES;
