@@ -651,6 +651,24 @@ __device__ __forceinline__ uint32_t wave_kth_key(const uint32_t (&r)[J], int k) 
     return t;
 }
 
+// The k-th largest of x and of y (keys as above; n >= k of each, in the first n
+// lanes): the smallest key with fewer than k larger ones, every lane counting
+// the larger ones of its own two keys.  Three instructions per key and list
+// that do not wait for each other, where wave_kth_key's chain of compare,
+// count and branch takes some 25 steps (500k users, lists of 27: 0.60 to 0.44
+// ms for k_thresh_select).
+__device__ __forceinline__ void wave_kth_pair(uint32_t x, uint32_t y, int n, int k, uint32_t &kx,
+                                              uint32_t &ky) {
+    int gx = 0, gy = 0;
+#pragma unroll 4
+    for (int q = 0; q < n; ++q) {
+        gx += (uint32_t)__builtin_amdgcn_readlane((int)x, q) > x ? 1 : 0;
+        gy += (uint32_t)__builtin_amdgcn_readlane((int)y, q) > y ? 1 : 0;
+    }
+    kx = ~dpp_wave_max_u32(x != 0u && gx < k ? ~x : 0u);
+    ky = ~dpp_wave_max_u32(y != 0u && gy < k ? ~y : 0u);
+}
+
 // The k-th largest of the list x[0..n) in LDS, counting repetitions (-inf
 // when n < k); lists past 1024 values are read again for every bit.
 template <int J>
@@ -681,9 +699,11 @@ __device__ float wave_kth_largest(const float *x, int n, int k, int lane) {
 // (k_thresh_final takes the others): as k_thresh_final, but with the joined
 // list in registers (J entries per lane) from its load to the ids left for
 // the recomputation, so that no LDS limits the waves in flight.  Latency and
-// the selection's instructions bound it: 500k users, e4m3 lists of 429
-// entries 2.5 ms (in LDS, the k-th largest by rounds of the next largest:
-// 9.9 ms); BF16 lists of 32 entries 0.64 ms (0.72 ms).
+// the selection's instructions bound it: 500k users, e4m3 lists of 241
+// entries 1.6 ms (lists of 429 2.5 ms; in LDS, by rounds of the next largest:
+// 9.9 ms); BF16 lists of 27 entries 0.44 ms, 2M users with lists of 11 1.17 ms
+// (0.72 and 2.0 ms), of which reading the counts two users and the entries one
+// user ahead is 0.03 and 0.2 ms.
 constexpr int SEL_MAX = 2048;
 // lists up to SEL_SHORT leave registers for four waves per SIMD, up to
 // SEL_MID (e4m3, k = 20) for three, longer ones for two
@@ -692,35 +712,50 @@ struct SelOut {
     float Lstar;      // k-th largest lower bound of the stored entries (-inf: fewer than k)
     int nrec, ns;     // entries left to recompute, survivors
 };
+// entry g of the user's joined list (pre: the lists' inclusive prefixes, one
+// per lane; split = number of them that are <= g)
+__device__ __forceinline__ void joined_entry(const ThreshArgs &a, int64_t u, int pre, int stored,
+                                             int g, float2 &cv, int &ci) {
+    int sp = 0, before = 0;
+    for (int q = 0; q < a.nsplit; ++q) {
+        const int pq = __builtin_amdgcn_readlane(pre, q);
+        if (pq <= g) {
+            sp = q + 1;
+            before = pq;
+        }
+    }
+    cv = make_float2(0.0f, 0.0f);
+    ci = 0;
+    if (g < stored) {
+        const int64_t e = (u * a.nsplit + sp) * a.cap + (g - before);
+        cv = a.cand[e];
+        ci = a.cand_id[e];
+    }
+}
+// (J = 1: the entry is e0, id0)
 template <int J>
 __device__ __forceinline__ SelOut select_regs(const ThreshArgs &a, int64_t u, int pre, int stored,
-                                              bool over, int lane) {
+                                              bool over, float2 e0, int id0, int lane) {
     uint32_t lo[J], hi[J];  // keys of the bounds vh -/+ E, 0 past the end
     int ci[J];
 #pragma unroll
     for (int t = 0; t < J; ++t) {
-        // entry g of the joined list: split = number of inclusive prefixes <= g
         const int g = 64 * t + lane;
-        int sp = 0, before = 0;
-        for (int q = 0; q < a.nsplit; ++q) {
-            const int pq = __builtin_amdgcn_readlane(pre, q);
-            if (pq <= g) {
-                sp = q + 1;
-                before = pq;
-            }
-        }
-        float2 cv = make_float2(0.0f, 0.0f);
-        ci[t] = 0;
-        if (g < stored) {
-            const int64_t e = (u * a.nsplit + sp) * a.cap + (g - before);
-            cv = a.cand[e];
-            ci[t] = a.cand_id[e];
-        }
+        float2 cv = e0;
+        ci[t] = id0;
+        if (J > 1) joined_entry(a, u, pre, stored, g, cv, ci[t]);
         lo[t] = g < stored ? float_key(cv.x - cv.y) : 0u;
         hi[t] = g < stored ? float_key(cv.x + cv.y) : 0u;
     }
     SelOut o{-INFINITY, 0, 0};
-    const uint32_t L = stored >= a.k ? wave_kth_key(lo, a.k) : 0u;
+    // (the k-th largest upper bound is the same with and without the entries
+    // below L*: at least k reach it)
+    uint32_t L = 0u, Hk = ~0u;
+    const bool pair = J == 1 && !a.topk;  // (for L* alone the chain is the shorter: 0.15, 0.19 ms)
+    if (stored >= a.k) {
+        if (pair) wave_kth_pair(lo[0], hi[0], stored, a.k, L, Hk);
+        else L = wave_kth_key(lo, a.k);
+    }
     if (stored >= a.k) o.Lstar = key_float(L);
     if (over) return o;
     // survivors: upper bound reaches L*; left to recompute: those whose lower
@@ -731,7 +766,7 @@ __device__ __forceinline__ SelOut select_regs(const ThreshArgs &a, int64_t u, in
         if (hi[t] < L) hi[t] = 0u;
         o.ns += __popcll(__ballot(hi[t] != 0u));
     }
-    const uint32_t Hk = a.topk ? ~0u : wave_kth_key(hi, a.k);
+    if (J > 1 && !a.topk) Hk = wave_kth_key(hi, a.k);
     const int64_t c0 = u * a.nsplit * (int64_t)a.cap;
 #pragma unroll
     for (int t = 0; t < J; ++t) {
@@ -754,29 +789,43 @@ void k_thresh_select(ThreshArgs a) {
     unsigned long long st_cand = 0, st_rec = 0;
     const int64_t step = (int64_t)gridDim.x * nw;
     int64_t pos = (int64_t)blockIdx.x * nw + w;
-    // the split counts of a user, one per lane, are read one user ahead
-    int64_t u = pos < nlist ? (int64_t)a.ulist[pos] : 0;
-    int cl = (pos < nlist && lane < a.nsplit) ? a.cand_cnt[u * a.nsplit + lane] : 0;
+    // the split counts of a user, one per lane (at most 16), are read two users
+    // ahead, and the entries of a list of up to 64 one user ahead
+    auto user_at = [&](int64_t p) { return p < nlist ? (int64_t)a.ulist[p] : 0; };
+    auto counts_of = [&](int64_t p, int64_t x) {
+        return (p < nlist && lane < a.nsplit) ? a.cand_cnt[x * a.nsplit + lane] : 0;
+    };
+    // inclusive prefix of the stored counts (in the first row of 16 lanes)
+    auto prefix_of = [&](int c) {
+        int p = c < a.cap ? c : a.cap;
+        p += dpp_from<0x111, 0xf>(0, p);
+        p += dpp_from<0x112, 0xf>(0, p);
+        p += dpp_from<0x114, 0xf>(0, p);
+        p += dpp_from<0x118, 0xf>(0, p);
+        return p;
+    };
+    int64_t u = user_at(pos), un = user_at(pos + step);
+    int cl = counts_of(pos, u), cn = counts_of(pos + step, un);
+    int pre = prefix_of(cl), stored = __builtin_amdgcn_readlane(pre, 15);
+    float2 cv = make_float2(0.0f, 0.0f);
+    int id = 0;
+    if (stored <= 64) joined_entry(a, u, pre, stored, lane, cv, id);
     for (; pos < nlist; pos += step) {
-        const int64_t np = pos + step;
-        const int64_t un = np < nlist ? (int64_t)a.ulist[np] : 0;
-        const int cn = (np < nlist && lane < a.nsplit) ? a.cand_cnt[un * a.nsplit + lane] : 0;
+        const int64_t u2 = user_at(pos + 2 * step);
+        const int c2 = counts_of(pos + 2 * step, u2);
+        const int pren = prefix_of(cn), storedn = __builtin_amdgcn_readlane(pren, 15);
+        float2 cvn = make_float2(0.0f, 0.0f);
+        int idn = 0;
+        if (storedn <= 64) joined_entry(a, un, pren, storedn, lane, cvn, idn);
         const bool over = __ballot(cl > a.cap) != 0ull;
-        int pre = cl < a.cap ? cl : a.cap;  // inclusive prefix of the stored counts
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int y = __shfl_up(pre, o);
-            if (lane >= o) pre += y;
-        }
-        const int stored = __builtin_amdgcn_readlane(pre, 63);
         SelOut o;
-        if (stored <= 64) o = select_regs<1>(a, u, pre, stored, over, lane);
-        else if (stored <= 128) o = select_regs<2>(a, u, pre, stored, over, lane);
-        else if (stored <= 256) o = select_regs<4>(a, u, pre, stored, over, lane);
-        else if (stored <= 512) o = select_regs<8>(a, u, pre, stored, over, lane);
+        if (stored <= 64) o = select_regs<1>(a, u, pre, stored, over, cv, id, lane);
+        else if (stored <= 128) o = select_regs<2>(a, u, pre, stored, over, cv, id, lane);
+        else if (stored <= 256) o = select_regs<4>(a, u, pre, stored, over, cv, id, lane);
+        else if (stored <= 512) o = select_regs<8>(a, u, pre, stored, over, cv, id, lane);
         else if (MAX == SEL_SHORT || stored <= SEL_SHORT)
-            o = select_regs<SEL_SHORT / 64>(a, u, pre, stored, over, lane);
-        else o = select_regs<MAX / 64>(a, u, pre, stored, over, lane);
+            o = select_regs<SEL_SHORT / 64>(a, u, pre, stored, over, cv, id, lane);
+        else o = select_regs<MAX / 64>(a, u, pre, stored, over, cv, id, lane);
         if (over) {
             // screened again from a tighter bound, or the exact fallback
             if (lane == 0) {
@@ -800,6 +849,12 @@ void k_thresh_select(ThreshArgs a) {
             a.cand_cnt[u * a.nsplit] = over ? -1 : (a.k - 1 - (o.ns - o.nrec)) | (o.nrec << 8);
         u = un;
         cl = cn;
+        pre = pren;
+        stored = storedn;
+        cv = cvn;
+        id = idn;
+        un = u2;
+        cn = c2;
     }
     if (cs && lane == 0) {
         if (st_cand) atomicAdd(cs, st_cand);
