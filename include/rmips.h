@@ -63,7 +63,8 @@ typedef enum {
 
 /* Screening precision of the dense products of stages (a) and (b). */
 typedef enum {
-    RMIPS_FP32 = 0,         /* FP32 inputs, FP32 matrix-core accumulation */
+    RMIPS_FP32 = 0,         /* FP32 inputs (from d = 32 on as two FP16 parts, hi +
+                               lo, per value), FP32 matrix-core accumulation */
     RMIPS_BF16 = 1,         /* BF16-rounded inputs, FP32 accumulation */
     RMIPS_FP8_E4M3 = 2,     /* OCP e4m3 inputs with a per-vector power-of-two
                                scale, FP32 accumulation */

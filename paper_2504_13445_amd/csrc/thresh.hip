@@ -73,7 +73,6 @@ __device__ __forceinline__ void merge32_desc(float (&v)[32]) {
 // in registers), two item-tile buffers in LDS (the next tile is copied in while
 // the current one is used; the registers allow one workgroup per CU, which
 // has the LDS to itself), nch 16-byte chunks per half row.
-constexpr int SCR_NW = 12;  // at most
 // 12 waves while a half row fits in 8 chunks, or 14 in BF16 (three waves
 // per SIMD, 168 registers each; longer rows would spill), 8 up
 // to 28 chunks (two per SIMD, 256 registers each: a wave's band test then
