@@ -82,6 +82,9 @@ size_t count_lds(int prec, int D) {
     return b;
 }
 
+int count_items(int prec, int D) { return 32 * count_waves(D * elem_bytes(prec) / 32); }
+bool count_windows(int prec) { return count_staged(prec); }
+
 // 16 bytes of an FP32 row from dim e, zeros past the row's d values; vec: rows
 // of whole 16-byte vectors
 __device__ __forceinline__ float4 row_vec(const float *__restrict__ r, int e, int d, bool vec) {

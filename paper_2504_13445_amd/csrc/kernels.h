@@ -193,6 +193,9 @@ void launch_count(const CountArgs &a, hipStream_t st);
 void launch_batch_order(int32_t *rows, int32_t *cid, int64_t nb, const int32_t *cs, int32_t *ulen,
                         hipStream_t st);
 size_t count_lds(int prec, int D);
+// items per counting workgroup, and whether rechecks go by window (wide bands)
+int count_items(int prec, int D);
+bool count_windows(int prec);
 
 struct BoundArgs {
     int ka;                            // augmented row length 16 KS: KS <= 11, or even up to 18

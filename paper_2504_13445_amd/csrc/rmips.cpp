@@ -673,6 +673,27 @@ int count_splits(int64_t nb, int64_t ulen, int maxs) {
     return (int)std::max<int64_t>(1, std::min<int64_t>(s, maxs));
 }
 
+// Splits for rmips_scores' queries: the fewest whole rounds of workgroups (one
+// per compute unit, 256) that are nine tenths full, because a workgroup's start
+// (its items' rows, the first chunk's copy) costs as much as some chunks, and a
+// round begun by a few workgroups as much as a whole one: 1000 queries x 500k
+// users, d = 100, FP32 in one round 0.45 ms, in two 0.50, in eight 0.54; 3000 at
+// d = 20 1.19 ms with 252 workgroups, 1.33 with 2052.  The wide bands'
+// rechecks differ from block to block and even out over more workgroups (200k
+// x 1000, d = 200, e4m3: one round 0.95, two 0.85, eight 0.77), as do those of
+// the few items past a whole block in a batch of the visit.
+int query_splits(int prec, int D, int64_t nq, int64_t n) {
+    if (!count_windows(prec)) {
+        const int64_t blocks = (nq + count_items(prec, D) - 1) / count_items(prec, D);
+        const int64_t smax = std::min<int64_t>(256, std::max<int64_t>(1, (n + 63) / 64 / 2));
+        for (int64_t r = 1; r <= 8; ++r) {
+            const int64_t s = std::min(256 * r / blocks, smax);
+            if (s * blocks * 10 >= 256 * r * 9) return (int)s;
+        }
+    }
+    return count_splits(nq, n, 256);
+}
+
 // Stage (c), first part: users sorted by their ratio keys without the low
 // 8 bits (3 passes instead of 4): each item's prefix may take users whose
 // ratio is up to 2^-15 relative above its norm, which the bound and the
@@ -1301,7 +1322,7 @@ rmips_status rmips_scores(rmips_ctx *ctx, const float *U, int64_t n, const doubl
     a.item_tie = q_ids; a.item_orig = nullptr; a.Porig = Q;
     a.Us = L.Uq; a.ulen = n; a.us = L.us; a.Uorig = U; a.d = d; a.D = L.D;
     a.c_err = ec.c; a.c2 = ec.c2; a.e_abs = E_ABS;
-    a.nsplit = count_splits(nq, n, 256);
+    a.nsplit = query_splits(L.prec, L.D, nq, n);
     a.partial = L.partial;
     a.rechecks = L.rech;
     HIPTRY(hipMemsetAsync(L.rech, 0, sizeof(int64_t), st));

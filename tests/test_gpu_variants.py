@@ -281,3 +281,17 @@ def test_recheck_windows(prec, n, q, d, noise):
     rm = _rm()
     got = rm.scores(_g(U), _g(t), _g(j), _g(Q), prec=prec)
     assert np.array_equal(got.cpu().numpy(), orc.reverse_counts_c(U, t, j, Q))
+
+
+# Queries by whole rounds of workgroups: one block and several, a last block of
+# one query, more blocks than a round holds, few users
+@pytest.mark.parametrize("prec,n,q,d", [("fp32", 40000, 257, 8), ("fp32", 40000, 129, 224),
+                                        ("bf16", 3000, 3000, 5), ("bf16", 300, 70000, 3),
+                                        ("fp32", 64, 2000, 33)])
+def test_query_rounds(prec, n, q, d):
+    _say("rounds", prec, n, q, d)
+    rng = np.random.default_rng(q)
+    U, P, Q = (synth.isotropic(rng, r, d, 0.3) for r in (n, 50, q))
+    t, j, _ = orc.kmips_c(U, P, 5)
+    got = _rm().scores(_g(U), _g(t), _g(j), _g(Q), prec=prec)
+    assert np.array_equal(got.cpu().numpy(), orc.reverse_counts_c(U, t, j, Q))
