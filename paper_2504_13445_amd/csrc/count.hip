@@ -1307,7 +1307,10 @@ void k_bound_table(BoundArgs a, BoundTableArgs bt) {
                     rl = 32 * (e >> 4) + mfma32_row(e & 15, lane);
                 }
                 const int64_t row = ib + RPW * w + rl;
-                if (row >= a.m) continue;  // padding rows
+                // padding rows; columns past the prefix, whose difference is
+                // +inf unless the product is +inf or NaN (the input check is
+                // read after this kernel)
+                if (row >= a.m || ul >= left) continue;
                 const int us = (int)(j * SU) + ul;
                 const int s = atomicAdd(&ln, 1);
                 if (s < BT_CAP) {

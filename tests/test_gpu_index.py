@@ -97,3 +97,24 @@ def test_index_rejects_bad_arguments():
     ri, rs = orc.topn_from_scores(orc.histogram_scores(tk, 200), 5)
     ids, sc, _ = idx.topn(3, 5)
     assert ids.tolist() == ri.tolist() and sc.tolist() == rs.tolist()
+
+
+# A NaN or an Inf makes products without a sign to rely on, in every user
+# column of a stage (those past the last user included): the build must stay
+# within its arrays, report the input, and leave the context usable.  Row
+# lengths of both matrix-core steps (up to 176 terms and past them)
+@pytest.mark.parametrize("n,m,d", [(65, 130, 20), (1001, 577, 50), (129, 700, 200)])
+@pytest.mark.parametrize("bad", ["nan_user", "nan_item", "inf_user", "inf_item", "all_nan_items"])
+def test_index_rejects_nonfinite_input(n, m, d, bad):
+    import paper_2504_13445_amd as rm
+    from paper_2504_13445_amd import _lib
+    print("[case] index nonfinite", n, m, d, bad, flush=True)
+    rng = np.random.default_rng(n)
+    U, P = synth.isotropic(rng, n, d, 0.3), synth.isotropic(rng, m, d, 0.6)
+    Ub, Pb = U.copy(), P.copy()
+    x = Ub if bad.endswith("user") else Pb
+    x[slice(None) if bad == "all_nan_items" else 3, 1] = np.inf if bad.startswith("inf") else np.nan
+    with pytest.raises(rm.RmipsError) as e:
+        rm.Index(_g(Ub), _g(Pb), 5)
+    assert e.value.status == _lib.RMIPS_ENONFINITE
+    _check_index(U, P, "fp32", (1, 5), (10,), kmax=5)
