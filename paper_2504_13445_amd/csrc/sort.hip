@@ -375,7 +375,7 @@ hipError_t radix_sort_u32(uint32_t *keys, int32_t *vals, int64_t n, void *scratc
                           hipStream_t st, int lo_bit, int hi_bit) {
     if (n <= 1 || hi_bit <= lo_bit) return hipSuccess;
     if (lo_bit < 0 || hi_bit > 32) return hipErrorInvalidValue;
-    const int npass = (hi_bit - lo_bit + 7) / 8;
+    int npass = (hi_bit - lo_bit + 7) / 8;
     if (n <= BLOCK_SORT) {
         RMIPS_PROF(st, "k_block_sort");
         auto go = [&](auto rc) {
@@ -389,6 +389,12 @@ hipError_t radix_sort_u32(uint32_t *keys, int32_t *vals, int64_t n, void *scratc
         else go(std::integral_constant<int, BLOCK_SORT / BLOCK_SORT_THREADS>{});
         return hipGetLastError();
     }
+    // A pass of several blocks does not write where it reads: a block's writes
+    // would meet elements that another has yet to load.  So a single pass is
+    // followed by a second one on eight more bits (those above hi_bit, the same
+    // in every key, or again the last eight): it keeps the order and brings the
+    // result back.
+    if (npass == 1) npass = 2;
     const int rounds = sort_rounds(n), chunk = SORT_THREADS * rounds;
     const int nblocks = (int)((n + chunk - 1) / chunk);
     const bool small = nblocks <= PREFIX_MAX_BLOCKS;
@@ -418,11 +424,12 @@ hipError_t radix_sort_u32(uint32_t *keys, int32_t *vals, int64_t n, void *scratc
     const uint32_t *ks = keys;
     const int32_t *vs = vals;
     for (int q = 0; q < npass; ++q) {
-        const int shift = lo_bit + 8 * q;
+        const int shift = std::min(lo_bit + 8 * q, 24);
         const bool last = q == npass - 1;
         uint32_t *kd = last ? keys : ((q & 1) ? k2 : k1);
         int32_t *vd = last ? vals : ((q & 1) ? v2 : v1);
         uint32_t *cq = counts + q * total;
+        const int next = last ? -1 : std::min(lo_bit + 8 * (q + 1), 24);
         if (!small) {
             RMIPS_PROF(st, "k_scan");
             k_scan_reduce<<<ntiles, SORT_THREADS, 0, st>>>(cq, total, tsum);
@@ -431,10 +438,10 @@ hipError_t radix_sort_u32(uint32_t *keys, int32_t *vals, int64_t n, void *scratc
         RMIPS_PROF(st, "k_radix_scatter");
         if (rounds == SORT_R_SMALL)
             k_radix_scatter<SORT_R_SMALL><<<nblocks, SORT_THREADS, 0, st>>>(
-                ks, vs, kd, vd, n, shift, last ? -1 : shift + 8, nblocks, cq, cq + total);
+                ks, vs, kd, vd, n, shift, next, nblocks, cq, cq + total);
         else
             k_radix_scatter<SORT_R_LARGE><<<nblocks, SORT_THREADS, 0, st>>>(
-                ks, vs, kd, vd, n, shift, last ? -1 : shift + 8, nblocks, cq, cq + total);
+                ks, vs, kd, vd, n, shift, next, nblocks, cq, cq + total);
         ks = kd;
         vs = vd;
     }

@@ -295,3 +295,39 @@ def test_query_rounds(prec, n, q, d):
     t, j, _ = orc.kmips_c(U, P, 5)
     got = _rm().scores(_g(U), _g(t), _g(j), _g(Q), prec=prec)
     assert np.array_equal(got.cpu().numpy(), orc.reverse_counts_c(U, t, j, Q))
+
+
+# Sorts on at most eight key bits (the visit order of fewer than 256 users, the
+# step (5) ranges of fewer than 255 items) of more elements than one workgroup
+# takes: a pass never writes where it reads.  Blocks of 1,024 and 4,096, and
+# with scans
+@pytest.mark.parametrize("n,m,N", [(200, 8193, 1000), (255, 20000, 1000), (31, 140000, 200),
+                                   (3, 524289, 60)])
+def test_sort_few_bits_visit(n, m, N):
+    _say("few bits, visit", n, m)
+    rng = np.random.default_rng(m)
+    U, P = synth.isotropic(rng, n, 6, 0.3), synth.isotropic(rng, m, 6, 0.3)
+    k = 30
+    _, _, tk = orc.kmips_c(U, P, k)
+    ri, rs = orc.topn_from_scores(orc.histogram_scores(tk, m), N)
+    for dprime in (None, 2):  # (loose bounds: long runs of equal keys)
+        ids, s, _ = _rm().topn(_g(U), _g(P), k, N, dprime=dprime, batch=(64, 256))
+        assert ids.tolist() == ri.tolist() and s.tolist() == rs.tolist()
+
+
+@pytest.mark.parametrize("n,m", [(20000, 200), (150000, 120)])
+def test_sort_few_bits_budget(n, m):
+    _say("few bits, budget", n, m)
+    rng = np.random.default_rng(n)
+    U, P = synth.isotropic(rng, n, 12, 0.3), synth.isotropic(rng, m, 12, 0.2)
+    kmax, N = 5, 40
+    bi = _rm().BudgetIndex(_g(U), _g(P), kmax, kmax + 1, 2 * n, "uniform")
+    assert bi.info["u_dprime"] > 8192
+    us = bi.state()["uscore"].cpu().numpy()
+    _, _, tk = orc.kmips_c(U, P, kmax)
+    for k in (1, kmax):
+        sc = orc.histogram_scores(tk[:, :k], m)
+        assert np.all(us[k - 1] >= sc)
+        ids, s, _ = bi.topn(k, N)
+        ri, rs = orc.topn_from_scores(sc, N)
+        assert ids.tolist() == ri.tolist() and s.tolist() == rs.tolist()
