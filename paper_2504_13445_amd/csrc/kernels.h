@@ -121,7 +121,7 @@ struct ThreshArgs {
     // items (norm order): quantized rows (ntiles * 64), N, Nh, R, scale per item
     const void *Pq; const float *Np; const float *Nhp; const float *Rp; const float *sp;
     const float *tmax_nh; const float *tmax_r;  // per tile maxima of Nh and R
-    const unsigned int *rmax_bits;              // largest R/N over the items
+    const unsigned int *rmax_bits;              // largest ratio of a tile's largest R and N
     const int32_t *perm; int64_t m; int ntiles;
     const float *U; const float *P; int d;      // original FP32 rows (recheck)
     int D; int k; int t0tiles; int nsplit; int cap;

@@ -55,8 +55,9 @@ void launch_rows_prep(const float *X, int64_t rows, int d, int D, float *Xpad, f
 // s (FP8: the smallest with max |x_i| / s <= 448, but at least 2^-63 so
 // that 1/s and the product of two scales' reciprocals stay finite; split
 // FP32: max |x_i| / s <= 2^15 likewise; FP32 and BF16: 1).  Per row: N = ||x||, Nh = ||xq||, R = ||x - xq|| (FP64
-// sums, rounded up to FP32), sc = s; the largest R/N of the rows goes to
-// *rmax (a monotone atomic maximum of non-negative floats).
+// sums, rounded up to FP32), sc = s; the largest ratio over the blocks of their
+// largest R and largest N goes to *rmax (a monotone atomic maximum of
+// non-negative floats).
 //
 // Subnormal operands: the matrix cores may flush them to zero, so the
 // copy never holds one.  An FP32 or BF16 value below 2^-126 in magnitude,
@@ -190,7 +191,7 @@ __global__ __launch_bounds__(256) void k_quant(const float *__restrict__ X,
             }
         }
     }
-    float rrmax = 0.0f, nhmax = 0.0f, rmxv = 0.0f;
+    float nmax = 0.0f, nhmax = 0.0f, rmxv = 0.0f;
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
         const int64_t r = r0 + 16 * g + 4 * w + rq;
@@ -295,33 +296,35 @@ __global__ __launch_bounds__(256) void k_quant(const float *__restrict__ X,
                 R[r] = rr;
                 sc[r] = s;
             }
+            nmax = fmaxf(nmax, nx);
             nhmax = fmaxf(nhmax, nh);
             rmxv = fmaxf(rmxv, rr);
-            if (rmax && nx > 0.0f && rr > 0.0f)
-                rrmax = fmaxf(rrmax, __double2float_ru((double)rr / (double)nx));
         }
     }
-    // the block's largest Nh and R (tmax), and its largest R / N: one atomic
-    // per block (non-negative floats order like their bit patterns)
+    // the block's largest Nh and R (tmax), and its largest R over its largest N:
+    // one atomic per block (non-negative floats order like their bit patterns)
     if (rmax || tmax_nh) {
 #pragma unroll
         for (int o = 16; o < 64; o <<= 1) {
             nhmax = fmaxf(nhmax, __shfl_xor(nhmax, o));
             rmxv = fmaxf(rmxv, __shfl_xor(rmxv, o));
-            rrmax = fmaxf(rrmax, __shfl_xor(rrmax, o));
+            nmax = fmaxf(nmax, __shfl_xor(nmax, o));
         }
         if (lane == 0) {
             wmx[0][w] = nhmax;
             wmx[1][w] = rmxv;
-            wmx[2][w] = rrmax;
+            wmx[2][w] = nmax;
         }
         __syncthreads();
-        if (threadIdx.x < 3) {
-            const float *q = wmx[threadIdx.x];
-            const float m = fmaxf(fmaxf(q[0], q[1]), fmaxf(q[2], q[3]));
+        if (threadIdx.x < 2) {
+            auto largest = [&](int i) {
+                return fmaxf(fmaxf(wmx[i][0], wmx[i][1]), fmaxf(wmx[i][2], wmx[i][3]));
+            };
+            const float m = largest(threadIdx.x);
             if (threadIdx.x == 0 && tmax_nh) tmax_nh[blockIdx.x] = m;
             if (threadIdx.x == 1 && tmax_r) tmax_r[blockIdx.x] = m;
-            if (threadIdx.x == 2 && rmax && m > 0.0f) atomicMax(rmax, __float_as_uint(m));
+            if (threadIdx.x == 1 && rmax && m > 0.0f)
+                atomicMax(rmax, __float_as_uint(__double2float_ru((double)m / (double)largest(2))));
         }
     }
 }
@@ -340,7 +343,7 @@ __global__ __launch_bounds__(256) void k_quant_mx(const float *__restrict__ X,
     // 64 rows per block, 16 per wave; a row's values (D <= 256: at most 4
     // per lane) stay in registers between the two passes
     __shared__ float rowmax[64];
-    __shared__ float rmx[4];
+    __shared__ float wmx[2][4];
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t r0 = (int64_t)blockIdx.x * 64;
@@ -389,7 +392,7 @@ __global__ __launch_bounds__(256) void k_quant_mx(const float *__restrict__ X,
     // pass 2: quantize with the group's scale, residual sums in FP64; four
     // rows at a time, whose lane sums are reduced together (each row's sums
     // in the same order as alone)
-    float rrmax = 0.0f;
+    float nmax = 0.0f, rmxv = 0.0f;
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
         double sx[4], sq[4], sr[4];
@@ -483,19 +486,25 @@ __global__ __launch_bounds__(256) void k_quant_mx(const float *__restrict__ X,
                 Nh[r] = __double2float_ru(sqrt(sq[jj]) * up);
                 R[r] = rr;
                 sc[r] = sc4[jj];
-                if (nx > 0.0f && rr > 0.0f)
-                    rrmax = fmaxf(rrmax, __double2float_ru((double)rr / (double)nx));
+                nmax = fmaxf(nmax, nx);
+                rmxv = fmaxf(rmxv, rr);
             }
         }
     }
-    // largest R / N of the block, one atomic per block (non-negative floats
-    // order like their bit patterns)
+    // the block's largest R over its largest N, as in k_quant
     if (rmax) {
-        if (lane == 0) rmx[w] = rrmax;
+        if (lane == 0) {
+            wmx[0][w] = rmxv;
+            wmx[1][w] = nmax;
+        }
         __syncthreads();
         if (threadIdx.x == 0) {
-            const float m = fmaxf(fmaxf(rmx[0], rmx[1]), fmaxf(rmx[2], rmx[3]));
-            if (m > 0.0f) atomicMax(rmax, __float_as_uint(m));
+            auto largest = [&](int i) {
+                return fmaxf(fmaxf(wmx[i][0], wmx[i][1]), fmaxf(wmx[i][2], wmx[i][3]));
+            };
+            const float m = largest(0);
+            if (m > 0.0f)
+                atomicMax(rmax, __float_as_uint(__double2float_ru((double)m / (double)largest(1))));
         }
     }
 }

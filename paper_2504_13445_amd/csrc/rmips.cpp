@@ -312,7 +312,7 @@ void thresh_scratch_plan(int prec, int64_t n, int64_t m, int d, int k, int cap_o
     L.uord = cv.take<int32_t>(n);
     L.usort = cv.take<uint8_t>(radix_sort_scratch_bytes(n));
     L.nall = cv.take<int32_t>(64);
-    // the input flag and the largest R/N share a block (one fill clears both)
+    // the input flag and the tiles' largest R/N share a block (one fill clears both)
     L.bad = cv.take<int>(64);
     L.rmax = reinterpret_cast<unsigned int *>(L.bad + 32);
 }

@@ -331,3 +331,27 @@ def test_sort_few_bits_budget(n, m):
         ids, s, _ = bi.topn(k, N)
         ri, rs = orc.topn_from_scores(sc, N)
         assert ids.tolist() == ri.tolist() and s.tolist() == rs.tolist()
+
+
+# Items far smaller than their tile's largest (whose scale they share) are
+# stored as zero, but the norm-ordered scan ends where it does with zero rows
+# in their place
+@pytest.mark.parametrize("prec", ["fp32", "bf16", "fp8", "fp6"])
+@pytest.mark.parametrize("scale", [1e-6, 1e-10, 1e-16])
+def test_near_zero_items_keep_scan_end(prec, scale):
+    _say("near-zero items", prec, scale)
+    rng = np.random.default_rng(3)
+    n, m, d, k = 700, 6000, 48, 8
+    U, P = synth.isotropic(rng, n, d, 0.2), synth.isotropic(rng, m, d, 0.8)
+    small = [7, 3000, m - 1]
+    P[small] /= np.linalg.norm(P[small], axis=1, keepdims=True)
+    P0 = P.copy()
+    P[small] *= np.float32(scale)
+    P0[small] = 0.0
+    _, _, tk = orc.kmips_c(U, P, k)
+    ri, rs = orc.topn_from_scores(orc.histogram_scores(tk, m), 30)
+    ids, s, st = _rm().topn(_g(U), _g(P), k, 30, prec)
+    assert ids.tolist() == ri.tolist() and s.tolist() == rs.tolist()
+    st0 = _rm().topn(_g(U), _g(P0), k, 30, prec)[2]
+    assert st["thresh_pairs"] <= 1.02 * st0["thresh_pairs"]
+    assert st0["thresh_pairs"] < 0.8 * n * m  # (the scan does end early)
