@@ -50,13 +50,16 @@ void launch_rows_prep(const float *X, int64_t rows, int d, int D, float *Xpad, f
                                                             val, flag);
 }
 
-// Padded, quantized copy of rows, 64 rows per block.  Row r of the output is row order[r] of X (identity if NULL);
-// rows past `rows` are zero.  Rows of a group share one power-of-two scale
-// s (FP8: the smallest with max |x_i| / s <= 448, but at least 2^-63 so
-// that 1/s and the product of two scales' reciprocals stay finite; split
-// FP32: max |x_i| / s <= 2^15 likewise; FP32 and BF16: 1).  Per row: N = ||x||, Nh = ||xq||, R = ||x - xq|| (FP64
-// sums, rounded up to FP32), sc = s; the largest ratio over the blocks of their
-// largest R and largest N goes to *rmax (a monotone atomic maximum of
+// Padded, quantized copy of rows, 64 rows per block.  Row r of the output is
+// row order[r] of X (identity if NULL); rows past `rows` are zero.  Rows of a
+// group share one power-of-two scale s: for the 8-, 6- and 4-bit formats the
+// smallest with max |x_i| / s <= the format's largest value, but at least 2^-63,
+// for split FP32 rows the smallest with max |x_i| / s <= 2^15, but at least
+// 2^-126, the smallest normal FP32 value; FP32 and BF16: 1.  1/s is then finite
+// (the screens divide by one scale after the other: the product of two
+// reciprocals would not be).  Per row: N = ||x||, Nh = ||xq||, R = ||x - xq||
+// (FP64 sums, rounded up to FP32), sc = s; the largest ratio over the blocks of
+// their largest R and largest N goes to *rmax (a monotone atomic maximum of
 // non-negative floats).
 //
 // Subnormal operands: the matrix cores may flush them to zero, so the
@@ -102,7 +105,8 @@ __device__ __forceinline__ float row16_max(float x) {
     x = fmaxf(x, dpp_row_f32<0x122>(x));
     return fmaxf(x, dpp_row_f32<0x121>(x));
 }
-// The smallest power of two s >= 2^-63 with m / s <= the format's largest value.
+// The smallest power of two s with m / s <= the format's largest value, from
+// 2^-126 (split rows) or 2^-63 on.
 template <int PREC> __device__ __forceinline__ float pow2_scale(float m) {
     if (!(m > 0.0f)) return 1.0f;
     constexpr float FMAX = mx_max(PREC);
@@ -110,7 +114,7 @@ template <int PREC> __device__ __forceinline__ float pow2_scale(float m) {
     frexpf(m / FMAX, &e);  // m/FMAX = f * 2^e, f in [0.5, 1)
     float s = ldexpf(1.0f, e);
     if (m / ldexpf(1.0f, e - 1) <= FMAX) s = ldexpf(1.0f, e - 1);
-    return fmaxf(s, 0x1p-63f);
+    return fmaxf(s, PREC == PREC_SPLIT ? 0x1p-126f : 0x1p-63f);
 }
 
 // NG: 128-value parts of a row (D <= 128 NG)
@@ -207,7 +211,8 @@ __global__ __launch_bounds__(256) void k_quant(const float *__restrict__ X,
                 const float t = v[g][p][e];
                 // (values below 2^-126 are zero in the copy)
                 const bool sub = fabsf(t) < 0x1p-126f;
-                float qv;
+                float qv = 0.0f;
+                double qd;  // the copy's value
                 lo[e] = 0u;
                 if constexpr (PREC == PREC_FP32) {
                     qv = sub ? 0.0f : t;
@@ -231,11 +236,12 @@ __global__ __launch_bounds__(256) void k_quant(const float *__restrict__ X,
                     uint16_t l;
                     code[e] = to_split(sub ? 0.0f : t * inv, l, yq);
                     lo[e] = l;
-                    qv = yq * s;
+                    qd = (double)yq * (double)s;  // (below 2^-126 not always an FP32 value)
                 }
+                if constexpr (PREC != PREC_SPLIT) qd = (double)qv;
                 sx = __fma_rn((double)t, (double)t, sx);
-                sq = __fma_rn((double)qv, (double)qv, sq);
-                const double df = (double)t - (double)qv;  // exact: both are FP32
+                sq = __fma_rn(qd, qd, sq);
+                const double df = (double)t - qd;  // exact
                 sr = __fma_rn(df, df, sr);
             }
             // the codes of 8 consecutive values (VEC) or of 8 values 16 apart

@@ -199,16 +199,18 @@ void k_thresh_screen(ThreshArgs a) {
         uint4 ub[NCH];
         load_half_row<NCH>(ub, reinterpret_cast<const uint8_t *>(a.Uq), ug, uvalid, rowb, nch,
                            lane);
-        const float nu = uvalid ? a.Nu[ug] : 0.0f;
-        const float nhu = uvalid ? a.Nhu[ug] : 0.0f;
-        const float ru = uvalid ? a.Ru[ug] : 0.0f;
-        const float su = uvalid ? a.su[ug] : 1.0f;
-        const float su_inv = pow2_rcp(su);
+        // all values and bounds of a user are taken in units of its scale, a
+        // power of two (the same bits, and rows of any magnitude stay in range)
+        const float su = uvalid ? a.su[ug] : 1.0f, su_inv = pow2_rcp(su);
+        const float nu = uvalid ? a.Nu[ug] * su_inv : 0.0f;
+        const float nhu = uvalid ? a.Nhu[ug] * su_inv : 0.0f;
+        const float ru = uvalid ? a.Ru[ug] * su_inv : 0.0f;
+        const float e_abs = a.e_abs * su_inv;
 
         // error bound of this user against an item: E(u,p)
         auto ebound = [&](float n_p, float nh_p, float r_p) {
             return fmaf(ru, n_p,
-                        fmaf(nhu, r_p, fmaf(a.c_err * nhu, nh_p, fmaf(a.c2 * nu, n_p, a.e_abs))));
+                        fmaf(nhu, r_p, fmaf(a.c_err * nhu, nh_p, fmaf(a.c2 * nu, n_p, e_abs))));
         };
         // exit ratio: with N_t the largest norm of item p's tile, vh + E <=
         // K_u * N_t + 2 e_abs (R_p <= rmax N_t), so no item of a tile with N_t
@@ -218,15 +220,15 @@ void k_thresh_screen(ThreshArgs a) {
             if (uvalid) {
                 const float K = nu * (1.0f + a.g64 + 2.0f * a.c2) + 2.0f * ru +
                                 2.0f * nhu * (rmax + a.c_err * (1.0f + rmax));
-                rr = (L > 2.0f * a.e_abs && K > 0.0f) ? (L - 2.0f * a.e_abs) / K * (1.0f - 0x1p-20f)
-                                                      : 0.0f;
+                rr = (L > 2.0f * e_abs && K > 0.0f) ? (L - 2.0f * e_abs) / K * (1.0f - 0x1p-20f)
+                                                    : 0.0f;
             }
             return wave_min(rr);
         };
 
         float L0 = -INFINITY, rwg = INFINITY;
         if (listed) {
-            L0 = uvalid ? a.Luse[ug] : INFINITY;
+            L0 = uvalid ? a.Luse[ug] * su_inv : INFINITY;
             const float rr = exit_ratio(L0);
             if (lane == 0) red[w] = rr;
         }
@@ -266,7 +268,7 @@ void k_thresh_screen(ThreshArgs a) {
                 const float *Nsh = Nbase + buf * NSTRIDE;
                 const int64_t rb = (int64_t)t * TILE_ITEMS;
                 const float e_t = ebound(Nsh[0], Nsh[3 * TILE_ITEMS], Nsh[3 * TILE_ITEMS + 1]);
-                const float sc = su * Nsh[3 * TILE_ITEMS + 2];
+                const float sc = Nsh[3 * TILE_ITEMS + 2];
                 f32x16 acc0 = {0}, acc1 = {0};
                 MMR<PREC, NCH>::rows2(acc0, acc1, Psh, Psh + 32 * ls, ub, ls, nch, D, (a.d + 1) / 2, lane);
 #pragma unroll
@@ -300,7 +302,7 @@ void k_thresh_screen(ThreshArgs a) {
         if constexpr (!LISTED) {
             // the bounds-only pass (the launch without a user list): keep L0
             // and go to the next block
-            if (split == 0 && lane < 32 && uvalid) a.Luse[ug] = L0;
+            if (split == 0 && lane < 32 && uvalid) a.Luse[ug] = L0 * su;
             continue;
         }
         // phase 2 (tiles split, split + nsplit, ...): candidates vh + E >= L0
@@ -319,12 +321,12 @@ void k_thresh_screen(ThreshArgs a) {
             // tile maxima: N is sorted (first item), Nh and R staged with the tile
             const float e_t = ebound(Nsh[0], Nsh[3 * TILE_ITEMS], Nsh[3 * TILE_ITEMS + 1]);
             const float sp_t = Nsh[3 * TILE_ITEMS + 2];
-            const float sc = su * sp_t;  // product scale of this (user, tile)
             f32x16 acc0 = {0}, acc1 = {0};
             MMR<PREC, NCH>::rows2(acc0, acc1, Psh, Psh + 32 * ls, ub, ls, nch, D, (a.d + 1) / 2, lane);
-            // first on the tile bound, then per item; the scales are powers of
-            // two, so multiplying by their exact reciprocals divides exactly
-            const float thr = (L0 - e_t) * (su_inv * pow2_rcp(sp_t));
+            // first on the tile bound, then per item; the tile's scale is a power
+            // of two too, so multiplying by its exact reciprocal divides exactly
+            // (where that overflows no product, at most 2^38, reaches it)
+            const float thr = (L0 - e_t) * pow2_rcp(sp_t);
             // (a linear chain: it compiles to three-input maxima)
             float vmax = acc0[0];
 #pragma unroll
@@ -346,11 +348,11 @@ void k_thresh_screen(ThreshArgs a) {
                     pend &= pend - 1u;
                     const int r = mfma32_row(i & 15, lane) + (i >> 4) * 32;
                     if (rb + r >= a.m) continue;  // padding rows of the last tile
-                    const float v = pick32(acc0, acc1, i) * sc;
+                    const float v = pick32(acc0, acc1, i) * sp_t;
                     const float eb = ebound(Nsh[r], Nsh[TILE_ITEMS + r], Nsh[2 * TILE_ITEMS + r]);
                     if (v + eb >= L0) {
                         if (myc < half) {
-                            mycand[myc] = make_float2(v, eb);
+                            mycand[myc] = make_float2(v * su, eb * su);
                             mycid[myc] = __float_as_int(Nsh[4 * TILE_ITEMS + r]);
                         }
                         ++myc;
@@ -362,8 +364,6 @@ void k_thresh_screen(ThreshArgs a) {
             buf ^= 1;
         }
         if (listed && uvalid) a.cand_cnt[(ug * a.nsplit + split) * 2 + hw] = myc;
-        // the bound this pass used (equal for the two lanes of a user)
-        if (!listed && split == 0 && lane < 32 && uvalid) a.Luse[ug] = L0;
         pacc += (unsigned long long)(ntile_p2 * TILE_ITEMS * nub);
     }
     if (a.pairs && tid == 0 && pacc)
@@ -418,7 +418,8 @@ void k_thresh_screen_u2(ThreshArgs a) {
         bool uvalid[2];
         int64_t ug[2];
         uint4 ub0[NCH], ub1[NCH];
-        float nu[2], nhu[2], ru[2], su[2], su_inv[2], L0[2];
+        // (in units of the user's scale, as in k_thresh_screen)
+        float nu[2], nhu[2], ru[2], su[2], e_abs[2], L0[2];
         float2 *mycand[2];
         int32_t *mycid[2];
         int myc[2] = {0, 0};
@@ -428,20 +429,21 @@ void k_thresh_screen_u2(ThreshArgs a) {
             const int64_t pos = blk * TU + w * 64 + 32 * h + (lane & 31);
             uvalid[h] = pos < nlist;
             ug[h] = uvalid[h] ? (int64_t)a.ulist[pos] : 0;
-            nu[h] = uvalid[h] ? a.Nu[ug[h]] : 0.0f;
-            nhu[h] = uvalid[h] ? a.Nhu[ug[h]] : 0.0f;
-            ru[h] = uvalid[h] ? a.Ru[ug[h]] : 0.0f;
             su[h] = uvalid[h] ? a.su[ug[h]] : 1.0f;
-            su_inv[h] = pow2_rcp(su[h]);
-            L0[h] = uvalid[h] ? a.Luse[ug[h]] : INFINITY;
+            const float su_inv = pow2_rcp(su[h]);
+            nu[h] = uvalid[h] ? a.Nu[ug[h]] * su_inv : 0.0f;
+            nhu[h] = uvalid[h] ? a.Nhu[ug[h]] * su_inv : 0.0f;
+            ru[h] = uvalid[h] ? a.Ru[ug[h]] * su_inv : 0.0f;
+            e_abs[h] = a.e_abs * su_inv;
+            L0[h] = uvalid[h] ? a.Luse[ug[h]] * su_inv : INFINITY;
             mycand[h] = a.cand + (ug[h] * a.nsplit + split) * a.cap + hw * half;
             mycid[h] = a.cand_id + (ug[h] * a.nsplit + split) * a.cap + hw * half;
             // exit ratio as in k_thresh_screen
             if (uvalid[h]) {
                 const float K = nu[h] * (1.0f + a.g64 + 2.0f * a.c2) + 2.0f * ru[h] +
                                 2.0f * nhu[h] * (rmax + a.c_err * (1.0f + rmax));
-                const float r = (L0[h] > 2.0f * a.e_abs && K > 0.0f)
-                                    ? (L0[h] - 2.0f * a.e_abs) / K * (1.0f - 0x1p-20f)
+                const float r = (L0[h] > 2.0f * e_abs[h] && K > 0.0f)
+                                    ? (L0[h] - 2.0f * e_abs[h]) / K * (1.0f - 0x1p-20f)
                                     : 0.0f;
                 rr = fminf(rr, r);
             }
@@ -454,7 +456,7 @@ void k_thresh_screen_u2(ThreshArgs a) {
         if (lane == 0) red[w] = rr;
         auto ebound = [&](int h, float n_p, float nh_p, float r_p) {
             return fmaf(ru[h], n_p, fmaf(nhu[h], r_p,
-                                         fmaf(a.c_err * nhu[h], nh_p, fmaf(a.c2 * nu[h], n_p, a.e_abs))));
+                                         fmaf(a.c_err * nhu[h], nh_p, fmaf(a.c2 * nu[h], n_p, e_abs[h]))));
         };
         tile_copy<NW>(a, tile_of(0), rowb, w16, magic, ls, Pbase, Nbase, 0, w, lane);
         dma_wait();
@@ -483,8 +485,7 @@ void k_thresh_screen_u2(ThreshArgs a) {
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const float e_t = ebound(h, Nsh[0], Nsh[3 * TILE_ITEMS], Nsh[3 * TILE_ITEMS + 1]);
-                const float sc = su[h] * sp_t;
-                const float thr = (L0[h] - e_t) * (su_inv[h] * pow2_rcp(sp_t));
+                const float thr = (L0[h] - e_t) * pow2_rcp(sp_t);
                 float vmax = acc[h][0][0];
 #pragma unroll
                 for (int i = 1; i < 16; ++i) vmax = fmaxf(vmax, acc[h][0][i]);
@@ -503,12 +504,12 @@ void k_thresh_screen_u2(ThreshArgs a) {
                         pend &= pend - 1u;
                         const int r = mfma32_row(i & 15, lane) + (i >> 4) * 32;
                         if (rb + r >= a.m) continue;  // padding rows of the last tile
-                        const float v = pick32(acc[h][0], acc[h][1], i) * sc;
+                        const float v = pick32(acc[h][0], acc[h][1], i) * sp_t;
                         const float eb =
                             ebound(h, Nsh[r], Nsh[TILE_ITEMS + r], Nsh[2 * TILE_ITEMS + r]);
                         if (v + eb >= L0[h]) {
                             if (myc[h] < half) {
-                                mycand[h][myc[h]] = make_float2(v, eb);
+                                mycand[h][myc[h]] = make_float2(v * su[h], eb * su[h]);
                                 mycid[h][myc[h]] = __float_as_int(Nsh[4 * TILE_ITEMS + r]);
                             }
                             ++myc[h];

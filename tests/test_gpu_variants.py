@@ -355,3 +355,45 @@ def test_near_zero_items_keep_scan_end(prec, scale):
     st0 = _rm().topn(_g(U), _g(P0), k, 30, prec)[2]
     assert st["thresh_pairs"] <= 1.02 * st0["thresh_pairs"]
     assert st0["thresh_pairs"] < 0.8 * n * m  # (the scan does end early)
+
+
+# Rows of small and of very different magnitudes with FP32 screening: a power
+# of two on the users or the items changes no screened pair's band, so the
+# candidates stay what they are without it
+@pytest.mark.parametrize("su,sp", [(-70, 0), (0, -70), (-36, -36), (30, -90), (-95, 40)])
+def test_split_rows_small_magnitudes(su, sp):
+    _say("small magnitudes", su, sp)
+    rng = np.random.default_rng(8)
+    n, m, d, k = 700, 3000, 48, 8
+    U, P = synth.isotropic(rng, n, d, 0.2), synth.isotropic(rng, m, d, 0.6)
+    st0 = _rm().topn(_g(U), _g(P), k, 20)[2]
+    Us, Ps = U * np.float32(2.0 ** su), P * np.float32(2.0 ** sp)
+    _, _, tk = orc.kmips_c(Us, Ps, k)
+    ri, rs = orc.topn_from_scores(orc.histogram_scores(tk, m), 20)
+    ids, s, st = _rm().topn(_g(Us), _g(Ps), k, 20)
+    assert ids.tolist() == ri.tolist() and s.tolist() == rs.tolist()
+    for key in ("thresh_pairs", "cand_listed", "cand_pairs"):
+        assert st[key] <= 1.02 * st0[key] + 10, key
+
+
+# The ends of the range: values down to 2^-126 (the products then lie below
+# every band, and all pairs are decided in FP64), rows and items that differ
+# by 2^150, one row of each
+@pytest.mark.parametrize("d", [32, 75, 200])
+def test_split_rows_extreme_magnitudes(d):
+    _say("extreme magnitudes", d)
+    rng = np.random.default_rng(d)
+    n, m, k = 200, 260, 7
+    for eu, ep in [(-60, -60), (-118, 55), (55, -118), (-118, -20), (50, 50)]:
+        U = synth.isotropic(rng, n, d, 0.3) * np.float32(2.0 ** eu)
+        P = synth.isotropic(rng, m, d, 0.6) * np.float32(2.0 ** ep)
+        U[::7] = synth.isotropic(rng, len(U[::7]), d, 0.0)
+        P[::9] = synth.isotropic(rng, len(P[::9]), d, 0.0)
+        U, P = U.astype(np.float32), P.astype(np.float32)
+        t, j, tk = orc.kmips_c(U, P, k)
+        tau, tid, topk = _rm().thresholds(_g(U), _g(P), k, with_topk=True)
+        assert np.array_equal(tau.cpu().numpy().view(np.uint64), t.view(np.uint64)), (eu, ep)
+        assert np.array_equal(tid.cpu().numpy(), j) and np.array_equal(topk.cpu().numpy(), tk)
+        ids_all = torch.arange(m, dtype=torch.int32, device=_dev())
+        sc = _rm().scores(_g(U), tau, tid, _g(P), ids_all)
+        assert np.array_equal(sc.cpu().numpy(), orc.histogram_scores(tk, m)), (eu, ep)
