@@ -1146,6 +1146,12 @@ __host__ __device__ constexpr int bound_items(int ks) {
 // workgroup takes a few stages of one block only (4: 0.44 ms, 8: 0.67, a
 // sixteenth of the block's prefix: 3.7 ms).
 //
+// A pair that passes takes 45 to 105 ps (many in one entry of the table), a pass
+// per k some 0.13 ps per pair, so that with many of them the passes per k are
+// the shorter way: with norms so small that the bound's absolute slack admits
+// every pair 89 ms here against 6.3.  k_bound_sample therefore counts them in a
+// sample first, and where it finds more than `limit` this pass does nothing.
+//
 // Products in the same steps and order as the pass per k (k_bound and
 // k_bound_lds, or k_bound16 from KS = 12 on), so that the counts agree to the
 // last pair.  8 waves of 64 (48) items; stages of bt_users(KS) users in LDS.
@@ -1158,9 +1164,34 @@ constexpr size_t bt_lds_bytes(int ks) {
     return 2 * (size_t)bt_users(ks) * ((2 * ks + 1) * 16 + 4) + BT_CAP * 12;
 }
 
+// BOUND_SAMPLE pairs spread over the users (in rho order) and the items, one per
+// lane: *hits (cleared before) counts those that pass the bound within the
+// item's prefix.  8 us in an index call of 100k x 20k, most of them the launch.
+__global__ __launch_bounds__(256) void k_bound_sample(BoundArgs a, int64_t n,
+                                                      unsigned int *__restrict__ hits) {
+    const uint32_t t = blockIdx.x * 256 + threadIdx.x;
+    const int64_t us = (int64_t)((uint64_t)t * (uint64_t)n / BOUND_SAMPLE);
+    const int64_t it = (int64_t)(((uint64_t)(t * 2654435769u) * (uint64_t)a.m) >> 32);
+    bool hit = false;
+    if (us < a.cs[it]) {
+        const int words = a.ka / 8;  // 16-byte words per row
+        const uint4 *u = a.Ub + us * words, *p = a.Pb + it * words;
+        float s = 0.0f;
+        for (int w = 0; w < words; ++w) {
+            const bf16x8 x = __builtin_bit_cast(bf16x8, u[w]), y = __builtin_bit_cast(bf16x8, p[w]);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) s = fmaf((float)x[e], (float)y[e], s);
+        }
+        hit = s > a.tau_b[us];
+    }
+    const uint64_t bal = __ballot(hit);
+    if ((threadIdx.x & 63) == 0 && bal != 0ull) atomicAdd(hits, (unsigned)__popcll(bal));
+}
+
 template <int KS>
 __global__ __launch_bounds__(64 * BLW) __attribute__((amdgpu_waves_per_eu(2)))
 void k_bound_table(BoundArgs a, BoundTableArgs bt) {
+    if (*bt.hits > bt.limit) return;
     constexpr bool F16 = KS >= 12;  // 16x16x32 steps, 16-row tiles
     constexpr int TI = F16 ? 3 : 2, RPW = F16 ? 48 : 64, BI = bt_items(KS);
     constexpr int NQ = F16 ? KS / 2 : KS;      // steps per product
@@ -1356,6 +1387,10 @@ template <class F> void with_ks(int ks, F &&f) {
 }
 
 void launch_bound_table(const BoundArgs &a0, const BoundTableArgs &t0, int64_t n, hipStream_t st) {
+    {
+        RMIPS_PROF(st, "k_bound_sample");
+        k_bound_sample<<<BOUND_SAMPLE / 256, 256, 0, st>>>(a0, n, t0.hits);
+    }
     RMIPS_PROF(st, "k_bound_table");
     with_ks(a0.ka / 16, [&](auto ks) {
         constexpr int KS = decltype(ks)::value, BI = bt_items(KS);

@@ -213,7 +213,10 @@ int bound_splits(int64_t m, int ka, int smax = 16);
 // (kmax x m, norm order, cleared before) gets the pairs whose smallest k is
 // k0, so that the prefix sums over the rows are the counts that launch_bound
 // gives for each k.  a: the rows, order, thresholds and prefixes of kmax (no
-// partial counts).
+// partial counts).  *hits (cleared before) gets the number of BOUND_SAMPLE pairs
+// that pass the bound of kmax; where it is above `limit` the table is left as it
+// is (launch_bound for each k is then the shorter way).
+constexpr int BOUND_SAMPLE = 65536;
 struct BoundTableArgs {
     const double *topv;    // users' kmax largest values, caller order
     const int32_t *uperm;  // sorted position -> user
@@ -221,6 +224,7 @@ struct BoundTableArgs {
     const float *Np;       // ||p|| rounded up, norm order
     int kmax;
     int32_t *table;
+    unsigned int *hits, limit;
     int chunk;             // set by launch_bound_table: stages of users per workgroup
 };
 void launch_bound_table(const BoundArgs &a, const BoundTableArgs &t, int64_t n, hipStream_t st);

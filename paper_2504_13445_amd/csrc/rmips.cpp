@@ -356,6 +356,9 @@ rmips_status defer_check(rmips_ctx *ctx, const int *bad) {
     return RMIPS_OK;
 }
 
+// word beside the input flag that an index build counts sampled pairs in
+constexpr int TAB_HITS = 1;
+
 // Stage (a) into (tau, tau_id, topk); also leaves the prepared item/user
 // arrays of L in the workspace for later stages.
 rmips_status run_thresholds(rmips_ctx *ctx, const float *U, int64_t n, const float *P,
@@ -659,8 +662,16 @@ void index_query_plan(int64_t n, int64_t m, const IndexLayout &I, PrefixLayout &
 // 25, 0.14% of the pairs: build 7.8 -> 1.8 ms; 300k x 30k x 200, kmax = 3: 6.9 ->
 // 5.7 ms.  A rotation's bound lets too many pass (d' = 10 there: 33%, 6.5 ms by
 // passes per k, 49.9 ms by the one pass), and for one k the pass per k is the
-// shorter one (3.9 against 4.7 ms).
+// shorter one (3.9 against 4.7 ms).  Where a sample says that the data let more
+// pairs pass, the passes per k are taken after all.  A pair that passes costs up
+// to 105 ps; a pass per k costs 0.13 ps per pair, 1 ns per user (its sort) and 50
+// us (its launches): the line is where the two meet, as sampled pairs.
 constexpr int BOUND_TABLE_KMAX = 3;
+unsigned bound_table_limit(int64_t n, int64_t m, int kmax) {
+    const double pairs = (double)n * (double)m;
+    const double share = kmax * (pairs / 770 + 10.0 * (double)n + 500000.0) / pairs;
+    return (unsigned)(BOUND_SAMPLE * std::min(1.0, share));
+}
 
 // splits of the user range of a counting launch: about four rounds of
 // counting workgroups (256 items each, one per compute unit), each split
@@ -1529,7 +1540,8 @@ size_t rmips_index_workspace_size(int64_t n, int64_t m, int32_t d, int32_t kmax,
 // The index's header, read back (a synchronisation) before any launch that
 // takes item or user indices from the index: an index built with other
 // sizes has its arrays at other offsets, and those would not be indices.
-constexpr int H_HDR = 64;  // pinned status words that receive it
+constexpr int H_HDR = 64;    // pinned status words that receive it
+constexpr int H_FLAGS = 72;  // and a build's input flag and count of sampled pairs
 static rmips_status check_index_header(rmips_ctx *ctx, const int32_t *hdr_dev, int64_t n,
                                        int64_t m, int32_t d, int32_t kmax, rmips_prec prec) {
     HIPTRY(hipMemcpyAsync(ctx->h_status + H_HDR, hdr_dev, sizeof(int32_t) * INDEX_HDR_WORDS,
@@ -1612,7 +1624,20 @@ rmips_status rmips_index_build(rmips_ctx *ctx, const float *U, int64_t n, const 
     const double *Wd = rotate ? I.W : nullptr;
     launch_rotate_aug(P, T.perm, m, T.mpad, d, Wd, dp, ka, 1.0f, B.Pa, st);
     launch_invert_perm(T.perm, m, I.inv, st);
-    if (!rotate && kmax >= BOUND_TABLE_KMAX) {
+    // users in the rho order of each k's thresholds, one bound pass per k
+    // (row k - 1 of the table)
+    auto bounds_per_k = [&]() {
+        for (int k = 1; k <= kmax; ++k) {
+            launch_kth_column(I.topv, I.topk, n, kmax, k, X.tau, X.tau_id, st);
+            run_prefix(T, X, n, m, ec.c2, st, false);
+            run_bound(U, X, B, Wd, dp, n, m, T.mpad, d, nullptr, nullptr, nullptr,
+                      I.table + (size_t)(k - 1) * m, st);
+        }
+    };
+    const bool one_pass = !rotate && kmax >= BOUND_TABLE_KMAX;
+    unsigned *hits = reinterpret_cast<unsigned *>(T.bad + TAB_HITS);
+    const unsigned limit = bound_table_limit(n, m, kmax);
+    if (one_pass) {
         // the bound of every item for every k: users in the rho order of
         // kmax's thresholds, each counted pair in the row of its smallest k,
         // then prefix sums over the rows
@@ -1623,24 +1648,26 @@ rmips_status rmips_index_build(rmips_ctx *ctx, const float *U, int64_t n, const 
         ba.ka = ka;
         ba.Pb = B.Pa; ba.m = m; ba.mpad = T.mpad; ba.Ub = B.Ua; ba.tau_b = X.us.tau_b;
         ba.cs = X.cs;
-        launch_bound_table(ba, {I.topv, X.uperm, T.Nu, T.Np, kmax, I.table, 0}, n, st);
+        launch_bound_table(ba, {I.topv, X.uperm, T.Nu, T.Np, kmax, I.table, hits, limit, 0}, n,
+                           st);
         launch_budget_prefix_k(I.table, m, kmax, st);
     } else {
-        // users in the rho order of each k's thresholds, one bound pass per
-        // k (row k - 1 of the table)
-        for (int k = 1; k <= kmax; ++k) {
-            launch_kth_column(I.topv, I.topk, n, kmax, k, X.tau, X.tau_id, st);
-            run_prefix(T, X, n, m, ec.c2, st, false);
-            run_bound(U, X, B, Wd, dp, n, m, T.mpad, d, nullptr, nullptr, nullptr,
-                      I.table + (size_t)(k - 1) * m, st);
-        }
+        bounds_per_k();
     }
     HIPTRY(hipGetLastError());
     // the build waits for its work and reports its input check itself
-    HIPTRY(hipMemcpyAsync(ctx->h_status, T.bad, sizeof(int), hipMemcpyDeviceToHost, st));
+    // (pinned words; the count too, in one copy)
+    int32_t *h_flags = ctx->h_status + H_FLAGS;
+    HIPTRY(hipMemcpyAsync(h_flags, T.bad, (TAB_HITS + 1) * sizeof(int), hipMemcpyDeviceToHost, st));
     HIPTRY(hipStreamSynchronize(st));
     ctx->prof.resolve();
-    if (ctx->h_status[0] != 0) return fail(ctx, RMIPS_ENONFINITE, BAD_INPUT);
+    if (h_flags[0] != 0) return fail(ctx, RMIPS_ENONFINITE, BAD_INPUT);
+    if (one_pass && (unsigned)h_flags[TAB_HITS] > limit) {
+        bounds_per_k();
+        HIPTRY(hipGetLastError());
+        HIPTRY(hipStreamSynchronize(st));
+        ctx->prof.resolve();
+    }
     int32_t *hdr = ctx->h_status + H_HDR;  // pinned
     int32_t want[INDEX_HDR_WORDS];
     index_header(n, m, d, kmax, prec, dp, want);

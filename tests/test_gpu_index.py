@@ -118,3 +118,34 @@ def test_index_rejects_nonfinite_input(n, m, d, bad):
         rm.Index(_g(Ub), _g(Pb), 5)
     assert e.value.status == _lib.RMIPS_ENONFINITE
     _check_index(U, P, "fp32", (1, 5), (10,), kmax=5)
+
+
+# The table of all k takes one bound pass where a sample of the pairs says that
+# few pass the bound; where many do (norms so small that the bound's absolute
+# slack admits every pair, a catalogue of nearly equal items) the bounds come
+# from a pass per k.  Either way they are rmips_topn's bounds of each k.
+@pytest.mark.parametrize("d", [20, 200])
+@pytest.mark.parametrize("kind", ["plain", "small_users", "most_small_users", "equal_items"])
+def test_index_bounds_passes(kind, d):
+    import paper_2504_13445_amd as rm
+    print("[case] index passes", kind, d, flush=True)
+    rng = np.random.default_rng(d)
+    n, m, kmax = 6000, 6000, 3
+    U, P = synth.isotropic(rng, n, d, 0.3), synth.isotropic(rng, m, d, 0.6)
+    if kind == "small_users":
+        U *= np.float32(2.0 ** -70)
+    elif kind == "most_small_users":
+        U[np.arange(n) % 4 != 0] *= np.float32(2.0 ** -70)
+    elif kind == "equal_items":
+        P = (P[:1] + 1e-3 * P).astype(np.float32)
+    Ug, Pg = _g(U), _g(P)
+    rm.set_profiling(True)
+    idx = rm.Index(Ug, Pg, kmax)
+    launches = {name: c for name, c, _ in rm.profile()}
+    rm.set_profiling(False)
+    assert launches["k_bound_table"] == 1
+    assert launches.get("k_bound", 0) == (0 if kind == "plain" else kmax)
+    for k in range(1, kmax + 1):
+        b = torch.empty(m, dtype=torch.int32, device=_dev())
+        rm.topn(Ug, Pg, k, 5, bound_out=b, prepass=0)
+        assert torch.equal(idx.bounds(k), b), k
