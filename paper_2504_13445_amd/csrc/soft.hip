@@ -256,11 +256,13 @@ void k_soft(const float *__restrict__ U, int64_t n, const float *__restrict__ ta
 // out[q][c] = scale_q * (sum over slices k of P[k][q][c]) in FP64, c < width
 // (G), and for the last column of workgroups out_s[q] = the sum of S's slices.
 // One workgroup per query and 64 columns: each of its SR_WAVES waves adds its
-// share of the slices in slice order (loads in batches of 8; S: 64 slices at a
-// time across the lanes), then the partial sums are added in wave order, a
-// fixed order in every call.  The chain of loads bounds it: 16 waves instead of
-// 4, 235 slices of 40 x 64 values 6 us (10 us).
-constexpr int SR_WAVES = 16;
+// share of the slices in slice order (loads in batches of 8; S: four
+// waves, 64 slices at a time across their lanes), then the partial sums are added in wave order, a
+// fixed order in every call.  Latency bounds it: the chain of loads where a few
+// workgroups add many slices (235 of 40 x 64 values: 7.2 us with 16 waves, 7.5
+// with 4), else the waves in flight (2 slices of 3000 x 100 values 8.0 us with 4
+// waves, 22.7 with 16; 48 of 2000 x 32 8.1 and 15.3; 384 of 256 x 100 10.9 both).
+template <int SR_WAVES>
 __global__ __launch_bounds__(64 * SR_WAVES) void k_soft_reduce(
     const float *__restrict__ P, int nsplit, int64_t cols, int64_t ld_in, int64_t width,
     const float *__restrict__ dS, float *__restrict__ out, int64_t ld_out,
@@ -273,8 +275,9 @@ __global__ __launch_bounds__(64 * SR_WAVES) void k_soft_reduce(
     const bool ok = is_s || c < width;
     double s = 0.0;
     if (is_s) {
-        for (int k = w * 64 + lane; k < nsplit; k += 64 * SR_WAVES) s += (double)Sp[(int64_t)k * cols + q];
-        // (the lanes in a fixed tree)
+        // (four waves, whatever SR_WAVES is, and the lanes in a fixed tree)
+        if (w < 4)
+            for (int k = w * 64 + lane; k < nsplit; k += 256) s += (double)Sp[(int64_t)k * cols + q];
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
     } else if (ok) {
@@ -415,17 +418,23 @@ void launch_soft(const float *U, int64_t n, const float *tau, const float *Q, in
     RMIPS_PROF(st, "k_soft_reduce");
     // (S with G or dQ, in a column of workgroups of its own)
     const int gc = (d + 63) / 64;
+    auto reduce = [&](dim3 rg, const float *P, int64_t ld_in, int64_t width, const float *scale,
+                      float *out, float *out_s, int gcols) {
+        // (the same sums whether S is asked for with G or not)
+        if (nsplit >= 128 && nq * gc <= 256)
+            k_soft_reduce<16><<<rg, 64 * 16, 0, st>>>(P, nsplit, nq, ld_in, width, scale, out, d,
+                                                      spart, out_s, gcols);
+        else
+            k_soft_reduce<4><<<rg, 64 * 4, 0, st>>>(P, nsplit, nq, ld_in, width, scale, out, d,
+                                                    spart, out_s, gcols);
+    };
     if (wg) {
         const bool both = G && dQ;
-        k_soft_reduce<<<dim3((unsigned)nq, (unsigned)(gc + (S ? 1 : 0))), 64 * SR_WAVES, 0, st>>>(
-            gpart, nsplit, nq, sd.Dg, d, G ? nullptr : dS, G ? G : dQ, d, spart, S, gc);
-        if (both)
-            k_soft_reduce<<<dim3((unsigned)nq, (unsigned)gc), 64 * SR_WAVES, 0, st>>>(
-                gpart, nsplit, nq, sd.Dg, d, dS, dQ, d, nullptr, nullptr, gc);
+        reduce(dim3((unsigned)nq, (unsigned)(gc + (S ? 1 : 0))), gpart, sd.Dg, d, G ? nullptr : dS,
+               G ? G : dQ, S, gc);
+        if (both) reduce(dim3((unsigned)nq, (unsigned)gc), gpart, sd.Dg, d, dS, dQ, nullptr, gc);
     } else {
-        k_soft_reduce<<<dim3((unsigned)nq, 1u), 64 * SR_WAVES, 0, st>>>(nullptr, nsplit, nq, 0, 0,
-                                                                        nullptr, nullptr, 0, spart,
-                                                                        S, 0);
+        reduce(dim3((unsigned)nq, 1u), nullptr, 0, 0, nullptr, nullptr, S, 0);
     }
 }
 

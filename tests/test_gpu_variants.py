@@ -397,3 +397,28 @@ def test_split_rows_extreme_magnitudes(d):
         ids_all = torch.arange(m, dtype=torch.int32, device=_dev())
         sc = _rm().scores(_g(U), tau, tid, _g(P), ids_all)
         assert np.array_equal(sc.cpu().numpy(), orc.histogram_scores(tk, m)), (eu, ep)
+
+
+# Reductions of the relaxed score by 4 and by 16 waves (from 128 slices on for at
+# most 256 workgroups of the gradient), around both lines, with the same sums in
+# every entry point; the tolerance of test_soft_slices
+@pytest.mark.parametrize("n,d,nq", [(127 * 64, 20, 5), (127 * 64 + 1, 20, 5), (20000, 70, 128),
+                                    (20000, 70, 129), (9000, 64, 255), (9000, 64, 257),
+                                    (100, 9, 700)])
+def test_soft_reductions(n, d, nq):
+    _say("soft reductions", n, d, nq)
+    rng = np.random.default_rng(n + nq)
+    U = synth.isotropic(rng, n, d, 0.25)
+    Q = (rng.standard_normal((nq, d)) / np.sqrt(d)).astype(np.float32)
+    tau = rng.uniform(0.2, 0.6, n).astype(np.float32)
+    T = 0.1
+    S64 = orc.soft_score(U, tau.astype(np.float64), Q, T)
+    G64 = orc.soft_grad(U, tau.astype(np.float64), Q, T)
+    rm = _rm()
+    a = (_g(U), _g(tau), _g(Q), T)
+    S, G = rm.soft_fwd_grad(*a)
+    assert torch.equal(rm.soft_fwd(*a), S)
+    assert torch.equal(rm.soft_bwd(*a, torch.ones(nq, device=_dev())), G)
+    S, G = (x.cpu().numpy().astype(np.float64) for x in (S, G))
+    assert np.all(np.abs(S - S64) <= 1e-4 * S64)
+    assert np.all(np.linalg.norm(G - G64, axis=1) <= 1e-4 * np.linalg.norm(G64, axis=1))
