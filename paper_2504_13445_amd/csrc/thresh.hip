@@ -710,9 +710,12 @@ __device__ float wave_kth_largest(const float *x, int n, int k, int lane) {
 // (0.72 and 2.0 ms), of which reading the counts two users and the entries one
 // user ahead is 0.03 and 0.2 ms.
 constexpr int SEL_MAX = 2048;
-// lists up to SEL_SHORT leave registers for four waves per SIMD, up to
-// SEL_MID (e4m3, k = 20) for three, longer ones for two
-constexpr int SEL_SHORT = 1024, SEL_MID = 1280;
+// lists up to SEL_SHORT leave registers for four waves per SIMD (118), up to
+// SEL_MID for three (166 of 168), longer ones for two; a launch is one round of
+// the workgroups that are resident then (with four to a CU throughout, three
+// resident and a partial second round: e4m3, k = 20, 300k users 1.14 ms for
+// 0.92; k = 24 1.29 for 1.05, and 1.39 with two waves)
+constexpr int SEL_SHORT = 1024, SEL_MID = 1536;
 struct SelOut {
     float Lstar;      // k-th largest lower bound of the stored entries (-inf: fewer than k)
     int nrec, ns;     // entries left to recompute, survivors
@@ -785,8 +788,9 @@ __device__ __forceinline__ SelOut select_regs(const ThreshArgs &a, int64_t u, in
     return o;
 }
 
+constexpr int sel_waves(int max) { return max <= SEL_SHORT ? 4 : max <= SEL_MID ? 3 : 2; }
 template <int MAX>  // longest list
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MAX <= SEL_SHORT ? 4 : MAX <= SEL_MID ? 3 : 2)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sel_waves(MAX))))
 void k_thresh_select(ThreshArgs a) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
     const int64_t nlist = (int64_t)*a.ulist_cnt;
@@ -1633,13 +1637,17 @@ void launch_thresh(const ThreshArgs &a0, hipStream_t st) {
         ThreshArgs h = a;
         h.nsplit = 2 * a.nsplit;
         h.cap = a.cap / 2;
-        const unsigned sblocks = (unsigned)std::min<int64_t>((a0.n + 3) / 4, 4 * 256);
         if (capT <= SEL_MAX) {
             RMIPS_PROF(st, nf);
-            // one resident round
-            if (capT <= SEL_SHORT) k_thresh_select<SEL_SHORT><<<sblocks, 256, 0, st>>>(h);
-            else if (capT <= SEL_MID) k_thresh_select<SEL_MID><<<sblocks, 256, 0, st>>>(h);
-            else k_thresh_select<SEL_MAX><<<sblocks, 256, 0, st>>>(h);
+            auto select = [&](auto mx) {
+                constexpr int MAX = decltype(mx)::value;
+                // one resident round: a 4-wave workgroup per wave of a SIMD
+                const int64_t sblocks = std::min<int64_t>((a0.n + 3) / 4, 256 * sel_waves(MAX));
+                k_thresh_select<MAX><<<(unsigned)sblocks, 256, 0, st>>>(h);
+            };
+            if (capT <= SEL_SHORT) select(std::integral_constant<int, SEL_SHORT>{});
+            else if (capT <= SEL_MID) select(std::integral_constant<int, SEL_MID>{});
+            else select(std::integral_constant<int, SEL_MAX>{});
         } else {
             RMIPS_PROF(st, nf);
             k_thresh_final<true><<<(unsigned)fblocks, 64 * fw, lds_fin, st>>>(h, capT, capP);

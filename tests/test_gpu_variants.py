@@ -422,3 +422,23 @@ def test_soft_reductions(n, d, nq):
     S, G = (x.cpu().numpy().astype(np.float64) for x in (S, G))
     assert np.all(np.abs(S - S64) <= 1e-4 * S64)
     assert np.all(np.linalg.norm(G - G64, axis=1) <= 1e-4 * np.linalg.norm(G64, axis=1))
+
+
+# The selection's variants by the lists' capacity (64 k with e4m3: up to 1024,
+# 1536 and 2048 entries), at the values of k on both sides of each line, with
+# lists from short to nearly full
+@pytest.mark.parametrize("k", [16, 17, 24, 25, 32])
+@pytest.mark.parametrize("noise", [0.0, 0.02, 0.4])
+def test_selection_capacities(k, noise):
+    _say("selection capacities", k, noise)
+    rng = np.random.default_rng(k)
+    n, m, d = 1500, 64 * k - 40, 24
+    U = synth.isotropic(rng, n, d, 0.3)
+    P = (synth.isotropic(rng, 1, d, 0.0) + noise * rng.standard_normal((m, d))).astype(np.float32)
+    t, j, tk = orc.kmips_c(U, P, k)
+    for topk in (False, True):
+        r = _rm().thresholds(_g(U), _g(P), k, "fp8", with_topk=topk)
+        assert np.array_equal(r[0].cpu().numpy().view(np.uint64), t.view(np.uint64)), topk
+        assert np.array_equal(r[1].cpu().numpy(), j), topk
+        if topk:
+            assert np.array_equal(r[2].cpu().numpy(), tk)
