@@ -265,6 +265,8 @@ def kernel_table(prof, stats, steps, n, m, d, k, prec):
         # bytes: FP32 rows read, screening copies and four per-row floats written
         "k_quant": ((n + m) * (4.0 * d + D * eb + 16.0), "byte", HBM_PEAK, "hbm"),
         # candidate lists read (value, bound, id: 12 B each), tau and id written
+        # (the selection in registers, or in LDS where the lists may be longer)
+        "k_thresh_select/main": (12.0 * avg("cand_listed") + 12.0 * n, "byte", HBM_PEAK, "hbm"),
         "k_thresh_final/main": (12.0 * avg("cand_listed") + 12.0 * n, "byte", HBM_PEAK, "hbm"),
         # users' screening rows in rho order, gathered once, and their records
         # (28 bytes read, 40 written)
@@ -272,7 +274,7 @@ def kernel_table(prof, stats, steps, n, m, d, k, prec):
     }
     table = {}
     # (the stage (a) recomputations, cand_pairs FP32 item rows gathered, are
-    # shared by k_thresh_final, k_thresh_exact and k_thresh_exact_wide in
+    # shared by k_thresh_exact, k_thresh_exact_wide and k_thresh_final in
     # proportions the statistics do not give: no per-kernel work for them)
     for name, launches, ms in prof:
         e = {"launches_per_step": launches / steps, "ms_per_step": ms / steps,

@@ -568,8 +568,8 @@ constexpr int FIN_WAVES = 4;
 constexpr int FIN_WPE = 4;  // waves per SIMD of the final selection
 constexpr int FIN_ENTRY_BYTES = 12;  // LDS bytes per list entry of the final selection
 size_t final_entry_bytes() { return FIN_ENTRY_BYTES; }
-// recomputations per user handed from k_thresh_final to k_thresh_exact;
-// more, up to EXACT_WIDE, go to k_thresh_exact_wide
+// recomputations per user handed from the selection to k_thresh_exact; more, up
+// to EXACT_WIDE, go to k_thresh_exact_wide
 constexpr int EXACT_SLOTS = 8;
 constexpr int EXACT_WIDE = 2048;
 constexpr int EXACT_REGS = 1024;  // values ranked in registers
@@ -1632,13 +1632,13 @@ void launch_thresh(const ThreshArgs &a0, hipStream_t st) {
     // the screening pass writes each (user, split) list as two halves of
     // cap / 2 entries with their own counts: the final selection and the
     // deferred recomputations read them as 2 * nsplit lists
-    auto final = [&](const ThreshArgs &a, int capT, const char *nf, const char *ne,
-                     const char *nw) {
+    auto final = [&](const ThreshArgs &a, int capT, const char *ns, const char *nf,
+                     const char *ne, const char *nw) {
         ThreshArgs h = a;
         h.nsplit = 2 * a.nsplit;
         h.cap = a.cap / 2;
         if (capT <= SEL_MAX) {
-            RMIPS_PROF(st, nf);
+            RMIPS_PROF(st, ns);
             auto select = [&](auto mx) {
                 constexpr int MAX = decltype(mx)::value;
                 // one resident round: a 4-wave workgroup per wave of a SIMD
@@ -1693,7 +1693,8 @@ void launch_thresh(const ThreshArgs &a0, hipStream_t st) {
     if (a.ev0) (void)hipEventRecord(a.ev0, st);
     screen(a, dim3((unsigned)ublocks, (unsigned)a.nsplit), "k_thresh_screen/main");
     if (a.ev1) (void)hipEventRecord(a.ev1, st);
-    final(a, capU, "k_thresh_final/main", "k_thresh_exact/main", "k_thresh_exact_wide/main");
+    final(a, capU, "k_thresh_select/main", "k_thresh_final/main", "k_thresh_exact/main",
+          "k_thresh_exact_wide/main");
     // refinement passes over the users whose lists overflowed: the same
     // per-user capacity in fewer, longer lists per split
     int nsr = capU / 64;
@@ -1714,7 +1715,7 @@ void launch_thresh(const ThreshArgs &a0, hipStream_t st) {
         // are usually empty, and the workgroups loop over long ones
         const int64_t gx = ublocks < 256 / nsr ? ublocks : 256 / nsr;
         screen(b, dim3((unsigned)gx, (unsigned)nsr), "k_thresh_screen/refine");
-        final(b, b.nsplit * b.cap, "k_thresh_final/refine", nullptr,
+        final(b, b.nsplit * b.cap, "k_thresh_select/refine", "k_thresh_final/refine", nullptr,
               "k_thresh_exact_wide/refine");
     }
     int64_t fb = (a0.n + FB_WAVES - 1) / FB_WAVES;

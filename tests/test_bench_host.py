@@ -40,3 +40,13 @@ def test_bound_work_without_prepass():
     mpad = (m + 63) // 64 * 64
     assert t["k_aug_ident"]["work_per_launch"] == ((n + m) * 4.0 * d + (n + mpad) * 2.0 * 112) / 2
     assert "k_bound/rebound" not in t
+
+
+def test_selection_work_under_either_name():
+    # the selection has the name of the kernel that ran; its bytes are the
+    # lists' entries and a threshold per user
+    n, m, d = 20000, 3000, 100
+    prof = [("k_thresh_select/main", 2, 1.0), ("k_thresh_final/main", 1, 1.0)]
+    t = bench.kernel_table(prof, _stats(0, 0, 0.0), 1, n, m, d, 10, "fp8")
+    assert t["k_thresh_select/main"]["work_per_launch"] == 12.0 * (1.0e6 + n) / 2
+    assert t["k_thresh_final/main"]["work_per_launch"] == 12.0 * (1.0e6 + n)

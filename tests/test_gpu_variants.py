@@ -442,3 +442,20 @@ def test_selection_capacities(k, noise):
         assert np.array_equal(r[1].cpu().numpy(), j), topk
         if topk:
             assert np.array_equal(r[2].cpu().numpy(), tk)
+
+
+# Per-launch times carry the name of the kernel that ran: the selection in
+# registers up to lists of 2,048 entries, in LDS beyond (e2m1 at k = 32: 4,096)
+@pytest.mark.parametrize("prec,k,name", [("fp32", 10, "k_thresh_select"), ("fp8", 32, "k_thresh_select"),
+                                         ("fp4", 32, "k_thresh_final")])
+def test_selection_profile_name(prec, k, name):
+    _say("selection name", prec, k)
+    rng = np.random.default_rng(1)
+    U, P = _g(synth.isotropic(rng, 300, 20, 0.3)), _g(synth.isotropic(rng, 600, 20, 0.5))
+    rm = _rm()
+    rm.set_profiling(True)
+    rm.thresholds(U, P, k, prec)
+    names = {x[0].split("/")[0] for x in rm.profile()}
+    rm.set_profiling(False)
+    assert name in names
+    assert names & {"k_thresh_select", "k_thresh_final"} == {name}
