@@ -12,7 +12,7 @@ SOURCES = ["sort.hip", "prep.hip", "thresh.hip", "count.hip", "soft.hip", "budge
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-         "-Wall", "-Wno-unused-function", "-I", os.path.join(HERE, "..", "include")]
+         "-Wall", "-I", os.path.join(HERE, "..", "include")]
 
 
 # per-source extra flags: the bound kernel's matrix-core results go to

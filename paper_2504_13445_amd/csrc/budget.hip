@@ -28,13 +28,6 @@ __device__ __forceinline__ bool ranks_before(double v1, int id1, double v2, int 
     return v1 > v2 || (v1 == v2 && id1 < id2);
 }
 
-// exact u . p: FP64, products of FP32 values (exact), summed in index order
-__device__ __forceinline__ double ip64_rows(const float *u, const float *p, int d) {
-    double acc = 0.0;
-    for (int i = 0; i < d; ++i) acc = __fma_rn((double)u[i], (double)p[i], acc);
-    return acc;
-}
-
 // Eq. (3) on rotated coordinates: u^l . p^l + |u^r| |p^r| plus a relative
 // slack covering the rotation's rounding and its deviation from
 // orthonormality (both far below 2^-30 of |u| |p|)

@@ -42,10 +42,6 @@ hipError_t radix_sort_u32(uint32_t *keys, int32_t *vals, int64_t n, void *scratc
 void launch_rows_prep(const float *X, int64_t rows, int d, int D, float *Xpad,
                       float *norm, uint32_t *key, int32_t *val, int *flag,
                       hipStream_t st);
-// Pk[r] = P[perm[r]] for r < m, zero rows for m <= r < rows_pad; Np likewise.
-void launch_gather_rows(const float *P, const int32_t *perm, const float *norm_by_id,
-                        int64_t m, int64_t rows_pad, int d, int D, float *Pk,
-                        float *Np, hipStream_t st);
 // inv[perm[r]] = r
 void launch_invert_perm(const int32_t *perm, int64_t m, int32_t *inv, hipStream_t st);
 

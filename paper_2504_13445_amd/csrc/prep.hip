@@ -576,30 +576,6 @@ void launch_tile_max(const float *Nh, const float *R, int ntiles, float *tmax_nh
     k_tile_max<<<(unsigned)((ntiles + 3) / 4), 256, 0, st>>>(Nh, R, ntiles, tmax_nh, tmax_r);
 }
 
-__global__ void k_gather_rows(const float *__restrict__ P, const int32_t *__restrict__ perm,
-                              const float *__restrict__ nb_id, int64_t m, int64_t rows_pad,
-                              int d, int D, float *__restrict__ Pk, float *__restrict__ Np) {
-    const int lane = threadIdx.x & 63;
-    const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (r >= rows_pad) return;
-    if (r < m) {
-        const int64_t src = perm[r];
-        for (int i = lane; i < D; i += 64) Pk[r * D + i] = (i < d) ? P[src * d + i] : 0.0f;
-        if (lane == 0) Np[r] = nb_id[src];
-    } else {
-        for (int i = lane; i < D; i += 64) Pk[r * D + i] = 0.0f;
-        if (lane == 0) Np[r] = 0.0f;
-    }
-}
-
-void launch_gather_rows(const float *P, const int32_t *perm, const float *norm_by_id,
-                        int64_t m, int64_t rows_pad, int d, int D, float *Pk, float *Np,
-                        hipStream_t st) {
-    RMIPS_PROF(st, "k_gather_rows");
-    k_gather_rows<<<(unsigned)((rows_pad + 3) / 4), 256, 0, st>>>(P, perm, norm_by_id, m,
-                                                                  rows_pad, d, D, Pk, Np);
-}
-
 __global__ void k_invert_perm(const int32_t *__restrict__ perm, int64_t m,
                               int32_t *__restrict__ inv) {
     int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -801,8 +777,6 @@ void launch_gram(const float *X, int64_t ns, int64_t stride, int d, double *G, d
 // g * Kq + s (Kq = ceil(d / 4)), so each lane reads one contiguous quarter of
 // its row.  W is staged once per workgroup in LDS in the same order:
 // Wt[(s * 4 + g) * 64 + j] = W[j][g * Kq + s].
-constexpr int DP_MAX = 62;
-constexpr int KA_MAX = 64;
 constexpr int ROT_WAVES = 8;
 typedef double d4_t __attribute__((ext_vector_type(4)));
 

@@ -363,7 +363,7 @@ void k_thresh_screen(ThreshArgs a) {
             __syncthreads();
             buf ^= 1;
         }
-        if (listed && uvalid) a.cand_cnt[(ug * a.nsplit + split) * 2 + hw] = myc;
+        if (uvalid) a.cand_cnt[(ug * a.nsplit + split) * 2 + hw] = myc;
         pacc += (unsigned long long)(ntile_p2 * TILE_ITEMS * nub);
     }
     if (a.pairs && tid == 0 && pacc)
@@ -590,16 +590,6 @@ __device__ __forceinline__ void wave_sync() {
 template <int CTRL, int ROWS>
 __device__ __forceinline__ int dpp_from(int identity, int v) {
     return __builtin_amdgcn_update_dpp(identity, v, CTRL, ROWS, 0xf, false);
-}
-__device__ __forceinline__ float dpp_wave_max(float x) {
-    const int id = __float_as_int(-INFINITY);
-    x = fmaxf(x, __int_as_float(dpp_from<0xB1, 0xf>(id, __float_as_int(x))));
-    x = fmaxf(x, __int_as_float(dpp_from<0x4E, 0xf>(id, __float_as_int(x))));
-    x = fmaxf(x, __int_as_float(dpp_from<0x141, 0xf>(id, __float_as_int(x))));
-    x = fmaxf(x, __int_as_float(dpp_from<0x140, 0xf>(id, __float_as_int(x))));
-    x = fmaxf(x, __int_as_float(dpp_from<0x142, 0xa>(id, __float_as_int(x))));
-    x = fmaxf(x, __int_as_float(dpp_from<0x143, 0xc>(id, __float_as_int(x))));
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
 }
 __device__ __forceinline__ int dpp_wave_sum(int x) {
     x += dpp_from<0xB1, 0xf>(0, x);
@@ -881,7 +871,6 @@ void k_thresh_select(ThreshArgs a) {
 // to a power of two so that the bitonic sorts can pad in place.
 // Four waves per SIMD: the FP64 recomputations load 16 values per row at a
 // time (latency), which needs more than the registers of six.
-template <bool LISTED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FIN_WPE)))
 void k_thresh_final(ThreshArgs a, int capT, int capP) {
     extern __shared__ float smem[];
@@ -898,8 +887,7 @@ void k_thresh_final(ThreshArgs a, int capT, int capP) {
     int *cidx = reinterpret_cast<int *>(hi + capP);
     __shared__ float Lstar[FIN_WAVES];
     __shared__ int nsurv[FIN_WAVES];
-    constexpr bool listed = LISTED;
-    const int64_t nlist = listed ? (int64_t)*a.ulist_cnt : a.n;
+    const int64_t nlist = (int64_t)*a.ulist_cnt;
     unsigned long long *cs = a.cstats ? a.cstats + (blockIdx.x & (CSTAT_SLOTS - 1)) * 4 : nullptr;
     // statistics of this wave's users (candidates, recomputed), added to
     // the counters once at the end
@@ -908,7 +896,7 @@ void k_thresh_final(ThreshArgs a, int capT, int capP) {
     for (int64_t b0 = (int64_t)blockIdx.x * nw; b0 < nlist; b0 += (int64_t)gridDim.x * nw) {
         const int64_t pos = b0 + w;
         const bool valid = pos < nlist;
-        const int64_t u = valid ? (listed ? (int64_t)a.ulist[pos] : pos) : 0;
+        const int64_t u = valid ? (int64_t)a.ulist[pos] : 0;
         // the split counts, one per lane (nsplit <= 64), and their sums;
         // stored entries are laid out split after split
         int cl = 0;
@@ -1230,14 +1218,13 @@ __device__ __forceinline__ bool rows_vec(const float *U, const float *P, int d) 
 // one of rank tgt in the order (value desc, id asc) is tau_u.  2M users x 200
 // with one value each 0.66 ms (8 lanes and their own loads per user: 1.45 ms).
 constexpr int EXACT_WAVES = 2;  // per workgroup (LDS: 24 KB per wave)
-template <bool LISTED>
 __global__ __launch_bounds__(64 * EXACT_WAVES) void k_thresh_exact(ThreshArgs a) {
     __shared__ __align__(16) float sp_s[EXACT_WAVES][XB_FLOATS], su_s[EXACT_WAVES][XB_FLOATS];
     __shared__ double val_s[EXACT_WAVES][64 * EXACT_SLOTS];
     __shared__ int id_s[EXACT_WAVES][64 * EXACT_SLOTS];
     __shared__ uint8_t own_s[EXACT_WAVES][64 * EXACT_SLOTS];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int64_t nlist = LISTED ? (int64_t)*a.ulist_cnt : a.n;
+    const int64_t nlist = (int64_t)*a.ulist_cnt;
     const int64_t capU = (int64_t)a.nsplit * a.cap;
     double *val = val_s[w];
     int *ids = id_s[w];
@@ -1248,7 +1235,7 @@ __global__ __launch_bounds__(64 * EXACT_WAVES) void k_thresh_exact(ThreshArgs a)
         const int64_t pos = b0 + lane;
         int u = 0, meta = -1;
         if (pos < nlist) {
-            u = LISTED ? a.ulist[pos] : (int)pos;
+            u = a.ulist[pos];
             meta = a.cand_cnt[(int64_t)u * a.nsplit];
         }
         // (longer lists are k_thresh_exact_wide's)
@@ -1361,7 +1348,6 @@ __device__ __forceinline__ void wave_rank64(const uint64_t (&r)[J], const int (&
 // (at most 64 users at a time) and takes the wide ones in turn.  500k users x
 // 100 with 156 values each 3.7 ms (each lane its own loads, the rank by rounds
 // of maxima: 6.9 ms).
-template <bool LISTED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
 void k_thresh_exact_wide(ThreshArgs a) {
     __shared__ __align__(16) float sp_s[4][XB_FLOATS];
@@ -1369,7 +1355,7 @@ void k_thresh_exact_wide(ThreshArgs a) {
     __shared__ double topv_s[4][KMAX];
     __shared__ int topi_s[4][KMAX];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int64_t nlist = LISTED ? (int64_t)*a.ulist_cnt : a.n;
+    const int64_t nlist = (int64_t)*a.ulist_cnt;
     const int64_t capU = (int64_t)a.nsplit * a.cap;
     float *ul = urow_s[w], *sp = sp_s[w];
     const bool vec = rows_vec(a.U, a.P, a.d);
@@ -1381,7 +1367,7 @@ void k_thresh_exact_wide(ThreshArgs a) {
         const int64_t pos = c0 + lane;
         int myu = 0, meta = -1;
         if (lane < per && pos < nlist) {
-            myu = LISTED ? a.ulist[pos] : (int)pos;
+            myu = a.ulist[pos];
             meta = a.cand_cnt[(int64_t)myu * a.nsplit];
         }
         uint64_t wide = __ballot(meta >= 0 && (meta >> 8) > a.wide_from);
@@ -1650,7 +1636,7 @@ void launch_thresh(const ThreshArgs &a0, hipStream_t st) {
             else select(std::integral_constant<int, SEL_MAX>{});
         } else {
             RMIPS_PROF(st, nf);
-            k_thresh_final<true><<<(unsigned)fblocks, 64 * fw, lds_fin, st>>>(h, capT, capP);
+            k_thresh_final<<<(unsigned)fblocks, 64 * fw, lds_fin, st>>>(h, capT, capP);
         }
         // A launch costs about 5 us whatever it does.  The refinement passes'
         // lists are empty or hold many values, and up to 4096 users find a
@@ -1659,10 +1645,10 @@ void launch_thresh(const ThreshArgs &a0, hipStream_t st) {
         h.wide_from = a.n <= 4 * wblocks_max || ne == nullptr ? 0 : EXACT_SLOTS;
         if (h.wide_from > 0) {
             RMIPS_PROF(st, ne);
-            k_thresh_exact<true><<<(unsigned)eblocks, 64 * EXACT_WAVES, 0, st>>>(h);
+            k_thresh_exact<<<(unsigned)eblocks, 64 * EXACT_WAVES, 0, st>>>(h);
         }
         RMIPS_PROF(st, nw);
-        k_thresh_exact_wide<true><<<(unsigned)wblocks, 256, 0, st>>>(h);
+        k_thresh_exact_wide<<<(unsigned)wblocks, 256, 0, st>>>(h);
     };
     // bounds-only pass (the launch without a user list): every user's L0
     // from the first tiles (phase 1), in workgroups of its own size
