@@ -5,16 +5,18 @@ Cauchy-Schwarz and Eq. (3) bounds, bound-ordered exact scoring, top-N).
 The default workload is the largest one that runs on one GPU, at the scale
 of the paper's Amazon-Movie data: n = 2,000,000 users (64-cluster
 directions), m = 100,000 items, d = 200, k = 10, N = 100, seed 3, synthetic
-vectors resident in HBM before the timed region.  `value` is the plain FP32
-path; the BF16- and FP8-screened paths run on the same inputs as variants
-whose top-N must be identical.  Metric: G user-item pairs per second,
-n * m / (seconds per step) / 1e9.
+vectors resident in HBM before the timed region.  `value` is the path with
+FP32 screening (from d = 32 on its products are formed from two FP16 parts
+per value, with FP32 sums); the BF16-, FP8- and FP6-screened paths run on the
+same inputs as variants whose top-N must be identical.  Metric: G user-item
+pairs per second, n * m / (seconds per step) / 1e9.
 
-Every kernel launch of the timed steps is bracketed by HIP events on the
-library's stream (rmips_set_profiling); the kernel with the largest total
-time is the one the roofline entry describes.
+The timed steps hold nothing but the calls.  As many further steps then have
+every kernel launch bracketed by HIP events on the library's stream
+(rmips_set_profiling); the kernel with the largest total time there is the one
+the roofline entry describes.
 
-Prints one JSON line.  --gpus above 1 is not supported: this build runs on
+Prints one JSON line on stdout; the whole per-kernel tables go to stderr.  --gpus above 1 is not supported: this build runs on
 one GPU (the path shards by users only in design).
 """
 import argparse
@@ -226,6 +228,44 @@ def run_topn(rm, Ug, Pg, k, N, prec, ws, steps, warmup, profile=False):
     return ids, sc, stats, dt, prof, pstats
 
 
+def result_line(out):
+    """The result as one JSON line of a few KB, whatever the number of kernels
+    and variants (a longer one is cut by readers of the output's tail): numbers
+    to six digits, of each per-kernel table the kernels of at least 1% of the
+    step with their launches, time and share of the roofline, and of a variant
+    no table."""
+    def short(x):
+        if isinstance(x, dict):
+            return {a: short(b) for a, b in x.items()}
+        if isinstance(x, (list, tuple)):
+            return [short(b) for b in x]
+        return float(f"{x:.6g}") if isinstance(x, float) else x
+
+    line = dict(out)
+    if "kernels" in line:
+        total = sum(e["ms_per_step"] for e in line["kernels"].values())
+        line["kernels"] = {a: {f: e[f] for f in ("launches_per_step", "ms_per_step", "frac") if f in e}
+                           for a, e in line["kernels"].items() if e["ms_per_step"] >= 0.01 * total}
+    if "variants" in line:
+        line["variants"] = {a: {f: b for f, b in v.items() if f != "kernels"}
+                            for a, v in line["variants"].items()}
+    if "table4" in line:
+        line["table4"] = {a: {f: b for f, b in v.items() if f not in ("kernels", "build_kernels")}
+                          for a, v in line["table4"].items()}
+    return json.dumps(short(line), separators=(",", ":"))
+
+
+def emit(out):
+    """The result line on stdout; the whole per-kernel tables on stderr."""
+    tables = {"": out, **out.get("variants", {}), **out.get("table4", {})}
+    for name, t in tables.items():
+        for key in ("kernels", "build_kernels"):
+            if key in t:
+                print(f"[bench] {key} {name or out['dtype']}: {json.dumps(t[key])}", file=sys.stderr,
+                      flush=True)
+    print(result_line(out), flush=True)
+
+
 def kernel_table(prof, stats, steps, n, m, d, k, prec):
     """Per kernel: launches and ms per step, and where the algorithmic work
     of a launch is defined (units of the hot path, never the hardware's
@@ -394,6 +434,7 @@ def main():
         "warmup": args.warmup, "ms_per_step": ms, "higher_is_better": True,
         "scaling": "weak", "vs_baseline": None, "dtype": prec, "data": "synthetic",
         "config": {"workload": workload, "screening": prec,
+                   "products": "2 x fp16 per value" if prec == "fp32" and d >= 32 else prec,
                    "n": n, "m": m, "d": d, "k": k, "N": N, "parallelism": "single GPU"},
         "roofline": roofline,
         "seconds_per_step": ms / 1e3,
@@ -422,7 +463,7 @@ def main():
     if not args.no_cpu_baseline:
         print("[bench] cpu baseline", file=sys.stderr, flush=True)
         out["cpu_baseline"] = cpu_baseline(cfg, U, P, k, args.cpu_seconds)
-    print(json.dumps(out), flush=True)
+    emit(out)
 
 
 def bench_soft(args, cfg):
@@ -517,7 +558,7 @@ def bench_soft(args, cfg):
                    "S_mean_end": float(s_end.double().mean()),
                    "max_norm_end": float(q.norm(dim=1).max()), "radius": R},
     }
-    print(json.dumps(out), flush=True)
+    emit(out)
 
 
 def bench_budget(args, cfg):
@@ -596,7 +637,7 @@ def bench_budget(args, cfg):
         "same_top_n": len(heads) == 1,
         "table4": table,
     }
-    print(json.dumps(out), flush=True)
+    emit(out)
 
 
 if __name__ == "__main__":

@@ -50,3 +50,32 @@ def test_selection_work_under_either_name():
     t = bench.kernel_table(prof, _stats(0, 0, 0.0), 1, n, m, d, 10, "fp8")
     assert t["k_thresh_select/main"]["work_per_launch"] == 12.0 * (1.0e6 + n) / 2
     assert t["k_thresh_final/main"]["work_per_launch"] == 12.0 * (1.0e6 + n)
+
+
+def test_result_line_is_short():
+    # forty kernels in the table and in each of four variants: one JSON line of
+    # less than 6 KB with the contract's keys, values to six digits
+    import json
+    k = {f"k_some_long_kernel_name_{i}/main": {
+        "launches_per_step": 1.0 / 3, "ms_per_step": 10.0 / (i + 3), "ms_per_launch": 1.0 / 7,
+        "bound": "mfma", "unit_work": "flop", "work_per_launch": 1e12 / 3, "achieved": 1e3 / 3,
+        "peak": 2500.0, "rate_unit": "TFLOP/s", "frac": 1.0 / 3} for i in range(40)}
+    out = {"metric": "m", "value": 2576.123456789, "unit": "G pairs/s", "n_gpus": 1, "steps": 20,
+           "warmup": 5, "ms_per_step": 77.6 / 3, "higher_is_better": True, "scaling": "weak",
+           "vs_baseline": None, "dtype": "fp32", "data": "synthetic", "config": {"n": 2000000},
+           "kernels": k, "paper_context": "x" * 300, "top_ids": list(range(10 ** 5, 10 ** 5 + 20)),
+           "variants": {v: {"ms_per_step": 1 / 3, "value": 2e3 / 3, "same_top_n": True, "kernels": k,
+                            "dominant_kernel": "k_thresh_screen/main", "dominant_frac": 1 / 3,
+                            "recheck_pairs": 1e8 / 3, "cand_listed": 1e8 / 3, "cand_pairs": 1e7 / 3,
+                            "refine_users": 0.0} for v in ("bf16", "fp8", "fp6", "fp4")}}
+    line = bench.result_line(out)
+    assert "\n" not in line and len(line) < 6000
+    got = json.loads(line)
+    for key in ("metric", "unit", "n_gpus", "steps", "warmup", "higher_is_better", "scaling",
+                "vs_baseline", "dtype", "data", "config"):
+        assert got[key] == out[key]
+    assert abs(got["value"] - out["value"]) <= 1e-5 * out["value"]
+    assert abs(got["ms_per_step"] - out["ms_per_step"]) <= 1e-5 * out["ms_per_step"]
+    assert got["variants"]["fp8"]["same_top_n"] and "kernels" not in got["variants"]["fp8"]
+    top = max(k, key=lambda a: k[a]["ms_per_step"])
+    assert got["kernels"][top]["ms_per_step"] == 3.33333
