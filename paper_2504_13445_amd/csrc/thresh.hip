@@ -200,8 +200,9 @@ void k_thresh_screen(ThreshArgs a) {
         load_half_row<NCH>(ub, reinterpret_cast<const uint8_t *>(a.Uq), ug, uvalid, rowb, nch,
                            lane);
         // all values and bounds of a user are taken in units of its scale, a
-        // power of two (the same bits, and rows of any magnitude stay in range)
-        const float su = uvalid ? a.su[ug] : 1.0f, su_inv = pow2_rcp(su);
+        // power of two (the same bits, and rows of any magnitude stay in range);
+        // unscaled formats: 1
+        const float su = scaled_prec(PREC) && uvalid ? a.su[ug] : 1.0f, su_inv = pow2_rcp(su);
         const float nu = uvalid ? a.Nu[ug] * su_inv : 0.0f;
         const float nhu = uvalid ? a.Nhu[ug] * su_inv : 0.0f;
         const float ru = uvalid ? a.Ru[ug] * su_inv : 0.0f;
@@ -268,7 +269,7 @@ void k_thresh_screen(ThreshArgs a) {
                 const float *Nsh = Nbase + buf * NSTRIDE;
                 const int64_t rb = (int64_t)t * TILE_ITEMS;
                 const float e_t = ebound(Nsh[0], Nsh[3 * TILE_ITEMS], Nsh[3 * TILE_ITEMS + 1]);
-                const float sc = Nsh[3 * TILE_ITEMS + 2];
+                const float sc = scaled_prec(PREC) ? Nsh[3 * TILE_ITEMS + 2] : 1.0f;
                 f32x16 acc0 = {0}, acc1 = {0};
                 MMR<PREC, NCH>::rows2(acc0, acc1, Psh, Psh + 32 * ls, ub, ls, nch, D, (a.d + 1) / 2, lane);
 #pragma unroll
@@ -320,7 +321,7 @@ void k_thresh_screen(ThreshArgs a) {
             const int64_t rb = (int64_t)t * TILE_ITEMS;
             // tile maxima: N is sorted (first item), Nh and R staged with the tile
             const float e_t = ebound(Nsh[0], Nsh[3 * TILE_ITEMS], Nsh[3 * TILE_ITEMS + 1]);
-            const float sp_t = Nsh[3 * TILE_ITEMS + 2];
+            const float sp_t = scaled_prec(PREC) ? Nsh[3 * TILE_ITEMS + 2] : 1.0f;
             f32x16 acc0 = {0}, acc1 = {0};
             MMR<PREC, NCH>::rows2(acc0, acc1, Psh, Psh + 32 * ls, ub, ls, nch, D, (a.d + 1) / 2, lane);
             // first on the tile bound, then per item; the tile's scale is a power
@@ -429,7 +430,7 @@ void k_thresh_screen_u2(ThreshArgs a) {
             const int64_t pos = blk * TU + w * 64 + 32 * h + (lane & 31);
             uvalid[h] = pos < nlist;
             ug[h] = uvalid[h] ? (int64_t)a.ulist[pos] : 0;
-            su[h] = uvalid[h] ? a.su[ug[h]] : 1.0f;
+            su[h] = scaled_prec(PREC) && uvalid[h] ? a.su[ug[h]] : 1.0f;
             const float su_inv = pow2_rcp(su[h]);
             nu[h] = uvalid[h] ? a.Nu[ug[h]] * su_inv : 0.0f;
             nhu[h] = uvalid[h] ? a.Nhu[ug[h]] * su_inv : 0.0f;
@@ -477,7 +478,7 @@ void k_thresh_screen_u2(ThreshArgs a) {
                 tile_copy<NW>(a, tn, rowb, w16, magic, ls, Pbase, Nbase, buf ^ 1, w, lane);
             const uint8_t *Psh = Pbase + buf * bstride;
             const int64_t rb = (int64_t)t * TILE_ITEMS;
-            const float sp_t = Nsh[3 * TILE_ITEMS + 2];
+            const float sp_t = scaled_prec(PREC) ? Nsh[3 * TILE_ITEMS + 2] : 1.0f;
             f32x16 acc[2][2];
 #pragma unroll
             for (int h = 0; h < 2; ++h) acc[h][0] = acc[h][1] = f32x16{0};
