@@ -36,14 +36,19 @@ __host__ __device__ constexpr float mx_max(int prec) {
     return prec == PREC_FP6 ? 7.5f : prec == PREC_FP4 ? 6.0f : prec == PREC_SPLIT ? 0x1p15f : 448.0f;
 }
 // FP32 screening of rows of at least SPLIT_MIN_D values multiplies x = hi + lo
-// in FP16 (22 bits and more of each value, exact products, FP32 sums):
-// hi hi + hi lo + lo hi, three v_mfma_f32_32x32x16_f16 per 16 terms where the
-// FP32 matrix step takes eight of twice the time.  Measured against FP64 over
-// normal, shifted and positive rows (512 x 512 pairs, relative to |u||p|):
-// d = 32 rms 1.67e-8 (FP32 steps: 1.82e-8), d = 96 1.33e-8 (1.81e-8), d = 208
-// 1.20e-8 (1.80e-8); positive rows at d = 208 7.7e-8 (1.31e-7), the largest
-// errors in the same proportion.  At d = 16 it is larger than the FP32 steps'
-// (2.08e-8 against 1.84e-8), so shorter rows keep those.
+// in FP16 (exact products, FP32 sums): hi hi + hi lo + lo hi, three
+// v_mfma_f32_32x32x16_f16 per 16 terms where the FP32 matrix step takes eight of
+// twice the time.  hi + lo keeps 22 bits of a value down to 2^-18 of the largest
+// one that shares its scale (a user's row, a tile's 64 items), 11 bits down to
+// 2^-29 and nothing below; what is lost is in the row's R and so in the bound,
+// whose constant for the sum is three times that of the FP32 steps plus 2^-22.
+// Measured against FP64 on catalogues with log-normal norms (sigma 0.3 to 0.8,
+// tiles in norm order; isotropic and clustered users; d = 32 to 256; 512 x 512
+// pairs each, relative to |u||p|) both the rms and the largest error are below
+// the FP32 steps' in all 114 sets: rms 1.66e-8 to 1.77e-8 at d = 32 and 33 (FP32
+// steps 1.80e-8 to 1.84e-8), 1.32e-8 (1.80e-8) at d = 96, 1.21e-8 (1.80e-8) at
+// d = 200; largest 0.97e-7 to 1.86e-7 (1.56e-7 to 3.0e-7).  At d = 16 the rms is
+// larger (2.08e-8 against 1.84e-8), so shorter rows keep the FP32 steps.
 constexpr int SPLIT_MIN_D = 32;
 __host__ __device__ constexpr int screen_prec(int prec, int d) {
     return prec == PREC_FP32 && d >= SPLIT_MIN_D ? PREC_SPLIT : prec;

@@ -961,10 +961,9 @@ void k_thresh_final(ThreshArgs a, int capT, int capP) {
             }
         }
         wave_sync();
-        // L* = k-th largest lower bound: by ranks for short lists, else by
-        // rounds of the largest value below the previous round's, counted
-        // with its repetitions, until k values are reached (the list stays
-        // in place, paired with the upper bounds and ids)
+        // L* = k-th largest lower bound: by ranks for short lists, else bit by
+        // bit (wave_kth_largest; the list stays in place, paired with the upper
+        // bounds and ids)
         if (valid && stored <= capT) {
             if (stored <= 128) {
                 for (int e = lane; e < stored; e += 64) {
