@@ -696,10 +696,10 @@ __device__ float wave_kth_largest(const float *x, int n, int k, int lane) {
 // list in registers (J entries per lane) from its load to the ids left for
 // the recomputation, so that no LDS limits the waves in flight.  Latency and
 // the selection's instructions bound it: 500k users, e4m3 lists of 241
-// entries 1.6 ms (lists of 429 2.5 ms; in LDS, by rounds of the next largest:
-// 9.9 ms); BF16 lists of 27 entries 0.44 ms, 2M users with lists of 11 1.17 ms
-// (0.72 and 2.0 ms), of which reading the counts two users and the entries one
-// user ahead is 0.03 and 0.2 ms.
+// entries 1.3 ms (1.6 with four workgroups to a CU; lists of 429 2.5 ms then,
+// and 9.9 ms in LDS by rounds of the next largest); BF16 lists of 27 entries
+// 0.44 ms, 2M users with lists of 11 1.17 ms (0.72 and 2.0 ms), of which reading
+// the counts two users and the entries one user ahead is 0.03 and 0.2 ms.
 constexpr int SEL_MAX = 2048;
 // lists up to SEL_SHORT leave registers for four waves per SIMD (118), up to
 // SEL_MID for three (166 of 168), longer ones for two; a launch is one round of
